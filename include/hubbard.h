@@ -177,8 +177,8 @@ hub_status hub_matvec(const hub_sector *sec, int32_t dtype, const void *dev_x, v
 /*
  * Product schedule: which kernel applies the Kronecker sum of Sec. IV A and
  * with what tile shape.  Every schedule computes each element of y with the
- * same operations in the same order (diagonal, H_up entries in column order,
- * H_dn entries in column order, one fused multiply-add each), so the choice
+ * same operations in the same order (H_dn entries in column order, diagonal,
+ * H_up entries in column order, one fused multiply-add each), so the choice
  * never changes a result.
  *
  *   HUB_SCHED_COLUMNS  whole columns of V staged in LDS, four rows per lane
@@ -208,7 +208,8 @@ typedef struct hub_schedule {
     int32_t family;          /* HUB_SCHED_* (AUTO in hub_get_schedule: not chosen yet) */
     int32_t tile_cols;       /* COLUMNS: 1..3; CHUNKED: 1, 2 or 4 columns per workgroup */
     int32_t block;           /* COLUMNS: 512 or 1024 lanes per workgroup (CHUNKED: 1024) */
-    int32_t order;           /* COLUMNS: 1 = XCD-contiguous tiles, 0 = launch order */
+    int32_t order;           /* COLUMNS: 1 = XCD-contiguous tiles, 0 = launch order;
+                                COLUMNS and CHUNKED: 2 = the H_dn term by a pass of its own */
     int32_t quads_per_lane;  /* CHUNKED: 4 or 8 (a work item covers 4096 * quads_per_lane rows);
                                 tile_cols * quads_per_lane <= 16 (FP32) or 8 (FP64) */
     int32_t chunk_rows;      /* CHUNKED: rows per staged chunk (0 = as many as fit; multiple of 4) */

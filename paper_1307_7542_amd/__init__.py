@@ -272,7 +272,7 @@ class Sector:
             _check(lib().hub_set_schedule(self._h, dtype, None), "hub_set_schedule")
             return
         if family == SCHED_CHUNKED:
-            order, block = 0, 1024
+            order, block = (2 if order == 2 else 0), 1024
         sc = Schedule(family, tile_cols, block, order, quads_per_lane, chunk_rows, int(no_fused_update), 0.0)
         _check(lib().hub_set_schedule(self._h, dtype, ctypes.byref(sc)), "hub_set_schedule")
 

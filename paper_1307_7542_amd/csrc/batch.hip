@@ -106,8 +106,8 @@ __device__ __forceinline__ double binv(double b) { return b > 0.0 ? 1.0 / b : 0.
 // in flight together (loads unconditional: a position past the end, or an
 // entry past its row's length, re-reads a valid one and only the update is
 // selected).  Every element is formed as in the single-sector product
-// (diagonal, then the H_up entries in sliced-ELL order, then the H_dn entries
-// in CSR order, one fused multiply-add each): the two agree bit for bit.
+// (the H_dn entries in CSR order, then the diagonal, then the H_up entries in
+// sliced-ELL order, one fused multiply-add each): the two agree bit for bit.
 // SEL (the Lanczos step): x = u_k and y = w from the pointer table at the device
 // step counter, and the first update fused in: w = (H u_k) / beta_k -
 // (beta_k / beta_{k-1}) u_{k-1}, evaluated in FP64 and rounded once, and this
@@ -183,38 +183,8 @@ __global__ __launch_bounds__(BS) void k_batch_kron(const BDesc<T> *__restrict__ 
             const int f = (f0 + j * BS < F) ? f0 + j * BS : f0;
             rg[j] = (int)(((uint64_t)(uint32_t)f * D.cu_magic) >> 32);
             ra[j] = f - rg[j] * cu;
-            const uint32_t ub = D.up_basis[ra[j]];
-            const T eu = D.e_up[ra[j]];
 #pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const int c = min(rg[j] * TB + t, ncol - 1);
-                acc[j][t] = (bdiag(D, ub & ldnb[c]) + eu + ledn[c]) * xs[f * TB + t];
-            }
-        }
-        // H_up: entry k of row a at ell[64 sl_off[a / 64] + a % 64 + 64 k]
-        int eo[R], el_n[R], lmax = 0;
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int s = ra[j] >> 6;
-            eo[j] = D.sl_off[s] * 64 + (ra[j] & 63);
-            el_n[j] = D.sl_off[s + 1] - D.sl_off[s];
-            lmax = max(lmax, el_n[j]);
-        }
-        for (int k = 0; k < lmax; ++k) {
-            uint32_t c[R];
-#pragma unroll
-            for (int j = 0; j < R; ++j) c[j] = D.ell[el_n[j] > 0 ? eo[j] + 64 * min(k, el_n[j] - 1) : 0];
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const T v = tab[c[j] >> 24];
-                const BVec<T, TB> xv =
-                    *reinterpret_cast<const BVec<T, TB> *>(xs + (rg[j] * cu + (int)(c[j] & 0xFFFFFFu)) * TB);
-#pragma unroll
-                for (int t = 0; t < TB; ++t) {
-                    const T f = fma(v, xv.v[t], acc[j][t]);
-                    acc[j][t] = (k < el_n[j]) ? f : acc[j][t];
-                }
-            }
+            for (int t = 0; t < TB; ++t) acc[j][t] = (T)0;
         }
         // H_dn: the row of each column's CSR (from LDS), neighbour columns read
         // from the vector
@@ -245,6 +215,42 @@ __global__ __launch_bounds__(BS) void k_batch_kron(const BDesc<T> *__restrict__ 
                     const T f = fma(w[j][t], xv[j][t], acc[j][t]);
                     acc[j][t] = (u < dn[j][t]) ? f : acc[j][t];
                 }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int f = (f0 + j * BS < F) ? f0 + j * BS : f0;
+            const uint32_t ub = D.up_basis[ra[j]];
+            const T eu = D.e_up[ra[j]];
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                const int c = min(rg[j] * TB + t, ncol - 1);
+                acc[j][t] = fma(bdiag(D, ub & ldnb[c]) + eu + ledn[c], xs[f * TB + t], acc[j][t]);
+            }
+        }
+        // H_up: entry k of row a at ell[64 sl_off[a / 64] + a % 64 + 64 k]
+        int eo[R], el_n[R], lmax = 0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int s = ra[j] >> 6;
+            eo[j] = D.sl_off[s] * 64 + (ra[j] & 63);
+            el_n[j] = D.sl_off[s + 1] - D.sl_off[s];
+            lmax = max(lmax, el_n[j]);
+        }
+        for (int k = 0; k < lmax; ++k) {
+            uint32_t c[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) c[j] = D.ell[el_n[j] > 0 ? eo[j] + 64 * min(k, el_n[j] - 1) : 0];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const T v = tab[c[j] >> 24];
+                const BVec<T, TB> xv =
+                    *reinterpret_cast<const BVec<T, TB> *>(xs + (rg[j] * cu + (int)(c[j] & 0xFFFFFFu)) * TB);
+#pragma unroll
+                for (int t = 0; t < TB; ++t) {
+                    const T f = fma(v, xv.v[t], acc[j][t]);
+                    acc[j][t] = (k < el_n[j]) ? f : acc[j][t];
+                }
+            }
         }
 #pragma unroll
         for (int j = 0; j < R; ++j) {

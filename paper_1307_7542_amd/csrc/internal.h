@@ -19,6 +19,17 @@ constexpr int kBinomN = 33;  // binomial table C[n][k], 0 <= n, k <= 32
 
 void set_error(const std::string &msg);
 
+// Place in LDS of row a of n staged rows in the kernels whose lanes own four
+// consecutive rows (of n rounded up to a multiple of 4 places): groups of 256 rows are stored transposed (4 x
+// 64), so that 64 lanes that gather at a stride of four rows, which is what a
+// hop that shifts whole runs of basis states makes them do, touch consecutive
+// words instead of every fourth (or, two columns interleaved, every eighth) bank.
+__host__ __device__ inline int lds_slot(int a, int n)
+{
+    const int g = a & ~255, left = n - g, w = left < 256 ? left : 256;
+    return g + (a & 3) * ((w + 3) >> 2) + ((a - g) >> 2);
+}
+
 // Device tables of one spin sector (Sec. II: basis; Sec. IV A: H_sigma in CSR).
 struct SpinTables {
     int N = 0;
@@ -48,6 +59,7 @@ struct SpinTables {
     // code = 2*bond + (esign < 0) and code 255 = padding (value 0).  Built when
     // count < 2^24 and the sector has at most 127 bonds.
     uint32_t *ell_c32 = nullptr;
+    uint32_t *ell_q32 = nullptr;  // the same with lds_slot(column) for the column (four-row kernels)
     double *code_v64 = nullptr;  // [256]
     float *code_v32 = nullptr;   // [256]
 };
@@ -83,15 +95,15 @@ struct K0Tables {
 // Compact entries of H_sigma split by column chunk (for products whose staged
 // data covers one chunk of columns at a time): chunk p holds, for every row,
 // the entries whose column lies in [p rows, (p+1) rows) -- a contiguous
-// sub-range of the sorted CSR row -- with columns relative to the chunk, in the
-// sliced-ELL layout (slice offsets in units of 64 entries).
+// sub-range of the sorted CSR row -- with the columns' places in the staged
+// chunk (lds_slot), in the sliced-ELL layout (slice offsets in units of 64 entries).
 struct ChunkSet {
     int spin = 0;
     int rows = 0;               // columns per chunk
     int n = 0;                  // chunks
     int32_t *off = nullptr;     // [n * (nslices + 1)]
     int64_t *base = nullptr;    // [n] first entry of chunk p
-    uint32_t *ell = nullptr;    // entries {column - p rows : 24, code : 8}
+    uint32_t *ell = nullptr;    // entries {lds_slot(column - p rows) : 24, code : 8}
 };
 
 // Product schedule (see hub_schedule in hubbard.h): fam 0 = not chosen yet.

@@ -16,13 +16,17 @@
 //             reads its neighbour columns through L2 / MALL.
 //   chunked   columns larger than the LDS (k_kron_chunked_parts): the columns
 //             are staged chunk by chunk while the output rows stay in registers.
+//   (order 2 of both: the H_dn term in a pass of its own, k_dn_rows, which
+//   leaves it in y; the column kernel then starts from y.)
 //   rows      one row per lane (k_kron_fused), for count_up % 4 != 0 or
 //             vectors that are not 16-byte aligned.
 //   csr       rows of the CSR gathered from global memory (no compact entries).
 //
-// Every schedule computes each element as: diagonal, then the H_up entries in
-// column order, then the H_dn entries in column order, one fused multiply-add
-// per term, so all give bit-identical products (tested).
+// Every schedule computes each element as: the H_dn entries in column order,
+// then the diagonal, then the H_up entries in column order, one fused
+// multiply-add per term from zero, so all give bit-identical products (tested):
+// the H_dn term first, because it may then come from its own pass through y
+// while the column kernel keeps the diagonal, the H_up term and the epilogue.
 //
 // H_up is read from its sliced-ELL copy: lane r of a wavefront owns row
 // 64*s + r of slice s and loads entry k from a coalesced address; the default
@@ -62,6 +66,10 @@ struct MvArgs {
     uint32_t umask;
     int32_t stream;  // vectors beyond the MALL: data read or written once bypasses retention (k_kron_quad)
 };
+
+// one fused multiply-add, a * b + c
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <typename T>
 using Pk = typename std::conditional<sizeof(T) == 8, uint4, uint2>::type;
@@ -115,10 +123,10 @@ __device__ __forceinline__ void up_term(T (&acc)[TB], const T *xs, const Pk<T> *
         const Vec<T, TB> x3 = *reinterpret_cast<const Vec<T, TB> *>(xs + c3 * TB);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
-            acc[t] += v0 * x0.v[t];
-            acc[t] += v1 * x1.v[t];
-            acc[t] += v2 * x2.v[t];
-            acc[t] += v3 * x3.v[t];
+            acc[t] = mad(v0, x0.v[t], acc[t]);
+            acc[t] = mad(v1, x1.v[t], acc[t]);
+            acc[t] = mad(v2, x2.v[t], acc[t]);
+            acc[t] = mad(v3, x3.v[t], acc[t]);
         }
     }
     for (; k < len; ++k) {
@@ -127,7 +135,7 @@ __device__ __forceinline__ void up_term(T (&acc)[TB], const T *xs, const Pk<T> *
         unpack(ell[o0 + 64 * k], c0, v0);
         const Vec<T, TB> x0 = *reinterpret_cast<const Vec<T, TB> *>(xs + c0 * TB);
 #pragma unroll
-        for (int t = 0; t < TB; ++t) acc[t] += v0 * x0.v[t];
+        for (int t = 0; t < TB; ++t) acc[t] = mad(v0, x0.v[t], acc[t]);
     }
 }
 
@@ -148,10 +156,10 @@ __device__ __forceinline__ void up_term_c(T (&acc)[TB], const T *xs, const T *ta
         const Vec<T, TB> x3 = *reinterpret_cast<const Vec<T, TB> *>(xs + (e3 & 0xFFFFFFu) * TB);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
-            acc[t] += v0 * x0.v[t];
-            acc[t] += v1 * x1.v[t];
-            acc[t] += v2 * x2.v[t];
-            acc[t] += v3 * x3.v[t];
+            acc[t] = mad(v0, x0.v[t], acc[t]);
+            acc[t] = mad(v1, x1.v[t], acc[t]);
+            acc[t] = mad(v2, x2.v[t], acc[t]);
+            acc[t] = mad(v3, x3.v[t], acc[t]);
         }
     }
     for (; k < len; ++k) {
@@ -159,7 +167,7 @@ __device__ __forceinline__ void up_term_c(T (&acc)[TB], const T *xs, const T *ta
         const T v0 = tab[e0 >> 24];
         const Vec<T, TB> x0 = *reinterpret_cast<const Vec<T, TB> *>(xs + (e0 & 0xFFFFFFu) * TB);
 #pragma unroll
-        for (int t = 0; t < TB; ++t) acc[t] += v0 * x0.v[t];
+        for (int t = 0; t < TB; ++t) acc[t] = mad(v0, x0.v[t], acc[t]);
     }
 }
 
@@ -168,7 +176,7 @@ template <typename T>
 __device__ __forceinline__ void dn_term(T &acc, const MvArgs<T> &A, int ks, int ke, const T *__restrict__ xa)
 {
     const int64_t cu = A.cu;
-    for (int k = ks; k < ke; ++k) acc += A.dn_val[k] * xa[(int64_t)A.dn_col[k] * cu];
+    for (int k = ks; k < ke; ++k) acc = mad(A.dn_val[k], xa[(int64_t)A.dn_col[k] * cu], acc);
 }
 
 // Block -> tile with every XCD (workgroup i runs on XCD i mod 8) owning a
@@ -267,6 +275,137 @@ __device__ __forceinline__ void st_q4(T *p, const T (&v)[4])
     }
 }
 
+// Quads of columns whose length is no multiple of 4: element-aligned 16-byte
+// accesses, and the first nv (1..3) rows alone in a column's last quad.
+template <typename T>
+__device__ __forceinline__ Q4<T> ld_q4e(const T *p, int nv)
+{
+    constexpr int N = 16 / (int)sizeof(T);
+    typedef T VecU __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+    Q4<T> r;
+    if (nv >= 4) {
+#pragma unroll
+        for (int h = 0; h < 4 / N; ++h) {
+            const VecU q = *reinterpret_cast<const VecU *>(p + h * N);
+#pragma unroll
+            for (int i = 0; i < N; ++i) r.v[h * N + i] = q[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.v[i] = i < nv ? p[i] : (T)0;
+    }
+    return r;
+}
+
+template <typename T>
+__device__ __forceinline__ void st_q4e(T *p, const T (&v)[4], int nv)
+{
+    constexpr int N = 16 / (int)sizeof(T);
+    typedef T VecU __attribute__((ext_vector_type(N), aligned(sizeof(T))));
+    if (nv >= 4) {
+#pragma unroll
+        for (int h = 0; h < 4 / N; ++h) {
+            VecU q;
+#pragma unroll
+            for (int i = 0; i < N; ++i) q[i] = v[h * N + i];
+            *reinterpret_cast<VecU *>(p + h * N) = q;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < nv) p[i] = v[i];
+    }
+}
+
+// A quad of a column: RAG columns have cu % 4 != 0 (nv: its rows inside the column)
+template <typename T, bool RAG>
+__device__ __forceinline__ Q4<T> ldq(const T *p, int nv)
+{
+    if constexpr (RAG) return ld_q4e(p, nv);
+    else return ld_q4(p);
+}
+
+template <typename T, bool RAG>
+__device__ __forceinline__ Q4<T> ldq_once(const T *p, int nv, int stream)
+{
+    if constexpr (RAG) return ld_q4e(p, nv);
+    else return stream ? ld_q4_nt(p) : ld_q4(p);
+}
+
+template <typename T, bool RAG>
+__device__ __forceinline__ void stq_once(T *p, const T (&v)[4], int nv, int stream)
+{
+    if constexpr (RAG) st_q4e(p, v, nv);
+    else if (stream) st_q4_nt(p, v);
+    else st_q4(p, v);
+}
+
+// Distance in LDS between the four rows of quad q of nq staged quads (lds_slot)
+__device__ __forceinline__ int quad_pitch(int q, int nq) { return min(64, nq - (q & ~63)); }
+
+// N interleaved columns' values of one row, as one LDS access where N is a power of two
+template <typename T, int N>
+__device__ __forceinline__ Vec<T, N> ld_vec(const T *p)
+{
+    struct alignas((N & (N - 1)) == 0 && sizeof(T) * N <= 16 ? sizeof(T) * N : sizeof(T)) V {
+        Vec<T, N> v;
+    };
+    return reinterpret_cast<const V *>(p)->v;
+}
+
+// Stage quads q0 .. q1-1 of TB columns xb of cu rows, interleaved by column, at their lds_slot
+template <typename T, int TB, bool RAG>
+__device__ __forceinline__ void stage_quads(T *xs, const T *const (&xb)[TB], int q0, int q1, int cu, int bs)
+{
+    struct alignas((TB & (TB - 1)) == 0 && sizeof(T) * TB <= 16 ? sizeof(T) * TB : sizeof(T)) V {
+        Vec<T, TB> v;
+    };
+    for (int q = q0 + threadIdx.x; q < q1; q += bs) {
+        Q4<T> v[TB];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) v[t] = ldq<T, RAG>(xb[t] + 4 * q, cu - 4 * q);
+        const int s0 = lds_slot(4 * (q - q0), 4 * (q1 - q0)), sw = quad_pitch(q - q0, q1 - q0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            V o;
+#pragma unroll
+            for (int t = 0; t < TB; ++t) o.v.v[t] = v[t].v[r];
+            *reinterpret_cast<V *>(xs + (s0 + r * sw) * TB) = o;
+        }
+    }
+}
+
+// acc[r][t] += the H_up entries of a quad's four rows (entry k of the four in
+// e4[16 k]), two entry columns at a time, the next two loaded meanwhile.  Bound
+// by the LDS: two reads an entry, 76 % of the cycles on the 4x4 torus (FP32, two
+// columns; without the next entries' loads 1.24 instead of 1.20 ms a product).
+template <typename T, int TB>
+__device__ __forceinline__ void up_quad(T (&acc)[4][TB], const T *xs, const T *tab, const uint4 *__restrict__ e4,
+                                        int len)
+{
+    auto use = [&](const uint4 &q) {
+        const uint32_t e[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const T v = tab[e[i] >> 24];
+            const Vec<T, TB> xr = ld_vec<T, TB>(xs + (e[i] & 0xFFFFFFu) * TB);
+#pragma unroll
+            for (int t = 0; t < TB; ++t) acc[i][t] = mad(v, xr.v[t], acc[i][t]);
+        }
+    };
+    if (len <= 0) return;
+    uint4 na = e4[0], nb = e4[16 * min(1, len - 1)];
+    int k = 0;
+    for (; k + 2 <= len; k += 2) {
+        const uint4 ea = na, eb = nb;
+        na = e4[16 * min(k + 2, len - 1)];
+        nb = e4[16 * min(k + 3, len - 1)];
+        use(ea);
+        use(eb);
+    }
+    if (k < len) use(na);
+}
+
 // First Lanczos update fused into the product's epilogue: w = (H x) - beta v_prev
 // (rounded as the separate update kernel does) and partial sums of w * x.
 //
@@ -341,7 +480,7 @@ __device__ __forceinline__ T epi_w(const LzEpi<T> &E, const EpiCoef<T> &c, T o, 
 // Lanczos update, each group of 64 lane-quads (256 rows) summed by one
 // wavefront in a fixed order, then the groups of a column in increasing order,
 // so the per-column partials do not depend on the tile shape.
-template <typename T, int TB, int BS, bool XC, bool EPI>
+template <typename T, int TB, int BS, bool XC, bool EPI, bool SPLIT, bool RAG>
 __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__restrict__ sl_off,
                                                   const uint32_t *__restrict__ ellc, const T *__restrict__ code_v,
                                                   int ntiles, LzEpi<T> E)
@@ -349,7 +488,7 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *tab = reinterpret_cast<T *>(smem_raw);  // 256 code values
     T *xs = tab + 256;                         // TB staged columns, interleaved
-    double *gpart = reinterpret_cast<double *>(xs + TB * A.cu);  // EPI: TB x G group partials
+    double *gpart = reinterpret_cast<double *>(xs + TB * ((A.cu + 3) & ~3));  // EPI: TB x G group partials
     int tile;
     if (XC) {
         tile = xcd_tile(ntiles);
@@ -357,17 +496,14 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
         tile = (int)blockIdx.x < ntiles ? (int)blockIdx.x : -1;
     }
     if (tile < 0) return;
-    const int cu = A.cu, cd = A.cd, nq = cu >> 2;
+    const int cu = A.cu, cd = A.cd, nq = (cu + 3) >> 2;
     const int b0 = tile * TB;
     for (int i = threadIdx.x; i < 256; i += BS) tab[i] = code_v[i];
+    {
+        const T *xb[TB];
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-        const T *__restrict__ xb = A.x + (int64_t)min(b0 + t, cd - 1) * cu;
-        for (int q = threadIdx.x; q < nq; q += BS) {
-            const Q4<T> v = ld_q4(xb + 4 * q);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) xs[(4 * q + r) * TB + t] = v.v[r];
-        }
+        for (int t = 0; t < TB; ++t) xb[t] = A.x + (int64_t)min(b0 + t, cd - 1) * cu;
+        stage_quads<T, TB, RAG>(xs, xb, 0, nq, cu, BS);
     }
     __syncthreads();
     int ds[TB], de[TB];
@@ -390,6 +526,8 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     for (int q = threadIdx.x; EPI ? (q - lane < nq) : (q < nq); q += BS) {
         const bool live = !EPI || q < nq;
         const int a0 = 4 * (live ? q : 0);
+        const int s0 = lds_slot(a0, cu), sw = quad_pitch(a0 >> 2, nq);  // rows a0 .. a0+3 at s0 + r sw
+        const int nv = cu - a0;
         T acc[4][TB];
         // the epilogue's v_prev rows are loaded first: a lane runs only one or
         // two iterations, so a load issued after the gathers leaves its latency exposed
@@ -397,66 +535,51 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
         if (EPI && live && E.vprev) {
 #pragma unroll
             for (int t = 0; t < TB; ++t)
-                vpq[t] = A.stream ? ld_q4_nt(E.vprev + (int64_t)min(b0 + t, cd - 1) * cu64 + a0)
-                                  : ld_q4(E.vprev + (int64_t)min(b0 + t, cd - 1) * cu64 + a0);
+                vpq[t] = ldq_once<T, RAG>(E.vprev + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
         }
         const uint4 ub = *reinterpret_cast<const uint4 *>(A.up_basis + a0);
         const uint32_t uu[4] = {ub.x, ub.y, ub.z, ub.w};
         const Q4<T> eu = ld_q4(A.e_up + a0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int t = 0; t < TB; ++t)
-                acc[r][t] = (diag_u(A, uu[r] & dnb[t]) + eu.v[r] + edn[t]) * xs[(a0 + r) * TB + t];
-        // H_up term: entries k of rows a0 .. a0+3 are lanes (a0 & 63) .. +3 of slice a0 >> 6
-        const int s = a0 >> 6;
-        const uint4 *__restrict__ e4 = reinterpret_cast<const uint4 *>(ellc + (int64_t)sl_off[s] * 64 + (a0 & 63));
-        const int len = sl_off[s + 1] - sl_off[s];
-        int k = 0;
-        for (; k + 2 <= len; k += 2) {
-            const uint4 ea = e4[16 * k], eb = e4[16 * (k + 1)];
-            const uint32_t e[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const T v = tab[e[i] >> 24];
-                const T *xr = xs + (e[i] & 0xFFFFFFu) * TB;
-#pragma unroll
-                for (int t = 0; t < TB; ++t) acc[i & 3][t] += v * xr[t];
-            }
-        }
-        if (k < len) {
-            const uint4 ea = e4[16 * k];
-            const uint32_t e[4] = {ea.x, ea.y, ea.z, ea.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const T v = tab[e[i] >> 24];
-                const T *xr = xs + (e[i] & 0xFFFFFFu) * TB;
-#pragma unroll
-                for (int t = 0; t < TB; ++t) acc[i][t] += v * xr[t];
-            }
-        }
-        // H_dn term: whole neighbour columns, four rows per load
+        // H_dn term: from y (SPLIT), else whole neighbour columns, four rows per load
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
+            if (SPLIT) {
+                const Q4<T> v = ldq_once<T, RAG>(A.y + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r][t] = v.v[r];
+                continue;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r][t] = (T)0;
             int kk = ds[t];
             for (; kk + 4 <= de[t]; kk += 4) {
                 Q4<T> v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = ld_q4(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0);
+                for (int u = 0; u < 4; ++u) v[u] = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0, nv);
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const T w = A.dn_val[kk + u];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[r][t] += w * v[u].v[r];
+                    for (int r = 0; r < 4; ++r) acc[r][t] = mad(w, v[u].v[r], acc[r][t]);
                 }
             }
             for (; kk < de[t]; ++kk) {
-                const Q4<T> v = ld_q4(A.x + (int64_t)A.dn_col[kk] * cu64 + a0);
+                const Q4<T> v = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk] * cu64 + a0, nv);
                 const T w = A.dn_val[kk];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r][t] += w * v.v[r];
+                for (int r = 0; r < 4; ++r) acc[r][t] = mad(w, v.v[r], acc[r][t]);
             }
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                acc[r][t] = mad(diag_u(A, uu[r] & dnb[t]) + eu.v[r] + edn[t], xs[(s0 + r * sw) * TB + t], acc[r][t]);
+        // H_up term: entries k of rows a0 .. a0+3 are lanes (a0 & 63) .. +3 of slice a0 >> 6
+        const int s = a0 >> 6;
+        const uint4 *__restrict__ e4 = reinterpret_cast<const uint4 *>(ellc + (int64_t)sl_off[s] * 64 + (a0 & 63));
+        const int len = sl_off[s + 1] - sl_off[s];
+        up_quad<T, TB>(acc, xs, tab, e4, len);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             if (b0 + t >= cd) continue;
@@ -467,15 +590,13 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o[r] = epi_w(E, ec, o[r], E.vprev ? vpq[t].v[r] : (T)0);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) part += (double)o[r] * (double)xs[(a0 + r) * TB + t];
+                    for (int r = 0; r < 4; ++r)
+                        if (!RAG || r < nv) part += (double)o[r] * (double)xs[(s0 + r * sw) * TB + t];
                 }
                 part = quad_wave_sum(part);
                 if (lane == 0) gpart[t * E.G + (q >> 6)] = part;
             }
-            if (live) {
-                if (A.stream) st_q4_nt(A.y + (int64_t)(b0 + t) * cu64 + a0, o);
-                else st_q4(A.y + (int64_t)(b0 + t) * cu64 + a0, o);
-            }
+            if (live) stq_once<T, RAG>(A.y + (int64_t)(b0 + t) * cu64 + a0, o, nv, A.stream);
         }
     }
     if (EPI) {
@@ -495,18 +616,20 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
 // in turn (interleaved, element (a, t) at a TB + t) and accumulates the chunk's
 // H_up entries of its rows, each entry serving the TB columns; then the H_dn
 // term and one store.  No partial results go through memory.  Tiles are
-// interleaved over the XCDs (tile = 8 k + xcd) and row parts dispatched in
-// turn (every tile's first part, then every tile's second, ...), so the
-// neighbour rows the H_dn term reads at a time are one part's (2x9 ladder:
-// FP32 30.6 -> 30.0 ms, FP64 57.8 -> 56.1 ms against the parts of a tile
-// dispatched together).
+// interleaved over the XCDs (tile = 8 k + xcd).  In one pass the row parts are
+// dispatched in turn (every tile's first part, then every tile's second, ...),
+// so the neighbour rows the H_dn term reads at a time are one part's (2x9
+// ladder: FP32 30.6 -> 30.0 ms, FP64 57.8 -> 56.1 ms against the parts of a tile
+// dispatched together); after a pass of its own for the H_dn term (SPLIT) the
+// parts of a tile run together, and stage the same chunks out of the L2 (2x9
+// ladder, both passes: FP64 57.1 -> 47.2 ms, FP32 27.3 -> 22.9 ms).
 //
 // EPI: the first Lanczos update fused into the store, as in k_kron_quad: each
 // wavefront's 64 lane-quads (one group of 256 rows of a column) are summed in
 // the same fixed order into E.gpart[column][group]; k_epi_colsum then adds a
 // column's groups in increasing order, so the per-column partials equal the
 // columns schedule's bit for bit.
-template <typename T, int BS, int QPL, int TB, bool EPI>
+template <typename T, int BS, int QPL, int TB, bool EPI, bool SPLIT, bool RAG>
 __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const int32_t *__restrict__ ch_off,
                                                            const int64_t *__restrict__ ch_base,
                                                            const uint32_t *__restrict__ ch_ell,
@@ -520,10 +643,10 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
     const int cd = A.cd;
     const int ntiles = (cd + TB - 1) / TB;
     const int n8 = (ntiles + 7) / 8;
-    const int tile = 8 * (r % n8) + xcd, part = r / n8;
+    const int tile = 8 * (SPLIT ? r / P : r % n8) + xcd, part = SPLIT ? r % P : r / n8;
     if (tile >= ntiles) return;
     const int b0 = tile * TB;
-    const int cu = A.cu, nq = cu >> 2;
+    const int cu = A.cu, nq = (cu + 3) >> 2;
     const int64_t cu64 = cu;
     const int qa = part * BS * QPL;
     for (int i = threadIdx.x; i < 256; i += BS) tab[i] = code_v[i];
@@ -551,10 +674,38 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
             const Q4<T> eu = ld_q4(A.e_up + a0);
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
-                const Q4<T> xv = ld_q4(xb[t] + a0);
+                const Q4<T> xv = ldq<T, RAG>(xb[t] + a0, cu - a0);
+                if (SPLIT) {
+                    const Q4<T> v =
+                        ldq_once<T, RAG>(A.y + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, cu - a0, A.stream);
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] = v.v[rr];
+                } else {
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] = (T)0;
+                    int kk = ds[t];
+                    for (; kk + 4 <= de[t]; kk += 4) {
+                        Q4<T> v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            v[u] = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0, cu - a0);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const T w = A.dn_val[kk + u];
+#pragma unroll
+                            for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] = mad(w, v[u].v[rr], acc[i][rr][t]);
+                        }
+                    }
+                    for (; kk < de[t]; ++kk) {
+                        const Q4<T> v = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk] * cu64 + a0, cu - a0);
+                        const T w = A.dn_val[kk];
+#pragma unroll
+                        for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] = mad(w, v.v[rr], acc[i][rr][t]);
+                    }
+                }
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)
-                    acc[i][rr][t] = (diag_u(A, uu[rr] & dnb[t]) + eu.v[rr] + edn[t]) * xv.v[rr];
+                    acc[i][rr][t] = mad(diag_u(A, uu[rr] & dnb[t]) + eu.v[rr] + edn[t], xv.v[rr], acc[i][rr][t]);
             }
         }
     }
@@ -562,13 +713,7 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
         const int q0 = (p * chunk_rows) >> 2;
         const int q1 = min(nq, q0 + (chunk_rows >> 2));
         __syncthreads();  // previous chunk done with xs
-#pragma unroll
-        for (int t = 0; t < TB; ++t)
-            for (int q = q0 + threadIdx.x; q < q1; q += BS) {
-                const Q4<T> v = ld_q4(xb[t] + 4 * q);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) xs[(4 * (q - q0) + rr) * TB + t] = v.v[rr];
-            }
+        stage_quads<T, TB, RAG>(xs, xb, q0, q1, cu, BS);
         __syncthreads();
         const int32_t *off = ch_off + (int64_t)p * (nslices + 1);
         const uint32_t *ell = ch_ell + ch_base[p];
@@ -580,29 +725,7 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
             const int sl = a0 >> 6;
             const uint4 *__restrict__ e4 = reinterpret_cast<const uint4 *>(ell + (int64_t)off[sl] * 64 + (a0 & 63));
             const int len = off[sl + 1] - off[sl];
-            int k = 0;
-            for (; k + 2 <= len; k += 2) {
-                const uint4 ea = e4[16 * k], eb = e4[16 * (k + 1)];
-                const uint32_t e[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w};
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const T v = tab[e[u] >> 24];
-                    const T *xr = xs + (e[u] & 0xFFFFFFu) * TB;
-#pragma unroll
-                    for (int t = 0; t < TB; ++t) acc[i][u & 3][t] += v * xr[t];
-                }
-            }
-            if (k < len) {
-                const uint4 ea = e4[16 * k];
-                const uint32_t e[4] = {ea.x, ea.y, ea.z, ea.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const T v = tab[e[u] >> 24];
-                    const T *xr = xs + (e[u] & 0xFFFFFFu) * TB;
-#pragma unroll
-                    for (int t = 0; t < TB; ++t) acc[i][u][t] += v * xr[t];
-                }
-            }
+            up_quad<T, TB>(acc[i], xs, tab, e4, len);
         }
     }
     EpiCoef<T> ec;
@@ -618,49 +741,25 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
         const int a0 = 4 * (live ? q : 0);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
-            if (live) {
-                int kk = ds[t];
-                for (; kk + 4 <= de[t]; kk += 4) {
-                    Q4<T> v[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) v[u] = ld_q4(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const T w = A.dn_val[kk + u];
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] += w * v[u].v[rr];
-                    }
-                }
-                for (; kk < de[t]; ++kk) {
-                    const Q4<T> v = ld_q4(A.x + (int64_t)A.dn_col[kk] * cu64 + a0);
-                    const T w = A.dn_val[kk];
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) acc[i][rr][t] += w * v.v[rr];
-                }
-            }
             if (b0 + t < cd) {
                 T o[4] = {acc[i][0][t], acc[i][1][t], acc[i][2][t], acc[i][3][t]};
                 if (EPI) {
                     double part = 0.0;
                     if (live) {
-                        const Q4<T> xv = ld_q4(xb[t] + a0);
+                        const Q4<T> xv = ldq<T, RAG>(xb[t] + a0, cu - a0);
                         Q4<T> vp;
-                        if (E.vprev) {
-                            const T *pv = E.vprev + (int64_t)(b0 + t) * cu64 + a0;
-                            vp = A.stream ? ld_q4_nt(pv) : ld_q4(pv);
-                        }
+                        if (E.vprev)
+                            vp = ldq_once<T, RAG>(E.vprev + (int64_t)(b0 + t) * cu64 + a0, cu - a0, A.stream);
 #pragma unroll
                         for (int r = 0; r < 4; ++r) o[r] = epi_w(E, ec, o[r], E.vprev ? vp.v[r] : (T)0);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) part += (double)o[r] * (double)xv.v[r];
+                        for (int r = 0; r < 4; ++r)
+                            if (!RAG || r < cu - a0) part += (double)o[r] * (double)xv.v[r];
                     }
                     part = quad_wave_sum(part);
                     if (lane == 0) E.gpart[(int64_t)(b0 + t) * E.G + (q >> 6)] = part;
                 }
-                if (live) {
-                    if (EPI && A.stream) st_q4_nt(A.y + (int64_t)(b0 + t) * cu64 + a0, o);
-                    else st_q4(A.y + (int64_t)(b0 + t) * cu64 + a0, o);
-                }
+                if (live) stq_once<T, RAG>(A.y + (int64_t)(b0 + t) * cu64 + a0, o, cu - a0, EPI && A.stream);
             }
         }
     }
@@ -683,7 +782,7 @@ __global__ void k_epi_colsum(const double *__restrict__ gpart, int G, int cd, do
 // first Lanczos update fused into the store (as in k_kron_quad), each lane
 // summing its rows' products in row order and the workgroup combining the
 // lanes in a fixed tree, one partial per column.
-template <typename T, int TB, int BS, int R, bool CF, bool EPI>
+template <typename T, int TB, int BS, int R, bool CF, bool EPI, bool SPLIT>
 __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *__restrict__ sl_off,
                                                    const Pk<T> *__restrict__ ell, const uint32_t *__restrict__ ellc,
                                                    const T *__restrict__ code_v, int ntiles, LzEpi<T> E)
@@ -721,34 +820,43 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
         int as[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int a = min(a0 + j * BS, cu - 1);
-            as[j] = a;
+            as[j] = min(a0 + j * BS, cu - 1);
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                acc[j][t] = SPLIT ? A.y[(int64_t)min(b0 + t, cd - 1) * cu64 + as[j]] : (T)0;
+        }
+        if (!SPLIT) {
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                int k = ds[t];
+                for (; k + 4 <= de[t]; k += 4) {
+                    T y[4][R];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int j = 0; j < R; ++j) y[u][j] = A.x[(int64_t)A.dn_col[k + u] * cu64 + as[j]];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int j = 0; j < R; ++j) acc[j][t] = mad(A.dn_val[k + u], y[u][j], acc[j][t]);
+                }
+                for (; k < de[t]; ++k)
+#pragma unroll
+                    for (int j = 0; j < R; ++j)
+                        acc[j][t] = mad(A.dn_val[k], A.x[(int64_t)A.dn_col[k] * cu64 + as[j]], acc[j][t]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int a = as[j];
             const uint32_t ua = A.up_basis[a];
             const T eua = A.e_up[a];
             const Vec<T, TB> xa = *reinterpret_cast<const Vec<T, TB> *>(xs + a * TB);
 #pragma unroll
-            for (int t = 0; t < TB; ++t) acc[j][t] = (diag_u(A, ua & dnb[t]) + eua + edn[t]) * xa.v[t];
+            for (int t = 0; t < TB; ++t) acc[j][t] = mad(diag_u(A, ua & dnb[t]) + eua + edn[t], xa.v[t], acc[j][t]);
             const int s = a >> 6;
             if (CF) up_term_c<T, TB>(acc[j], xs, tab, ellc, sl_off[s] * 64 + lane, sl_off[s + 1] - sl_off[s]);
             else up_term<T, TB>(acc[j], xs, ell, sl_off[s] * 64 + lane, sl_off[s + 1] - sl_off[s]);
-        }
-#pragma unroll
-        for (int t = 0; t < TB; ++t) {
-            int k = ds[t];
-            for (; k + 4 <= de[t]; k += 4) {
-                T y[4][R];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int j = 0; j < R; ++j) y[u][j] = A.x[(int64_t)A.dn_col[k + u] * cu64 + as[j]];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int j = 0; j < R; ++j) acc[j][t] += A.dn_val[k + u] * y[u][j];
-            }
-            for (; k < de[t]; ++k)
-#pragma unroll
-                for (int j = 0; j < R; ++j) acc[j][t] += A.dn_val[k] * A.x[(int64_t)A.dn_col[k] * cu64 + as[j]];
         }
 #pragma unroll
         for (int j = 0; j < R; ++j)
@@ -780,6 +888,87 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
     }
 }
 
+// ---- the H_dn term in a pass of its own: y = V H_dn^T ----------------------
+// One wavefront per (column b, segment of 1 KB of rows): 16 bytes of rows per
+// lane, the row of H_dn uniform over the wavefront (scalar loads), up to eight
+// neighbour segments in flight.  Work is ordered by segment, then by column, and
+// every XCD takes a contiguous eighth of that list, so its CUs gather from one
+// narrow band of rows, of which the L2 (4 MB) keeps the last 4000 columns,
+// instead of from whole columns, of which it keeps 44 (4x4 torus FP64) or 10
+// (2x9 ladder FP64).  The last lane of a segment overlaps the one before where
+// count_up is no multiple of the 16 bytes (both store the same values).
+// Bound: lines in flight per CU (about 90 of 128 bytes, 415 cycles each by the
+// counters, so 15 to 20 TB/s over the chip).  Segments of 256 and 512 bytes hit
+// the L2 more often (4x4 torus FP64: 18 and 28 instead of 44 million reads from
+// beyond it) and are no faster.  4x4 torus 0.89 ms FP64, 0.50 ms FP32; 2x9
+// ladder 21.6 / 10.9 ms; re-reading the last entry to fill up the batches of
+// eight cost 1.12 / 0.58 and 23.5 / 11.8 ms.
+template <typename T>
+constexpr int kDnRows = 16 / (int)sizeof(T);  // rows per lane
+constexpr int kDnWaves = 4;                   // wavefronts (columns) per workgroup
+
+template <typename T>
+__global__ __launch_bounds__(64 * kDnWaves) void k_dn_rows(MvArgs<T> A, int ntile, int nwork)
+{
+    typedef T VecU __attribute__((ext_vector_type(kDnRows<T>), aligned(sizeof(T))));
+    constexpr int RL = kDnRows<T>;
+    const int wk = xcd_tile(nwork);
+    if (wk < 0) return;
+    const int seg = (int)((uint32_t)wk / (uint32_t)ntile), tile = wk - seg * ntile;
+    const int b = tile * kDnWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (b >= A.cd) return;
+    const uint32_t cu = (uint32_t)A.cu;
+    const int a0 = min((seg * 64 + ((int)threadIdx.x & 63)) * RL, A.cu - RL);
+    const int ks = A.dn_rp[b], n = A.dn_rp[b + 1] - ks;
+    const int32_t *__restrict__ col = A.dn_col + ks;
+    const T *__restrict__ val = A.dn_val + ks;
+    T acc[RL];
+#pragma unroll
+    for (int r = 0; r < RL; ++r) acc[r] = (T)0;
+    const T *__restrict__ xa = A.x + a0;
+    auto load = [&](int k) { return *reinterpret_cast<const VecU *>(xa + (uint64_t)(uint32_t)col[k] * cu); };
+    auto use = [&](int k, const VecU &v) {
+        const T w = val[k];
+#pragma unroll
+        for (int r = 0; r < RL; ++r) acc[r] = mad(w, v[r], acc[r]);
+    };
+    int k = 0;
+    for (; k + 8 <= n; k += 8) {
+        VecU v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = load(k + u);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) use(k + u, v[u]);
+    }
+    // the last n % 8 entries: every load issued before the first update
+    VecU v4[4], v2[2], v1;
+    const int m = n - k, k2 = k + (m & 4), k1 = k2 + (m & 2);
+    if (m & 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v4[u] = load(k + u);
+    }
+    if (m & 2) {
+        v2[0] = load(k2);
+        v2[1] = load(k2 + 1);
+    }
+    if (m & 1) v1 = load(k1);
+    if (m & 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) use(k + u, v4[u]);
+    }
+    if (m & 2) {
+        use(k2, v2[0]);
+        use(k2 + 1, v2[1]);
+    }
+    if (m & 1) use(k1, v1);
+    VecU o;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) o[r] = acc[r];
+    VecU *dst = reinterpret_cast<VecU *>(A.y + (uint64_t)(uint32_t)b * cu + a0);
+    if (A.stream) __builtin_nontemporal_store(o, dst);
+    else *dst = o;
+}
+
 // ---- fallback: CSR rows, H_up gathered from global memory ----------------
 template <typename T, int BS>
 __global__ __launch_bounds__(BS) void k_kron_csr(MvArgs<T> A)
@@ -791,9 +980,10 @@ __global__ __launch_bounds__(BS) void k_kron_csr(MvArgs<T> A)
     const uint32_t dnb = A.dn_basis[b];
     const T edn = A.e_dn[b];
     for (int a = threadIdx.x; a < cu; a += BS) {
-        T acc = (diag_u(A, A.up_basis[a] & dnb) + A.e_up[a] + edn) * xb[a];
-        for (int k = A.up_rp[a]; k < A.up_rp[a + 1]; ++k) acc += A.up_val[k] * xb[A.up_col[k]];
+        T acc = (T)0;
         dn_term(acc, A, ds, de, A.x + a);
+        acc = mad(diag_u(A, A.up_basis[a] & dnb) + A.e_up[a] + edn, xb[a], acc);
+        for (int k = A.up_rp[a]; k < A.up_rp[a + 1]; ++k) acc = mad(A.up_val[k], xb[A.up_col[k]], acc);
         A.y[(int64_t)b * cu + a] = acc;
     }
 }
@@ -895,16 +1085,24 @@ constexpr int dix()
     return sizeof(T) == 8 ? kF64 : kF32;
 }
 
-// A sector whose product can use the 16-byte-access kernels.
+// A sector whose product can use the kernels with four rows per lane, and one
+// whose columns are whole quads (count_up % 4 == 0, all shapes).
+bool quad_any(const hub_sector *s)
+{
+    return !s->k0 && s->spin[0].ell_q32 && s->spin[1].ell_c32 && s->spin[0].count >= 4;
+}
+
 bool quad_ok(const hub_sector *s)
 {
-    return !s->k0 && s->spin[0].ell_c32 && s->spin[1].ell_c32 && (s->spin[0].count % 4) == 0;
+    return quad_any(s) && (s->spin[0].count % 4) == 0;
 }
+
+int64_t quads(int64_t count) { return (count + 3) >> 2; }
 
 template <typename T>
 bool column_fits(const hub_sector *s, int tb, bool epi)
 {
-    const int64_t cu = s->spin[0].count;
+    const int64_t cu = 4 * quads(s->spin[0].count);
     const size_t g = (size_t)((cu / 4 + 63) / 64);
     return (size_t)(cu * tb + 256) * sizeof(T) + (epi ? (size_t)tb * g * sizeof(double) : 0) <= s->lds_max;
 }
@@ -937,44 +1135,67 @@ bool chunked_shape_ok(int tb, int qpl)
 
 // ---- launchers --------------------------------------------------------------
 
-template <typename T, int TB, int BS, bool XC, bool EPI>
+// y = V H_dn^T (count_up >= kDnRows, n = count of segments times columns in blocks)
+template <typename T>
+hub_status launch_dn_rows(const MvArgs<T> &A, hipStream_t st)
+{
+    const int seg_rows = 64 * kDnRows<T>;
+    const int nseg = (A.cu + seg_rows - 1) / seg_rows, ntile = (A.cd + kDnWaves - 1) / kDnWaves;
+    const int64_t nwork = (int64_t)nseg * ntile, grid = 8 * ((nwork + 7) / 8);
+    if (A.cu < kDnRows<T> || grid > INT32_MAX) {
+        set_error("row-segment pass: the sector is outside its range");
+        return HUB_ERR_UNSUPPORTED;
+    }
+    hipLaunchKernelGGL((k_dn_rows<T>), dim3((unsigned)grid), dim3(64 * kDnWaves), 0, st, A, ntile, (int)nwork);
+    HUB_HIP(hipGetLastError());
+    return HUB_OK;
+}
+
+template <typename T, int TB, int BS, bool XC, bool EPI, bool SPLIT, bool RAG>
 hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, const LzEpi<T> &E)
 {
     const SpinTables &U = s->spin[0];
     const int ntiles = (A.cd + TB - 1) / TB;
     const unsigned grid = XC ? 8u * (unsigned)((ntiles + 7) / 8) : (unsigned)ntiles;
-    const size_t lds = (size_t)(A.cu * TB + 256) * sizeof(T) + (EPI ? (size_t)TB * E.G * sizeof(double) : 0);
+    const size_t lds = (size_t)(4 * quads(A.cu) * TB + 256) * sizeof(T) +
+                       (EPI ? (size_t)TB * E.G * sizeof(double) : 0);
     if (lds > s->lds_max) {
         set_error("column product: tile does not fit in LDS");
         return HUB_ERR_UNSUPPORTED;
     }
-    HUB_TRY(allow_lds(k_kron_quad<T, TB, BS, XC, EPI>, s->lds_max));
-    hipLaunchKernelGGL((k_kron_quad<T, TB, BS, XC, EPI>), dim3(grid), dim3(BS), lds, st, A, U.sl_off, U.ell_c32,
+    HUB_TRY(allow_lds(k_kron_quad<T, TB, BS, XC, EPI, SPLIT, RAG>, s->lds_max));
+    hipLaunchKernelGGL((k_kron_quad<T, TB, BS, XC, EPI, SPLIT, RAG>), dim3(grid), dim3(BS), lds, st, A, U.sl_off, U.ell_q32,
                        code_table<T>(U), ntiles, E);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
 }
 
-// column product of shape (tb in 1..3, bs in {512, 1024}, xc); E: fused Lanczos update or NULL
+// column product of shape (tb in 1..3, bs in {512, 1024}, xc; 2 = from the H_dn
+// term already in y); E: fused Lanczos update or NULL
 template <typename T>
 hub_status launch_quad(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, int tb, int bs, int xc,
                        const LzEpi<T> *E)
 {
     const LzEpi<T> ne = no_epi<T>();
-#define HUB_QUAD(TBV, BSV, XCV)                                                              \
-    if (tb == TBV && bs == BSV && xc == XCV) {                                               \
-        if (E) return launch_quad_k<T, TBV, BSV, XCV, true>(s, A, st, *E);                  \
-        return launch_quad_k<T, TBV, BSV, XCV, false>(s, A, st, ne);                        \
+#define HUB_QUAD(TBV, BSV, XCV, RAGV)                                                           \
+    if (tb == TBV && bs == BSV && xc == XCV && ragged == RAGV) {                                \
+        if (E) return launch_quad_k<T, TBV, BSV, XCV == 1, true, XCV == 2, RAGV>(s, A, st, *E); \
+        return launch_quad_k<T, TBV, BSV, XCV == 1, false, XCV == 2, RAGV>(s, A, st, ne);       \
     }
-    HUB_QUAD(1, 512, 0) HUB_QUAD(1, 512, 1) HUB_QUAD(1, 1024, 0) HUB_QUAD(1, 1024, 1)
-    HUB_QUAD(2, 512, 0) HUB_QUAD(2, 512, 1) HUB_QUAD(2, 1024, 0) HUB_QUAD(2, 1024, 1)
-    HUB_QUAD(3, 512, 0) HUB_QUAD(3, 512, 1) HUB_QUAD(3, 1024, 0) HUB_QUAD(3, 1024, 1)
+    const bool ragged = (A.cu & 3) != 0;
+    HUB_QUAD(1, 512, 0, false) HUB_QUAD(1, 512, 1, false) HUB_QUAD(1, 1024, 0, false) HUB_QUAD(1, 1024, 1, false)
+    HUB_QUAD(2, 512, 0, false) HUB_QUAD(2, 512, 1, false) HUB_QUAD(2, 1024, 0, false) HUB_QUAD(2, 1024, 1, false)
+    HUB_QUAD(3, 512, 0, false) HUB_QUAD(3, 512, 1, false) HUB_QUAD(3, 1024, 0, false) HUB_QUAD(3, 1024, 1, false)
+    HUB_QUAD(1, 512, 2, false) HUB_QUAD(1, 1024, 2, false) HUB_QUAD(2, 512, 2, false) HUB_QUAD(2, 1024, 2, false)
+    HUB_QUAD(3, 512, 2, false) HUB_QUAD(3, 1024, 2, false)
+    HUB_QUAD(1, 512, 1, true) HUB_QUAD(1, 1024, 1, true) HUB_QUAD(2, 512, 1, true)
+    HUB_QUAD(1, 512, 2, true) HUB_QUAD(1, 1024, 2, true) HUB_QUAD(2, 512, 2, true) HUB_QUAD(2, 1024, 2, true)
 #undef HUB_QUAD
     set_error("unsupported column product shape");
     return HUB_ERR_UNSUPPORTED;
 }
 
-template <typename T, int QPL, int TB, bool EPI>
+template <typename T, int QPL, int TB, bool EPI, bool SPLIT, bool RAG>
 hub_status launch_chunked_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, const ChunkSet &C,
                             const LzEpi<T> &E)
 {
@@ -985,12 +1206,12 @@ hub_status launch_chunked_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t
         set_error("row-chunked product: chunk does not fit in LDS");
         return HUB_ERR_UNSUPPORTED;
     }
-    const int nq = (int)(A.cu >> 2);
+    const int nq = (int)quads(A.cu);
     const int P = (nq + BSC * QPL - 1) / (BSC * QPL);
     const int ntiles = (A.cd + TB - 1) / TB;
-    HUB_TRY(allow_lds(k_kron_chunked_parts<T, BSC, QPL, TB, EPI>, s->lds_max));
+    HUB_TRY(allow_lds(k_kron_chunked_parts<T, BSC, QPL, TB, EPI, SPLIT, RAG>, s->lds_max));
     const unsigned grid = 8u * (unsigned)P * (unsigned)((ntiles + 7) / 8);
-    hipLaunchKernelGGL((k_kron_chunked_parts<T, BSC, QPL, TB, EPI>), dim3(grid), dim3(BSC), lds, st, A, C.off,
+    hipLaunchKernelGGL((k_kron_chunked_parts<T, BSC, QPL, TB, EPI, SPLIT, RAG>), dim3(grid), dim3(BSC), lds, st, A, C.off,
                        C.base, C.ell, code_table<T>(U), C.n, C.rows, (int)U.nslices, P, E);
     if (EPI)
         hipLaunchKernelGGL(k_epi_colsum, dim3((unsigned)((A.cd + 255) / 256)), dim3(256), 0, st,
@@ -999,16 +1220,29 @@ hub_status launch_chunked_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t
     return HUB_OK;
 }
 
-// row-chunked product of shape (tb, qpl); E: fused Lanczos update or NULL
+// row-chunked product of shape (tb, qpl), with split from the H_dn term already
+// in y; E: fused Lanczos update or NULL
 template <typename T>
-hub_status launch_chunked(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, int tb, int qpl,
+hub_status launch_chunked(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, int tb, int qpl, bool split,
                           const ChunkSet &C, const LzEpi<T> *E)
 {
     const LzEpi<T> ne = no_epi<T>();
-#define HUB_CH(TBV, QV)                                                                  \
-    if (tb == TBV && qpl == QV) {                                                        \
-        if (E) return launch_chunked_k<T, QV, TBV, true>(s, A, st, C, *E);              \
-        return launch_chunked_k<T, QV, TBV, false>(s, A, st, C, ne);                    \
+#define HUB_CH(TBV, QV)                                                                      \
+    if (tb == TBV && qpl == QV) {                                                            \
+        if ((A.cu & 3) && split) {                                                           \
+            if (E) return launch_chunked_k<T, QV, TBV, true, true, true>(s, A, st, C, *E);  \
+            return launch_chunked_k<T, QV, TBV, false, true, true>(s, A, st, C, ne);        \
+        }                                                                                    \
+        if (split) {                                                                         \
+            if (E) return launch_chunked_k<T, QV, TBV, true, true, false>(s, A, st, C, *E); \
+            return launch_chunked_k<T, QV, TBV, false, true, false>(s, A, st, C, ne);       \
+        }                                                                                    \
+        if (E) return launch_chunked_k<T, QV, TBV, true, false, false>(s, A, st, C, *E);    \
+        return launch_chunked_k<T, QV, TBV, false, false, false>(s, A, st, C, ne);          \
+    }
+    if ((A.cu & 3) && !split) {
+        set_error("row-chunked product of ragged columns: only after a row-segment pass");
+        return HUB_ERR_UNSUPPORTED;
     }
     HUB_CH(1, 4) HUB_CH(1, 8) HUB_CH(2, 4)
     if constexpr (sizeof(T) == 4) {
@@ -1019,7 +1253,7 @@ hub_status launch_chunked(const hub_sector *s, const MvArgs<T> &A, hipStream_t s
     return HUB_ERR_UNSUPPORTED;
 }
 
-template <typename T, int TB, int BS, int R, bool EPI>
+template <typename T, int TB, int BS, int R, bool EPI, bool SPLIT>
 hub_status launch_rows(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, const LzEpi<T> &E)
 {
     const SpinTables &U = s->spin[0];
@@ -1028,15 +1262,15 @@ hub_status launch_rows(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, 
     const size_t lim = s->lds_max - (EPI ? (size_t)BS * sizeof(double) : 0);  // beside the static reduction array
     if (U.ell_c32) {
         const size_t lds = (size_t)(A.cu * TB + 256) * sizeof(T);
-        HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, true, EPI>, lim));
-        hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, true, EPI>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
+        HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, true, EPI, SPLIT>, lim));
+        hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, true, EPI, SPLIT>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
                            ell_of<T>(U), U.ell_c32, code_table<T>(U), ntiles, E);
         HUB_HIP(hipGetLastError());
         return HUB_OK;
     }
     const size_t lds = (size_t)A.cu * TB * sizeof(T);
-    HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, false, EPI>, lim));
-    hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, false, EPI>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
+    HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, false, EPI, SPLIT>, lim));
+    hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, false, EPI, SPLIT>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
                        ell_of<T>(U), (const uint32_t *)nullptr, (const T *)nullptr, ntiles, E);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
@@ -1061,9 +1295,11 @@ hub_status launch_rows_auto(const hub_sector *s, const MvArgs<T> &A, hipStream_t
     const size_t lim = s->lds_max - (E ? 1024 * sizeof(double) : 0);
     const LzEpi<T> ne = no_epi<T>();
     if (2 * col + extra <= lim / 2)
-        return E ? launch_rows<T, 2, 1024, 2, true>(s, A, st, *E) : launch_rows<T, 2, 1024, 2, false>(s, A, st, ne);
+        return E ? launch_rows<T, 2, 1024, 2, true, false>(s, A, st, *E)
+                 : launch_rows<T, 2, 1024, 2, false, false>(s, A, st, ne);
     if (col + extra <= lim)
-        return E ? launch_rows<T, 1, 1024, 4, true>(s, A, st, *E) : launch_rows<T, 1, 1024, 4, false>(s, A, st, ne);
+        return E ? launch_rows<T, 1, 1024, 4, true, false>(s, A, st, *E)
+                 : launch_rows<T, 1, 1024, 4, false, false>(s, A, st, ne);
     if (E) {
         set_error("one-row-per-lane product: a column does not fit in LDS beside the update's reduction");
         return HUB_ERR_UNSUPPORTED;
@@ -1083,11 +1319,13 @@ hub_status launch_sched(const hub_sector *s, const MvArgs<T> &A, hipStream_t st,
     }
     switch (q.fam) {
     case HUB_SCHED_COLUMNS:
+        if (q.xc == 2) HUB_TRY(launch_dn_rows<T>(A, st));
         return launch_quad<T>(s, A, st, q.tb, q.bs, q.xc, E);
     case HUB_SCHED_CHUNKED: {
+        if (q.xc == 2) HUB_TRY(launch_dn_rows<T>(A, st));
         const ChunkSet *C = nullptr;
         HUB_TRY(chunk_set(s, HUB_SPIN_UP, q.crows > 0 ? q.crows : chunked_rows<T>(s, q.tb), &C, st));
-        return launch_chunked<T>(s, A, st, q.tb, q.qpl, *C, E);
+        return launch_chunked<T>(s, A, st, q.tb, q.qpl, q.xc == 2, *C, E);
     }
     case HUB_SCHED_ROWS:
         return launch_rows_auto<T>(s, A, st, E);
@@ -1148,36 +1386,50 @@ hub_status time_candidates(hipStream_t st, int n, F launch, int &best, float &be
 // fused update, the shapes whose partials also fit), else the row-chunked
 // shapes (1, 2 or 4 columns per work item, 4 or 8 lane-quads per lane), with
 // or without the fused update.
+// The H_dn term in its own pass reads x and writes y once more, and its
+// gathers run from the L2 instead of from beyond it: worth it where vectors
+// exceed half of the 256 MB MALL (4x4 torus FP64 2.79 -> 2.35 ms, 2x9 ladder
+// FP64 55.4 -> 46.5 ms), not where they stay there (ring M=14 FP64, 94 MB:
+// 115 us in one pass, 137 us in two).
+template <typename T>
+bool split_range(const hub_sector *s)
+{
+    return (double)s->dim * sizeof(T) > 128.0 * 1024 * 1024 && s->spin[0].count >= 64 * kDnRows<T>;
+}
+
 template <typename T>
 std::vector<Sched> candidates(const hub_sector *s, bool epi)
 {
     std::vector<Sched> v;
-    if (column_fits<T>(s, 1, false)) {
-        for (int tb = 1; tb <= 3; ++tb) {
-            if (!column_fits<T>(s, tb, epi)) break;
-            for (int bs : {512, 1024})
-                for (int xc : {0, 1}) {
-                    Sched c;
-                    c.fam = HUB_SCHED_COLUMNS;
-                    c.tb = tb;
-                    c.bs = bs;
-                    c.xc = xc;
-                    v.push_back(c);
-                }
-        }
-        return v;
-    }
+    const bool ragged = !quad_ok(s), columns = column_fits<T>(s, 1, epi), split = split_range<T>(s);
+    for (int tb = 1; tb <= (ragged ? 2 : 3) && column_fits<T>(s, tb, epi); ++tb)
+        for (int bs : {512, 1024})
+            for (int xc : {0, 1, 2}) {
+                if (xc == 2 && !split) continue;
+                if (ragged && (xc == 0 || (tb == 2 && bs == 1024 && xc == 1))) continue;
+                Sched c;
+                c.fam = HUB_SCHED_COLUMNS;
+                c.tb = tb;
+                c.bs = bs;
+                c.xc = xc;
+                v.push_back(c);
+            }
     for (int tb : {1, 2, 4})
-        for (int qpl : {4, 8}) {
-            if (!chunked_shape_ok<T>(tb, qpl) || chunked_rows<T>(s, tb) <= 0) continue;
-            Sched c;
-            c.fam = HUB_SCHED_CHUNKED;
-            c.tb = tb;
-            c.qpl = qpl;
-            c.bs = 1024;
-            c.crows = chunked_rows<T>(s, tb);
-            v.push_back(c);
-        }
+        for (int qpl : {4, 8})
+            for (int xc : {0, 2}) {
+                if (!chunked_shape_ok<T>(tb, qpl) || chunked_rows<T>(s, tb) <= 0) continue;
+                if (xc == 0 && (columns || ragged)) continue;
+                // two passes: where a tile is not staged whole above, or no one-pass shape exists
+                if (xc == 2 && !(split ? !column_fits<T>(s, tb, epi) : v.empty() || (ragged && !columns))) continue;
+                Sched c;
+                c.fam = HUB_SCHED_CHUNKED;
+                c.tb = tb;
+                c.qpl = qpl;
+                c.bs = 1024;
+                c.xc = xc;
+                c.crows = chunked_rows<T>(s, tb);
+                v.push_back(c);
+            }
     return v;
 }
 
@@ -1197,7 +1449,7 @@ hub_status tune(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, bool ep
         HUB_HIP(hipMalloc((void **)&zero, sizeof(double)));
         zb.p = zero;
         HUB_HIP(hipMemsetAsync(zero, 0, sizeof(double), st));
-        E = LzEpi<T>{A.x, zero, apart, (int)(((A.cu >> 2) + 63) / 64), nullptr, 0, apart + A.cd};
+        E = LzEpi<T>{A.x, zero, apart, (int)((quads(A.cu) + 63) / 64), nullptr, 0, apart + A.cd};
     }
     std::vector<Sched> c = candidates<T>(s, epi);
     if (c.empty()) {
@@ -1267,7 +1519,7 @@ hub_status run_kron(const hub_sector *s, const void *x, void *y, hipStream_t st)
     MvArgs<T> A = make_args<T>(s, x, y);
     // the 16-byte-access kernels need 16-byte aligned vectors
     const bool aligned16 = (((uintptr_t)x | (uintptr_t)y) & 15u) == 0;
-    if (!aligned16 || !quad_ok(s)) {
+    if (!aligned16 || !quad_any(s)) {
         bool csr;
         {
             std::lock_guard<std::mutex> lk(s->mu);
@@ -1300,7 +1552,7 @@ bool lz_fusable(const hub_sector *s)
         if (q.fam == HUB_SCHED_CHUNKED) return quad_ok(s);
         return q.fam == HUB_SCHED_ROWS && rows_fit<T>(s, true);
     }
-    if (!quad_ok(s)) return rows_fit<T>(s, true);
+    if (!quad_any(s)) return rows_fit<T>(s, true);
     return column_fits<T>(s, 1, true) || (!column_fits<T>(s, 1, false) && chunked_rows<T>(s, 1) > 0);
 }
 
@@ -1311,12 +1563,12 @@ hub_status run_kron_lz(const hub_sector *s, const void *x, void *w, const void *
     if (!lz_fusable<T>(s)) return HUB_ERR_UNSUPPORTED;
     MvArgs<T> A = make_args<T>(s, x, w);
     Sched q;
-    if (quad_ok(s)) {
+    if (quad_any(s)) {
         HUB_TRY(schedule_for<T>(s, A, st, true, apart, q));
     } else {
         q.fam = HUB_SCHED_ROWS;  // the only fused shape without four-row quads
     }
-    const LzEpi<T> E{(const T *)vprev, beta, apart, (int)(((A.cu >> 2) + 63) / 64), beta_prev, unnorm,
+    const LzEpi<T> E{(const T *)vprev, beta, apart, (int)((quads(A.cu) + 63) / 64), beta_prev, unnorm,
                      apart + A.cd};
     *npart = (int64_t)A.cd;
     std::lock_guard<std::mutex> lk(s->mu);
@@ -1346,7 +1598,7 @@ int64_t matvec_lz_partials(const hub_sector *s)
 // then (row-chunked schedule) one per column and group of 256 rows.
 int64_t matvec_lz_workspace(const hub_sector *s)
 {
-    const int64_t cd = s->spin[1].count, G = ((s->spin[0].count >> 2) + 63) / 64;
+    const int64_t cd = s->spin[1].count, G = (quads(s->spin[0].count) + 63) / 64;
     return cd * (1 + G);
 }
 
@@ -1407,8 +1659,8 @@ hub_status check_forced(const hub_sector *s, const hub_schedule &h, Sched &q)
     switch (q.fam) {
     case HUB_SCHED_COLUMNS:
         if (!quad_ok(s)) return bad("columns schedule needs count_up % 4 == 0 and compact entries");
-        if (q.tb < 1 || q.tb > 3 || (q.bs != 512 && q.bs != 1024) || (q.xc != 0 && q.xc != 1))
-            return bad("columns schedule: tile_cols 1..3, block 512 or 1024, order 0 or 1");
+        if (q.tb < 1 || q.tb > 3 || (q.bs != 512 && q.bs != 1024) || q.xc < 0 || q.xc > 2)
+            return bad("columns schedule: tile_cols 1..3, block 512 or 1024, order 0, 1 or 2");
         if (!column_fits<T>(s, q.tb, false)) return bad("columns schedule: the tile does not fit in LDS");
         q.qpl = 0;
         q.crows = 0;
@@ -1422,7 +1674,7 @@ hub_status check_forced(const hub_sector *s, const hub_schedule &h, Sched &q)
         if (q.crows <= 0 || q.crows % 4 != 0 || ((size_t)q.crows * q.tb + 256) * sizeof(T) > s->lds_max)
             return bad("chunked schedule: chunk_rows must be a positive multiple of 4 that fits in LDS");
         q.bs = 1024;
-        q.xc = 0;
+        q.xc = q.xc == 2 ? 2 : 0;
         break;
     case HUB_SCHED_ROWS:
         if (!column_fits<T>(s, 1, false)) return bad("rows schedule: a column does not fit in LDS");

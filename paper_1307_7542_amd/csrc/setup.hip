@@ -216,7 +216,8 @@ __global__ void k_sell_fill(const int32_t *__restrict__ rp, const int32_t *__res
                             const double *__restrict__ val, const int32_t *__restrict__ bond,
                             const double *__restrict__ t, int64_t count, const int32_t *__restrict__ sp,
                             int32_t *__restrict__ ecol, float *__restrict__ e32, double *__restrict__ e64,
-                            uint2 *__restrict__ pk32, uint4 *__restrict__ pk64, uint32_t *__restrict__ c32)
+                            uint2 *__restrict__ pk32, uint4 *__restrict__ pk64, uint32_t *__restrict__ c32,
+                            uint32_t *__restrict__ q32)
 {
     // one lane per (padded) row of a slice
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -240,6 +241,7 @@ __global__ void k_sell_fill(const int32_t *__restrict__ rp, const int32_t *__res
             v = 0.0;
         }
         if (c32) c32[o] = ((uint32_t)c & 0xFFFFFFu) | (code << 24);
+        if (q32) q32[o] = ((uint32_t)lds_slot(c, (int)count) & 0xFFFFFFu) | (code << 24);
         ecol[o] = c;
         e64[o] = v;
         e32[o] = (float)v;
@@ -279,7 +281,7 @@ __global__ void k_slice_max(const int32_t *__restrict__ len, int64_t count, int6
 __global__ void k_chunk_fill(const int32_t *__restrict__ rstart, const int32_t *__restrict__ rlen,
                              const int32_t *__restrict__ col, const double *__restrict__ val,
                              const int32_t *__restrict__ bond, const double *__restrict__ t, int64_t count,
-                             const int32_t *__restrict__ sp, int c_lo, uint32_t *__restrict__ out)
+                             const int32_t *__restrict__ sp, int c_lo, int c_n, uint32_t *__restrict__ out)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t sl = r / 64, lane = r % 64;
@@ -293,7 +295,7 @@ __global__ void k_chunk_fill(const int32_t *__restrict__ rstart, const int32_t *
             const double v = val[r0 + k];
             const int b = bond[r0 + k];
             const uint32_t code = 2u * (uint32_t)b + ((v == t[b] && v != 0.0) ? 1u : 0u);
-            e = ((uint32_t)(col[r0 + k] - c_lo) & 0xFFFFFFu) | (code << 24);
+            e = ((uint32_t)lds_slot(col[r0 + k] - c_lo, c_n) & 0xFFFFFFu) | (code << 24);
         }
         out[base + 64 * (int64_t)k + lane] = e;
     }
@@ -347,10 +349,10 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
         set_error("hopping matrix would exceed 2^31 entries");
         return HUB_ERR_RANGE;
     }
-    HUB_TRY(dalloc(s, &T.basis, count));
+    HUB_TRY(dalloc(s, &T.basis, count + 3));  // + 3: the four-row kernels read whole quads
     HUB_TRY(dalloc(s, &T.rp, count + 1));
-    HUB_TRY(dalloc(s, &T.e64, count));
-    HUB_TRY(dalloc(s, &T.e32, count));
+    HUB_TRY(dalloc(s, &T.e64, count + 3));
+    HUB_TRY(dalloc(s, &T.e32, count + 3));
     int32_t *rowlen = nullptr;
     int64_t *tmp = nullptr, *bsum = nullptr;
     int32_t *dmax = nullptr;
@@ -418,6 +420,7 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
     const bool compact = count < (1 << 24) && s->nb <= 127;
     if (compact) {
         HUB_TRY(dalloc(s, &T.ell_c32, nell));
+        HUB_TRY(dalloc(s, &T.ell_q32, nell));
         HUB_TRY(dalloc(s, &T.code_v64, 256));
         HUB_TRY(dalloc(s, &T.code_v32, 256));
         std::vector<double> cv(256, 0.0);
@@ -432,7 +435,7 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
         HUB_HIP(hipMemcpy(T.code_v32, cf.data(), 256 * sizeof(float), hipMemcpyHostToDevice));
     }
     hipLaunchKernelGGL(k_sell_fill, dim3((unsigned)ns), dim3(64), 0, st, T.rp, T.col, T.val64, T.bond, s->d_t, count,
-                       sp, T.ell_col, T.ell_v32, T.ell_v64, T.ell_pk32, T.ell_pk64, T.ell_c32);
+                       sp, T.ell_col, T.ell_v32, T.ell_v64, T.ell_pk32, T.ell_pk64, T.ell_c32, T.ell_q32);
     HUB_HIP(hipGetLastError());
     HUB_HIP(hipStreamSynchronize(st));
     return HUB_OK;
@@ -508,7 +511,7 @@ static hub_status build_chunk_set(hub_sector *s, int spin, int chunk_rows, Chunk
         hipLaunchKernelGGL(k_chunk_rows, dim3(grid_for(count, B)), dim3(B), 0, st, T.rp, T.col, count, c_lo, c_hi,
                            rstart, rlen);
         hipLaunchKernelGGL(k_chunk_fill, dim3((unsigned)ns), dim3(64), 0, st, rstart, rlen, T.col, T.val64, T.bond,
-                           s->d_t, count, offs + (size_t)p * (ns + 1), c_lo, ell + base[p]);
+                           s->d_t, count, offs + (size_t)p * (ns + 1), c_lo, c_hi - c_lo, ell + base[p]);
     }
     HUB_HIP(hipGetLastError());
     HUB_HIP(hipStreamSynchronize(st));

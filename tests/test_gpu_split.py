@@ -1,0 +1,74 @@
+"""The H_dn term in a pass of its own (order 2), and columns of any length in the
+kernels with four rows per lane, against the row and CSR kernels (bit for bit)
+and the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hub():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("needs a GPU")
+    import paper_1307_7542_amd as h
+    h.lib()
+    return h
+
+
+# count_up: 4 (one quad), 252 (partial group of 256 rows), 924 (several groups, partial last one)
+@pytest.mark.parametrize("M,n_up,n_dn", [(4, 1, 2), (10, 5, 3), (12, 6, 2)])
+def test_separate_dn_pass_bitwise(hub, M, n_up, n_dn):
+    """Every two-pass shape gives the CSR kernel's product bit for bit, and a
+    solve through it the energy and steps of the one-pass product."""
+    import torch
+    m = W.ring(M, U=3.0, n_up=n_up, n_dn=n_dn).with_params(eps=[0.07 * i for i in range(M)])
+    s = hub.Sector(m)
+    assert s.count_up % 4 == 0
+    for dt in (hub.F64, hub.F32):
+        x = s.start_vector(seed=3, dtype=dt)
+        s.set_schedule(dt, hub.SCHED_CSR)
+        y0 = s.matvec(x)
+        s.set_schedule(dt, hub.SCHED_COLUMNS, tile_cols=1, block=512, order=1)
+        g0 = s.ground_state(dtype=dt, want_vector=False)
+        shapes = [(hub.SCHED_COLUMNS, dict(tile_cols=tb, block=bs)) for tb in (1, 2, 3) for bs in (512, 1024)]
+        shapes += [(hub.SCHED_CHUNKED, dict(tile_cols=tb, quads_per_lane=q, chunk_rows=c))
+                   for tb, q in ((1, 4), (2, 4), (1, 8)) for c in (0, 100)]
+        for fam, kw in shapes:
+            s.set_schedule(dt, fam, order=2, **kw)
+            assert torch.equal(s.matvec(x), y0), (dt, fam, kw)
+            g = s.ground_state(dtype=dt, want_vector=False)
+            assert (g.e0, g.info["iters"]) == (g0.e0, g0.info["iters"]), (dt, fam, kw)
+        s.set_schedule(dt, None)
+    s.close()
+
+
+# count_up % 4 = 1, 2, 3: 21 and 126 (less than one group of 256 rows), 715 (several),
+# 20349 and 24310 (columns beyond the LDS in FP64: chunks, two passes)
+@pytest.mark.parametrize("M,n_up,n_dn", [(7, 2, 3), (9, 4, 4), (13, 4, 2), (21, 5, 1), (17, 8, 1)])
+def test_ragged_columns(hub, M, n_up, n_dn):
+    """Tuned products of columns whose length is no multiple of four equal the
+    CSR kernel's bit for bit; FP64 solves reach the oracle's energy."""
+    import torch
+    m = W.ring(M, U=2.0, n_up=n_up, n_dn=n_dn).with_params(eps=[0.05 * ((5 * i) % M) for i in range(M)])
+    s = hub.Sector(m)
+    assert s.count_up % 4 != 0
+    for dt in (hub.F64, hub.F32):
+        x = s.start_vector(seed=5, dtype=dt)
+        y = s.matvec(x)
+        s.set_schedule(dt, hub.SCHED_CSR)
+        assert torch.equal(s.matvec(x), y), dt
+        s.set_schedule(dt, None)
+    xr = s.start_vector(seed=5, normalize=False)
+    osec = oracle.Sector(m)
+    ref = oracle.spmv(osec.csr(), oracle.start_vector(5, osec.dim))
+    assert np.max(np.abs(s.matvec(xr).cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
+    _, e_ref, _ = oracle.ground_state(m, want_vector=False)
+    g = s.ground_state(want_vector=True, refine=True)
+    assert abs(g.e0 - e_ref) <= 1e-10 * abs(e_ref)
+    assert g.info["true_residual"] <= 1e-9 * abs(e_ref)
+    s.close()
