@@ -166,12 +166,12 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
 
     struct Buf {
         void *p = nullptr;
-        ~Buf() { if (p) (void)hipFree(p); }
     } b_site, b_wu, b_wd, b_part;
-    HUB_HIP(hipMalloc(&b_site.p, sizeof(double) * (size_t)nsite_blocks * 2 * kMaxSites));
-    HUB_HIP(hipMalloc(&b_wu.p, sizeof(double) * (size_t)(nnz_u > 0 ? nnz_u : 1)));
-    HUB_HIP(hipMalloc(&b_wd.p, sizeof(double) * (size_t)(nnz_d > 0 ? nnz_d : 1)));
-    HUB_HIP(hipMalloc(&b_part.p, sizeof(double) * (size_t)nchunk * (size_t)(nnz_u > 0 ? nnz_u : 1)));
+    Workspace mem(st);
+    HUB_TRY(mem.alloc(&b_site.p, sizeof(double) * (size_t)nsite_blocks * 2 * kMaxSites));
+    HUB_TRY(mem.alloc(&b_wu.p, sizeof(double) * (size_t)(nnz_u > 0 ? nnz_u : 1)));
+    HUB_TRY(mem.alloc(&b_wd.p, sizeof(double) * (size_t)(nnz_d > 0 ? nnz_d : 1)));
+    HUB_TRY(mem.alloc(&b_part.p, sizeof(double) * (size_t)nchunk * (size_t)(nnz_u > 0 ? nnz_u : 1)));
 
     hipLaunchKernelGGL(k_site_terms, dim3(nsite_blocks), dim3(AB), 0, st, g, x, cu, cd, M, U.basis, D.basis,
                        (double *)b_site.p);

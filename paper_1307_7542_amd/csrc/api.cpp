@@ -37,6 +37,7 @@ void free_sector(hub_sector *s)
 {
     if (!s) return;
     for (void *p : s->owned) (void)hipFree(p);
+    if (s->counted) ws_sectors(s->device, -1);
     s->owned.clear();
     delete s->k0;
     delete s;
@@ -46,7 +47,7 @@ template <typename T>
 hub_status dalloc(hub_sector *s, T **p, size_t n)
 {
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, (n == 0 ? 1 : n) * sizeof(T));
+    hipError_t e = device_alloc(&q, (n == 0 ? 1 : n) * sizeof(T));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(HUB_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -174,6 +175,8 @@ hub_status create(const hub_model *m, int32_t n_up, int32_t n_dn, hub_sector **o
     if (cu > INT32_MAX || cd > INT32_MAX) return fail(HUB_ERR_RANGE, "one-spin dimension exceeds 2^31");
     s->dim = cu * cd;
     HUB_HIP(hipDeviceSynchronize());
+    ws_sectors(s->device, 1);
+    s->counted = true;
     guard.s = nullptr;
     *out = s;
     return HUB_OK;

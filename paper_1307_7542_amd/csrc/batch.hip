@@ -589,7 +589,7 @@ template <typename T>
 hub_status balloc(hub_batch *b, T **p, size_t n)
 {
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, (n == 0 ? 1 : n) * sizeof(T));
+    hipError_t e = device_alloc(&q, (n == 0 ? 1 : n) * sizeof(T));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return bfail(HUB_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -753,15 +753,9 @@ hub_status tune(hub_batch *b, hipStream_t st)
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = b->off[b->P];
     T *x = nullptr, *y = nullptr;
-    HUB_HIP(hipMalloc(&x, sizeof(T) * n));
-    if (hipMalloc(&y, sizeof(T) * n) != hipSuccess) {
-        (void)hipFree(x);
-        return bfail(HUB_ERR_OOM, "tuning buffers");
-    }
-    struct Free {
-        void *a, *c;
-        ~Free() { (void)hipFree(a); (void)hipFree(c); }
-    } fr{x, y};
+    Workspace mem(st);
+    HUB_TRY(mem.alloc((void **)&x, sizeof(T) * n));
+    HUB_TRY(mem.alloc((void **)&y, sizeof(T) * n));
     hipLaunchKernelGGL(k_b_start<T>, dim3(b->nblocks), dim3(BRB), 0, st, seg_of(b), x, (uint64_t)1);
     hipEvent_t e0, e1;
     HUB_HIP(hipEventCreate(&e0));
@@ -902,20 +896,8 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     HUB_TRY(tune<T>(b, st));
     if (o->refine) HUB_TRY(tune<double>(b, st));
 
-    std::vector<void *> mem;
-    struct MemGuard {
-        std::vector<void *> &m;
-        ~MemGuard() { for (void *q : m) (void)hipFree(q); }
-    } mg{mem};
-    auto alloc = [&](void **q, size_t bytes) -> hub_status {
-        hipError_t e = hipMalloc(q, bytes == 0 ? 1 : bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return bfail(HUB_ERR_OOM, "batch workspace");
-        }
-        mem.push_back(*q);
-        return HUB_OK;
-    };
+    Workspace mem(st);
+    auto alloc = [&](void **q, size_t bytes) -> hub_status { return mem.alloc(q, bytes); };
     T *V[3];
     for (int i = 0; i < 3; ++i) HUB_TRY(alloc((void **)&V[i], sizeof(T) * n));
     T **ptrs = nullptr;

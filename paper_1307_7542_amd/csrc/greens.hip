@@ -89,24 +89,6 @@ hub_status gfail(hub_status c, const std::string &m)
     return c;
 }
 
-struct DevBuf {
-    std::vector<void *> p;
-    ~DevBuf()
-    {
-        for (void *q : p) (void)hipFree(q);
-    }
-    hub_status alloc(void **q, size_t bytes)
-    {
-        hipError_t e = hipMalloc(q, bytes == 0 ? 1 : bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return gfail(HUB_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
-        }
-        p.push_back(*q);
-        return HUB_OK;
-    }
-};
-
 // <f| (w - H)^-1 |f> = norm2 / (w - a0 - b1^2 / (w - a1 - b2^2 / (... (w - a_{m-1}))))
 std::complex<double> cfrac(const double *a, const double *b, int m, double norm2, std::complex<double> w)
 {
@@ -132,7 +114,7 @@ hub_status check_pair(const hub_sector *src, const hub_sector *dst, int spin, in
 hub_status apply_op(const hub_sector *src, const hub_sector *dst, int site, int spin, int create, const double *x,
                     double *y, hipStream_t st)
 {
-    DevBuf mem;
+    Workspace mem(st);
     const SpinTables &D = dst->spin[spin];
     int32_t *map = nullptr;
     double *sgn = nullptr;
@@ -247,7 +229,7 @@ hub_status hub_greens_function(const hub_sector *sec, double e0, const void *dev
         if ((part == 0 && N >= sec->M) || (part == 1 && N <= 0)) continue;  // empty target sector
         SectorGuard g;
         HUB_TRY(shifted_sector(sec, spin, part == 0 ? 1 : -1, &g.s));
-        DevBuf mem;
+        Workspace mem(st);
         double *f = nullptr;
         HUB_TRY(mem.alloc((void **)&f, sizeof(double) * (size_t)g.s->dim));
         HUB_TRY(apply_op(sec, g.s, site, spin, part == 0, (const double *)dev_psi, f, st));

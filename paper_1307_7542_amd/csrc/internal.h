@@ -140,6 +140,7 @@ struct hub_sector {
     float *d_U32 = nullptr;           // [M]
     size_t lds_max = 65536;           // dynamic LDS a workgroup may request
     int cu_count = 256;
+    bool counted = false;             // in ws_sectors
     std::vector<void *> owned;        // every device allocation, freed by destroy
     hub::K0Tables *k0 = nullptr;      // set for a translation-symmetric k = 0 sector
     // Product schedules per dtype (0: FP64, 1: FP32): the tuner's pick for the
@@ -153,6 +154,30 @@ struct hub_sector {
 };
 
 namespace hub {
+
+// ---- workspace (workspace.cpp) ------------------------------------------
+// Device memory for one call on the current device, taken from and given back
+// to a bounded list of idle blocks.
+hub_status ws_alloc(void **p, size_t bytes);
+// all work on the block has finished (reusable), or its state is unknown (back to the driver)
+void ws_free(int device, void *p, bool reusable);
+void ws_trim();  // gives every idle block of the current device back to the driver
+hipError_t device_alloc(void **p, size_t bytes);  // hipMalloc, once more after ws_trim() if it fails
+size_t ws_idle_bytes(int device);  // held by the list, counted as free memory by size checks
+size_t ws_limit(int device);       // most that the list keeps
+void ws_sectors(int device, int delta);  // sectors living on the device (created / destroyed)
+
+// The blocks of one call: waits for the stream and gives them back when it ends.
+struct Workspace {
+    hipStream_t st;
+    int device = 0;
+    std::vector<void *> ptrs;
+    explicit Workspace(hipStream_t stream);
+    Workspace(const Workspace &) = delete;
+    Workspace &operator=(const Workspace &) = delete;
+    ~Workspace();
+    hub_status alloc(void **p, size_t bytes);
+};
 
 // ---- setup (setup.hip) -------------------------------------------------
 hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st);

@@ -306,7 +306,7 @@ hub_status dalloc(hub_sector *s, T **p, size_t n)
 {
     void *q = nullptr;
     const size_t bytes = (n == 0 ? 1 : n) * sizeof(T);
-    hipError_t e = hipMalloc(&q, bytes);
+    hipError_t e = device_alloc(&q, bytes);
     if (e != hipSuccess) {
         set_error(std::string("hipMalloc(") + std::to_string(bytes) + "): " + hipGetErrorString(e));
         return (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) ? HUB_ERR_OOM : HUB_ERR_DEVICE;

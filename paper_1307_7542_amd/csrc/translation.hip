@@ -419,7 +419,7 @@ template <typename T>
 hub_status talloc(hub_sector *s, T **p, size_t n)
 {
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, (n == 0 ? 1 : n) * sizeof(T));
+    hipError_t e = device_alloc(&q, (n == 0 ? 1 : n) * sizeof(T));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return tfail(HUB_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));

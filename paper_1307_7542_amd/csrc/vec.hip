@@ -512,11 +512,36 @@ __global__ void k_pro_beta(const int *__restrict__ state, const double *__restri
     if (threadIdx.x == 0 && blockIdx.x == 0 && state[1]) *beta = *beta_t;
 }
 
+// psi = sum_j y_j q_j over k stored vectors, j in order: one pass over all of
+// them, four elements per lane and four vectors in flight (16-byte aligned
+// vectors; the n % 4 tail element by element).  HBM bound.
 template <typename T>
-__global__ void k_psi_basis(const T *const *__restrict__ Q, int k, const double *__restrict__ y,
-                            double *__restrict__ psi, int64_t n)
+__global__ __launch_bounds__(256) void k_psi_basis(const T *const *__restrict__ Q, int k, const double *__restrict__ y,
+                                                   double *__restrict__ psi, int64_t n)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        int j = 0;
+        for (; j + 4 <= k; j += 4) {
+            E4<T> q[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) q[u] = ld_e4(Q[j + u] + 4 * i);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r] += y[j + u] * (double)q[u].v[r];
+        }
+        for (; j < k; ++j) {
+            const E4<T> q = ld_e4(Q[j] + 4 * i);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += y[j] * (double)q.v[r];
+        }
+        double *p = psi + 4 * i;  // the caller's vector: element alignment only
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[r] = acc[r];
+    }
+    for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
         double acc = 0.0;
         for (int j = 0; j < k; ++j) acc += y[j] * (double)Q[j][i];
         psi[i] = acc;
