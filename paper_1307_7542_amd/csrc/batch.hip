@@ -74,8 +74,9 @@ struct __attribute__((aligned(sizeof(T) * N < 16 ? sizeof(T) * N : 16))) BVec {
 };
 
 // The lockstep recurrence keeps its vectors unnormalised, u_k = beta_k v_k
-// (u_0 = v_0, beta_0 taken as 1), in three rotating slots: at step k, u_k =
-// V[k % 3], u_{k-1} = V[(k + 2) % 3], and w, then u_{k+1} in place, V[(k + 1) % 3].
+// (u_0 = v_0, beta_0 taken as 1), at the places of a pointer table: at step k,
+// u_k = ptrs[k], u_{k-1} = ptrs[k - 1], and w, then u_{k+1} in place, ptrs[k + 1].
+// The places are kept vectors, or three buffers in rotation (u_k in buffer k % 3).
 template <typename T>
 struct Roles {
     T *v, *vp, *w;
@@ -85,9 +86,9 @@ template <typename T>
 __device__ __forceinline__ Roles<T> roles(T *const *ptrs, int k)
 {
     Roles<T> r;
-    r.v = ptrs[k % 3];
-    r.vp = ptrs[(k + 2) % 3];
-    r.w = ptrs[(k + 1) % 3];
+    r.v = ptrs[k];
+    r.vp = ptrs[k > 0 ? k - 1 : 0];
+    r.w = ptrs[k + 1];
     return r;
 }
 
@@ -462,6 +463,32 @@ __global__ __launch_bounds__(BRB) void k_b_psi(Seg S, double *psi, const T *v, c
     // v_k = u_k / beta_k (beta_0 taken as 1)
     const double c = y[(int64_t)pp * kmax + k] * (k > 0 ? binv(beta[(int64_t)pp * kmax + k]) : 1.0);
     SEG_LOOP(S, p, i) psi[o_p + i] = (k == 0 ? 0.0 : psi[o_p + i]) + c * (double)v[o_p + i];
+}
+
+// psi = sum over j < min(mlen[p], nkept) of c_j u_j for the kept vectors, c_j =
+// y_j / beta_j: one pass over them, eight in flight per lane (64 impurity models,
+// FP64, 190 vectors of 79 MB).
+template <typename T>
+__global__ __launch_bounds__(BRB) void k_b_psi_kept(Seg S, double *psi, T *const *ptrs, const double *__restrict__ c,
+                                                    int kmax, const int *__restrict__ mlen, int nkept)
+{
+    const int pp = S.prob[blockIdx.x];
+    const int m = min(mlen[pp], nkept);
+    const double *__restrict__ cp = c + (int64_t)pp * kmax;
+    SEG_LOOP(S, p, i)
+    {
+        double acc = 0.0;
+        int j = 0;
+        for (; j + 8 <= m; j += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = ptrs[j + u][o_p + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += cp[j + u] * (double)v[u];
+        }
+        for (; j < m; ++j) acc += cp[j] * (double)ptrs[j][o_p + i];
+        psi[o_p + i] = acc;
+    }
 }
 
 // psi *= scale[p]
@@ -903,7 +930,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     T **ptrs = nullptr;
     int *step = nullptr, *active = nullptr, *mlen = nullptr;
     double *alpha = nullptr, *beta = nullptr, *partial = nullptr, *nrm = nullptr, *ycoef = nullptr;
-    HUB_TRY(alloc((void **)&ptrs, sizeof(T *) * 3));
+    HUB_TRY(alloc((void **)&ptrs, sizeof(T *) * (size_t)(max_iter + 2)));
     HUB_TRY(alloc((void **)&step, sizeof(int) * 4));
     unsigned int *done = reinterpret_cast<unsigned int *>(step + 1);  // arrival counter of k_b_beta
     HUB_TRY(alloc((void **)&active, sizeof(int) * P));
@@ -915,7 +942,30 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     HUB_TRY(alloc((void **)&ipart, sizeof(double) * (size_t)std::max(1, b->nitems[di])));
     HUB_TRY(alloc((void **)&nrm, sizeof(double) * (size_t)P * 4));
     HUB_TRY(alloc((void **)&ycoef, sizeof(double) * (size_t)P * kmax));
-    HUB_HIP(hipMemcpyAsync(ptrs, V, sizeof(T *) * 3, hipMemcpyHostToDevice, st));
+    // places of u_0 .. u_{max_iter}: kept ones while psi is wanted and the budget
+    // lasts, then the three buffers; written to the device 64 at a time, before
+    // the steps that use them
+    const bool want_psi = psi && (o->want_vector || o->refine);
+    KeptVectors kept(mem);
+    if (want_psi) {
+        size_t free_b = 0, total_b = 0;
+        HUB_HIP(hipMemGetInfo(&free_b, &total_b));
+        kept.budget(sizeof(T) * (size_t)n, free_b + ws_idle_bytes(b->device), max_iter + 1);
+    }
+    std::vector<T *> hptr;
+    hptr.reserve((size_t)max_iter + 2);
+    auto places = [&](int upto) -> hub_status {  // at least u_0 .. u_upto
+        const size_t have = hptr.size();
+        if ((int)have > upto) return HUB_OK;
+        const size_t want = std::min<size_t>((size_t)max_iter + 2, std::max<size_t>((size_t)upto + 1, have + 64));
+        while (hptr.size() < want) {
+            T *q = (T *)kept.take();
+            hptr.push_back(q ? q : V[hptr.size() % 3]);
+        }
+        HUB_HIP(hipMemcpyAsync(ptrs + have, hptr.data() + have, sizeof(T *) * (want - have), hipMemcpyHostToDevice, st));
+        return HUB_OK;
+    };
+    HUB_TRY(places(1));
     std::vector<int> hact(P, 1);
     HUB_HIP(hipMemcpyAsync(active, hact.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
     HUB_HIP(hipMemsetAsync(step, 0, sizeof(int) * 4, st));
@@ -933,7 +983,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
         HUB_HIP(hipGetLastError());
         return HUB_OK;
     };
-    HUB_TRY(make_start(V[0]));
+    HUB_TRY(make_start(hptr[0]));
 
     // one Lanczos step, captured as a graph: the fused product; alpha and
     // u_{k+1} = w - (alpha / beta_k) u_k; beta_{k+1} and the step counter
@@ -1036,6 +1086,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
         return HUB_OK;
     };
     auto enqueue_steps = [&](int nsteps) -> hub_status {
+        HUB_TRY(places(k + nsteps));
         if (gexec_g && nsteps == check_every) {
             HUB_HIP(hipGraphLaunch(gexec_g, st));
             replays += nsteps;
@@ -1120,30 +1171,48 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     }
     std::vector<double> e0(theta);
 
-    if (psi && (o->want_vector || o->refine)) {
-        // second pass with the stored alpha / beta; psi = sum_j (y_j / beta_j) u_j per sector
+    if (want_psi) {
+        // psi = sum_j (y_j / beta_j) u_j per sector: the kept vectors in one pass, the
+        // others by a second run with the stored alpha / beta
         int mmax = 0;
-        std::vector<double> hy((size_t)P * kmax, 0.0);
+        std::vector<double> hy((size_t)P * kmax, 0.0), hc((size_t)P * kmax, 0.0), hbeta((size_t)P * kmax);
+        HUB_HIP(hipMemcpyAsync(hbeta.data(), beta, sizeof(double) * hbeta.size(), hipMemcpyDeviceToHost, st));
+        HUB_HIP(hipStreamSynchronize(st));
         for (int p = 0; p < P; ++p) {
             mmax = std::max(mmax, m_final[p]);
-            for (int j = 0; j < m_final[p]; ++j) hy[(size_t)p * kmax + j] = ys[p][j];
+            for (int j = 0; j < m_final[p]; ++j) {
+                const size_t q = (size_t)p * kmax + j;
+                hy[q] = ys[p][j];
+                hc[q] = j == 0 ? hy[q] : hbeta[q] > 0.0 ? hy[q] * (1.0 / hbeta[q]) : 0.0;
+            }
         }
+        double *coef = nullptr;
+        HUB_TRY(alloc((void **)&coef, sizeof(double) * hc.size()));
+        HUB_HIP(hipMemcpyAsync(coef, hc.data(), sizeof(double) * hc.size(), hipMemcpyHostToDevice, st));
         HUB_HIP(hipMemcpyAsync(ycoef, hy.data(), sizeof(double) * hy.size(), hipMemcpyHostToDevice, st));
         HUB_HIP(hipMemcpyAsync(mlen, m_final.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
-        HUB_TRY(make_start(V[0]));
-        T *vp = V[2], *vc = V[0], *vn = V[1];
-        for (int j = 0; j < mmax; ++j) {
+        const int nk = (int)kept.u.size();
+        T *vp = V[2], *vc = V[0];
+        if (nk > 0) {
+            hipLaunchKernelGGL(k_b_psi_kept<T>, dim3(b->nblocks), dim3(BRB), 0, st, S, psi, ptrs,
+                               (const double *)coef, kmax, (const int *)mlen, nk);
+            vc = hptr[(size_t)nk - 1];
+            vp = hptr[(size_t)std::max(0, nk - 2)];
+        } else {
+            HUB_TRY(make_start(vc));
             hipLaunchKernelGGL(k_b_psi<T>, dim3(b->nblocks), dim3(BRB), 0, st, S, psi, (const T *)vc,
-                               (const double *)ycoef, (const double *)beta, kmax, j, (const int *)mlen);
-            if (j + 1 >= mmax) break;
+                               (const double *)ycoef, (const double *)beta, kmax, 0, (const int *)mlen);
+        }
+        for (int j = std::max(0, nk - 1); j + 1 < mmax; ++j) {
+            T *vn = V[0] != vc && V[0] != vp ? V[0] : V[1] != vc && V[1] != vp ? V[1] : V[2];
             HUB_TRY((launch_batch_product<T, false>(b, vc, vn, nullptr, nullptr, nullptr, st)));
             hipLaunchKernelGGL(k_b_replay<T>, dim3(b->nblocks), dim3(BRB), 0, st, S, vn, (const T *)vc,
                                (const T *)vp, (const double *)alpha, (const double *)beta, kmax, j,
                                (const int *)mlen);
-            T *tmp = vp;
+            hipLaunchKernelGGL(k_b_psi<T>, dim3(b->nblocks), dim3(BRB), 0, st, S, psi, (const T *)vn,
+                               (const double *)ycoef, (const double *)beta, kmax, j + 1, (const int *)mlen);
             vp = vc;
             vc = vn;
-            vn = tmp;
         }
         // normalise and fix the sign (largest-magnitude entry positive, lowest index on ties), on the device
         double *pa = nullptr;

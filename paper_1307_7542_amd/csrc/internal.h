@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <deque>
 #include <mutex>
@@ -177,6 +178,50 @@ struct Workspace {
     Workspace &operator=(const Workspace &) = delete;
     ~Workspace();
     hub_status alloc(void **p, size_t bytes);
+};
+
+// The unnormalised vectors u_0, u_1, ... of the plain recurrence, kept for the
+// eigenvector: psi = sum_j (y_j / beta_j) u_j is then one pass over them instead
+// of a second run of the recurrence (ring M=14 FP64, 188 steps: 17.7 GB read
+// once, 3.1 ms, against 40 ms).  They live in slabs of 64 vectors, up to what the
+// workspace list keeps for the next solve and an eighth of the device memory
+// that is free; the vectors beyond that (or beyond a slab that cannot be
+// allocated) are run again from the last two kept ones.
+struct KeptVectors {
+    Workspace &mem;
+    size_t bytes = 0;        // of one vector, rounded up to keep the slab aligned
+    int64_t cap = 0;         // vectors that may be kept
+    std::vector<void *> u;   // places handed out so far
+    char *next = nullptr;
+    int64_t left = 0;
+    explicit KeptVectors(Workspace &m) : mem(m) {}
+    void budget(size_t vec_bytes, size_t free_bytes, int64_t most)
+    {
+        bytes = (vec_bytes + 255) / 256 * 256;
+        const size_t lim = ws_limit(mem.device);
+        cap = (int64_t)(std::min(free_bytes / 8, lim - lim / 32) / bytes);
+        if (cap < 8) cap = 0;  // a handful would not pay for the pass over psi
+        cap = std::min(cap, most);
+    }
+    // the place of the next vector, or NULL once the budget is spent
+    void *take()
+    {
+        if ((int64_t)u.size() >= cap) return nullptr;
+        if (left == 0) {
+            const int64_t k = std::min<int64_t>(64, cap - (int64_t)u.size());
+            void *p = nullptr;
+            if (mem.alloc(&p, bytes * (size_t)k) != HUB_OK) {
+                cap = (int64_t)u.size();
+                return nullptr;
+            }
+            next = (char *)p;
+            left = k;
+        }
+        u.push_back(next);
+        next += bytes;
+        --left;
+        return u.back();
+    }
 };
 
 // ---- setup (setup.hip) -------------------------------------------------

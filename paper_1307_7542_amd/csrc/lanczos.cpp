@@ -125,42 +125,6 @@ double tri_lowest(const double *a, const double *b, int m, std::vector<double> &
 
 namespace {
 
-// The unnormalised vectors u_0, u_1, ... of the plain recurrence, kept for the
-// eigenvector: psi = sum_j (y_j / beta_j) u_j is then one pass over them instead
-// of a second run of the recurrence (ring M=14 FP64, 188 steps: 17.7 GB read
-// once, 3.1 ms, against 40 ms).  They live in slabs of 64 vectors, up to what the
-// workspace list keeps for the next solve and an eighth of the device memory
-// that is free; the vectors beyond that (or beyond a slab that cannot be
-// allocated) are run again from the last two kept ones.
-struct KeptVectors {
-    Workspace &mem;
-    size_t bytes = 0;        // of one vector, rounded up to keep the slab aligned
-    int64_t cap = 0;         // vectors that may be kept
-    std::vector<void *> u;   // places handed out so far
-    char *next = nullptr;
-    int64_t left = 0;
-    explicit KeptVectors(Workspace &m) : mem(m) {}
-    // the place of the next vector, or NULL once the budget is spent
-    void *take()
-    {
-        if ((int64_t)u.size() >= cap) return nullptr;
-        if (left == 0) {
-            const int64_t k = std::min<int64_t>(64, cap - (int64_t)u.size());
-            void *p = nullptr;
-            if (mem.alloc(&p, bytes * (size_t)k) != HUB_OK) {
-                cap = (int64_t)u.size();
-                return nullptr;
-            }
-            next = (char *)p;
-            left = k;
-        }
-        u.push_back(next);
-        next += bytes;
-        --left;
-        return u.back();
-    }
-};
-
 // HIP events around sampled product launches: every `every`-th product when
 // on (an event record between two kernels delays the second by a few
 // microseconds, so timing every launch of a short product slows the solve).
@@ -491,10 +455,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     KeptVectors kept(mem);
     std::vector<double> kept_coef;
     if (unnorm && want_vec) {
-        kept.bytes = (es * (size_t)n + 255) / 256 * 256;
-        kept.cap = (int64_t)(std::min(free_b / 8, ws_limit(s->device) - ws_limit(s->device) / 32) / kept.bytes);
-        if (kept.cap < 8) kept.cap = 0;  // a handful would not pay for the pass over psi
-        kept.cap = std::min<int64_t>(kept.cap, max_iter);
+        kept.budget(es * (size_t)n, free_b, max_iter);
         if (kept.cap > 0) {
             void *u0 = kept.take();
             if (u0) {
