@@ -9,8 +9,15 @@
 //                        (-esign) <g[:, b'], x[:, l]>  (column dot products),
 //   - U_i:   sum_{a,b} n_i(up_a & dn_b) g[a,b] x[a,b],
 //   - eps_i: sum_{a,b} (n_i(up_a) + n_i(dn_b)) g[a,b] x[a,b].
-// Every reduction has a fixed order (per-entry partial sums over fixed column
-// chunks, LDS trees, then in-order sums), so the result is reproducible.
+//
+// No partial result per matrix entry goes through memory.  Spin up: a state has
+// at most one hop per bond, so a table of partners [bond][state] (none where the
+// bond's ends are equally occupied) lets a lane keep one accumulator per bond in
+// registers, NB bonds at a time.  Spin down: the entries are uniform over a
+// wavefront, which sums eight of them at a time over its lanes and adds them to
+// its bond accumulators in LDS.  Every reduction has a fixed order (lanes
+// over a fixed set of rows and columns, butterflies, in-order sums), so the
+// result is reproducible.
 #include <vector>
 
 #include "internal.h"
@@ -18,138 +25,343 @@
 namespace hub {
 namespace {
 
-constexpr int AB = 256;
+constexpr int NB = 32;  // bonds per launch (their accumulators are 64 registers)
+constexpr uint32_t kNone = 0x7FFFFFFFu;
 
-__device__ __forceinline__ double block_sum_a(double v, double *s)
+// -esign for a hop across bond (i < j) from state x: esign = (-1)^(occupied strictly between)
+__device__ __forceinline__ bool esign_positive(uint32_t x, int i, int j)
 {
-    s[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = AB / 2; off > 0; off >>= 1) {
-        if (threadIdx.x < (unsigned)off) s[threadIdx.x] += s[threadIdx.x + off];
-        __syncthreads();
-    }
-    const double r = s[0];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ double neg_esign(uint32_t x, int i, int j)
-{
-    // -esign for a hop across bond (i < j) from state x: esign = (-1)^(occupied strictly between)
     const uint32_t below_j = (j >= 32) ? 0xFFFFFFFFu : ((1u << j) - 1u);
     const uint32_t upto_i = (i >= 31) ? 0xFFFFFFFFu : ((1u << (i + 1)) - 1u);
-    return (__popc(x & below_j & ~upto_i) & 1) ? 1.0 : -1.0;
+    return (__popc(x & below_j & ~upto_i) & 1) == 0;
 }
 
-// Site terms: per block partial sums of the 2M site accumulators.
-__global__ __launch_bounds__(AB) void k_site_terms(const double *__restrict__ g, const double *__restrict__ x,
-                                                   int cu, int cd, int M, const uint32_t *__restrict__ up,
-                                                   const uint32_t *__restrict__ dn, double *__restrict__ partial)
+// Partner of every state across bonds e0 .. e0 + NB - 1, [NB][state]: {-esign <
+// 0 : 1, basis index : 31}, kNone without a hop.
+__global__ __launch_bounds__(256) void k_partners(int64_t count, const int32_t *__restrict__ rp,
+                                                  const int32_t *__restrict__ col, const int32_t *__restrict__ bond,
+                                                  const uint32_t *__restrict__ basis, const int32_t *__restrict__ bi,
+                                                  const int32_t *__restrict__ bj, int e0, uint32_t *__restrict__ out)
 {
-    __shared__ double s[AB];
-    double aU[kMaxSites], aE[kMaxSites];
-#pragma unroll
-    for (int i = 0; i < kMaxSites; ++i) { aU[i] = 0.0; aE[i] = 0.0; }
-    for (int b = blockIdx.x; b < cd; b += gridDim.x) {
-        const uint32_t db = dn[b];
-        for (int a = threadIdx.x; a < cu; a += AB) {
-            const int64_t idx = (int64_t)b * cu + a;
-            const double gx = g[idx] * x[idx];
-            const uint32_t ua = up[a];
-            const uint32_t both = ua & db;
-#pragma unroll
-            for (int i = 0; i < kMaxSites; ++i) {
-                aU[i] += ((both >> i) & 1u) ? gx : 0.0;
-                aE[i] += (double)(((ua >> i) & 1u) + ((db >> i) & 1u)) * gx;
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxSites; ++i) {
-        if (i < M) {
-            const double rU = block_sum_a(aU[i], s);
-            const double rE = block_sum_a(aE[i], s);
-            if (threadIdx.x == 0) {
-                partial[(int64_t)blockIdx.x * 2 * kMaxSites + i] = rU;
-                partial[(int64_t)blockIdx.x * 2 * kMaxSites + kMaxSites + i] = rE;
-            }
-        }
-    }
-}
-
-// Down-spin entries: one block per row b of H_dn, a column dot product per entry.
-__global__ __launch_bounds__(AB) void k_dn_terms(const double *__restrict__ g, const double *__restrict__ x, int cu,
-                                                 const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                                 const int32_t *__restrict__ bond, const uint32_t *__restrict__ basis,
-                                                 const int32_t *__restrict__ bi, const int32_t *__restrict__ bj,
-                                                 double *__restrict__ wout)
-{
-    __shared__ double s[AB];
-    const int b = blockIdx.x;
-    const double *gb = g + (int64_t)b * cu;
-    for (int k = rp[b]; k < rp[b + 1]; ++k) {
-        const double *xl = x + (int64_t)col[k] * cu;
-        double acc = 0.0;
-        for (int a = threadIdx.x; a < cu; a += AB) acc += gb[a] * xl[a];
-        const double r = block_sum_a(acc, s);
-        if (threadIdx.x == 0) {
-            const int e = bond[k];
-            wout[k] = neg_esign(basis[b], bi[e], bj[e]) * r;
-        }
-    }
-}
-
-// Up-spin entries: blocks own column chunks; a lane owns row a and keeps one
-// accumulator per entry of that row (in windows of UW entries).
-constexpr int UW = 16;
-
-__global__ __launch_bounds__(AB) void k_up_terms(const double *__restrict__ g, const double *__restrict__ x, int cu,
-                                                 int cd, const int32_t *__restrict__ rp,
-                                                 const int32_t *__restrict__ col, int max_row, int nchunk,
-                                                 double *__restrict__ partial, int64_t nnz)
-{
-    const int chunk = blockIdx.x;
-    const int cols_per = (cd + nchunk - 1) / nchunk;
-    const int b0 = chunk * cols_per;
-    const int b1 = min(cd, b0 + cols_per);
-    for (int a = blockIdx.y * AB + threadIdx.x; a < cu; a += gridDim.y * AB) {
-        const int s0 = rp[a], len = rp[a + 1] - s0;
-        for (int w0 = 0; w0 < len; w0 += UW) {
-            double acc[UW];
-            int cl[UW];
-#pragma unroll
-            for (int u = 0; u < UW; ++u) {
-                acc[u] = 0.0;
-                cl[u] = (w0 + u < len) ? col[s0 + w0 + u] : 0;
-            }
-            for (int b = b0; b < b1; ++b) {
-                const double ga = g[(int64_t)b * cu + a];
-                const double *xb = x + (int64_t)b * cu;
-#pragma unroll
-                for (int u = 0; u < UW; ++u)
-                    if (w0 + u < len) acc[u] += ga * xb[cl[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < UW; ++u)
-                if (w0 + u < len) partial[(int64_t)chunk * nnz + s0 + w0 + u] = acc[u];
-        }
-    }
-    (void)max_row;
-}
-
-__global__ void k_up_finish(const double *__restrict__ partial, int nchunk, int64_t nnz, int cu,
-                            const int32_t *__restrict__ rp, const int32_t *__restrict__ bond,
-                            const uint32_t *__restrict__ basis, const int32_t *__restrict__ bi,
-                            const int32_t *__restrict__ bj, double *__restrict__ wout)
-{
-    const int a = blockIdx.x * blockDim.x + threadIdx.x;
-    if (a >= cu) return;
+    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (a >= count) return;
+    for (int e = 0; e < NB; ++e) out[e * count + a] = kNone;
     for (int k = rp[a]; k < rp[a + 1]; ++k) {
-        double acc = 0.0;
-        for (int c = 0; c < nchunk; ++c) acc += partial[(int64_t)c * nnz + k];
-        const int e = bond[k];
-        wout[k] = neg_esign(basis[a], bi[e], bj[e]) * acc;
+        const int e = bond[k] - e0;
+        if (e < 0 || e >= NB) continue;
+        out[e * count + a] =
+            (uint32_t)col[k] | (esign_positive(basis[a], bi[e + e0], bj[e + e0]) ? 0x80000000u : 0u);
     }
+}
+
+// Every matrix entry as {-esign < 0 : 1, column : 31}, in CSR order
+__global__ __launch_bounds__(256) void k_entries(int64_t count, const int32_t *__restrict__ rp,
+                                                 const int32_t *__restrict__ col, const int32_t *__restrict__ bond,
+                                                 const uint32_t *__restrict__ basis, const int32_t *__restrict__ bi,
+                                                 const int32_t *__restrict__ bj, uint32_t *__restrict__ out)
+{
+    const int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (a >= count) return;
+    for (int k = rp[a]; k < rp[a + 1]; ++k)
+        out[k] = (uint32_t)col[k] | (esign_positive(basis[a], bi[bond[k]], bj[bond[k]]) ? 0x80000000u : 0u);
+}
+
+// The table of [NB][state] partners as pairs of bonds in one word, for columns
+// that are staged whole: per half {-esign < 0 : 1, index : 15}, index = count
+// without a hop (count <= 32767).
+__global__ __launch_bounds__(256) void k_partner_pairs(int count, const uint32_t *__restrict__ part,
+                                                       uint32_t *__restrict__ out)
+{
+    const int i = (int)blockIdx.x * 256 + threadIdx.x;
+    const int e2 = (int)blockIdx.y;
+    if (i >= count) return;
+    uint32_t h[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint32_t p = part[(int64_t)(2 * e2 + u) * count + i];
+        h[u] = p == kNone ? (uint32_t)count : (p & 0x7FFFu) | ((p >> 31) << 15);
+    }
+    out[(int64_t)e2 * count + i] = h[0] | (h[1] << 16);
+}
+
+__device__ __forceinline__ double wave_sum_a(double v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// The sign of bit 31 of p applied to v.
+__device__ __forceinline__ double signed_by(double v, uint32_t p)
+{
+    return __hiloint2double(__double2hiint(v) ^ (int)(p & 0x80000000u), __double2loint(v));
+}
+
+// Spin-up bonds: a workgroup takes columns in turn, stages rows [c0, c0 + n) of
+// the x column in LDS (place n holds zero, for partners elsewhere or none), and
+// each lane adds g[a] x[partner] of its rows to the bond's accumulator.
+// Bound by the LDS gathers, one per row and bond (half of them the broadcast zero).
+// 768 lanes: the accumulators spill at the 128 registers a lane has with 1024.
+constexpr int UPB = 768;
+
+template <bool PAIRS>
+__global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, const double *__restrict__ x, int cu,
+                                                   int cd, int c0, int n, const uint32_t *__restrict__ part, int nb,
+                                                   double *__restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    double *xs = reinterpret_cast<double *>(smem_raw);
+    double acc[NB];
+#pragma unroll
+    for (int e = 0; e < NB; ++e) acc[e] = 0.0;
+    for (int b = blockIdx.x; b < cd; b += gridDim.x) {
+        const double *__restrict__ xb = x + (int64_t)b * cu + c0, *__restrict__ gb = g + (int64_t)b * cu;
+        for (int a = threadIdx.x; a < n; a += UPB) xs[a] = xb[a];
+        if (threadIdx.x == 0) xs[n] = 0.0;
+        __syncthreads();
+        for (int a = threadIdx.x; a < cu; a += UPB) {
+            const double ga = gb[a];
+            if (PAIRS) {
+#pragma unroll
+                for (int e8 = 0; e8 < NB; e8 += 8) {
+                    if (e8 >= nb) break;
+                    uint32_t p[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) p[u] = part[(int64_t)(e8 / 2 + u) * cu + a];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const double v0 = xs[p[u] & 0x7FFFu], v1 = xs[(p[u] >> 16) & 0x7FFFu];
+                        acc[e8 + 2 * u] = fma(signed_by(ga, p[u] << 16), v0, acc[e8 + 2 * u]);
+                        acc[e8 + 2 * u + 1] = fma(signed_by(ga, p[u]), v1, acc[e8 + 2 * u + 1]);
+                    }
+                }
+                continue;
+            }
+#pragma unroll
+            for (int e8 = 0; e8 < NB; e8 += 8) {
+                if (e8 >= nb) break;
+                uint32_t p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) p[u] = part[(int64_t)min(e8 + u, nb - 1) * cu + a];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double v = xs[min((p[u] & kNone) - (uint32_t)c0, (uint32_t)n)];
+                    acc[e8 + u] = fma(signed_by(ga, p[u]), v, acc[e8 + u]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int e = 0; e < NB; ++e) {
+        const double r = wave_sum_a(acc[e]);
+        if (lane == 0 && e < nb) xs[wave * NB + e] = r;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < nb) {
+        double r = 0.0;
+#pragma unroll
+        for (int w = 0; w < UPB / 64; ++w) r += xs[w * NB + threadIdx.x];
+        out[(int64_t)blockIdx.x * NB + threadIdx.x] = r;
+    }
+}
+
+// Rows r0, r0 + 1 of a column; FULL: both inside it, else zero from row cu on.
+template <bool FULL>
+__device__ __forceinline__ double2 ld_rows(const double *__restrict__ col, int r0, int cu)
+{
+    typedef double VecU __attribute__((ext_vector_type(2), aligned(8)));
+    if (FULL) {
+        const VecU v = *reinterpret_cast<const VecU *>(col + r0);
+        return make_double2(v[0], v[1]);
+    }
+    return make_double2(r0 < cu ? col[r0] : 0.0, r0 + 1 < cu ? col[r0 + 1] : 0.0);
+}
+
+// v of another lane of the same row of 16, chosen by the DPP control C
+template <int C>
+__device__ __forceinline__ double dpp(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), C, 0xf, 0xf, false));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kRor4 = 0x124, kRor8 = 0x128;  // quad_perm, row_ror (8: xor 8)
+
+// Entry of eight whose sum wave_sum8 leaves in lane l (the same in lanes that differ in bits 2, 3, 5)
+__device__ __forceinline__ int wave_sum8_entry(int l) { return (l & 3) | ((l >> 2) & 4); }
+
+// The sums over the wavefront of eight values per lane; lanes keep half of the
+// values in each of three exchanges, so that one value is left to add up.
+__device__ __forceinline__ double wave_sum8(const double (&p)[8], int lane)
+{
+    double a[4], b[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        a[i] = ((lane & 1) ? p[2 * i + 1] : p[2 * i]) + dpp<kXor1>((lane & 1) ? p[2 * i] : p[2 * i + 1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        b[i] = ((lane & 2) ? a[2 * i + 1] : a[2 * i]) + dpp<kXor2>((lane & 2) ? a[2 * i] : a[2 * i + 1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {  // over the row of 16 lanes: xor 8, then 4
+        b[i] += dpp<kRor8>(b[i]);
+        b[i] += dpp<kRor4>(b[i]);
+    }
+    double c = ((lane & 16) ? b[1] : b[0]) + __shfl_xor((lane & 16) ? b[0] : b[1], 16, 64);
+    c += __shfl_xor(c, 32, 64);
+    return c;
+}
+
+// slot[bond of entry] += -esign <g[:, b], x[:, column of entry]> over rows r0, r0 +
+// 1 of columns b0, b0 + step, ... < cd, by one wavefront
+template <bool FULL>
+__device__ __forceinline__ void dn_columns(double *slot, const double *__restrict__ g, const double *__restrict__ x,
+                                           int cu, int cd, int r0, int b0, int step, const int32_t *__restrict__ rp,
+                                           const uint32_t *__restrict__ ent, const int32_t *__restrict__ bond, int lane)
+{
+    for (int b = b0; b < cd; b += step) {
+        const double2 gv = ld_rows<FULL>(g + (int64_t)b * cu, r0, cu);
+        const int ks = rp[b], n = rp[b + 1] - ks;
+        const uint32_t *__restrict__ e = ent + ks;
+        const int lu = wave_sum8_entry(lane);
+        for (int k = 0; k < n; k += 8) {
+            const int m = min(8, n - k);
+            const bool mine = (lane & 44) == 0 && lu < m;
+            const int bd = mine ? bond[ks + k + lu] : 0;
+            const uint32_t es = mine ? e[k + lu] : 0u;
+            double2 v[8];
+            if (m == 8) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = ld_rows<FULL>(x + (uint64_t)(e[k + u] & kNone) * (uint32_t)cu, r0, cu);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    v[u] = make_double2(0.0, 0.0);
+                    if (u < m) v[u] = ld_rows<FULL>(x + (uint64_t)(e[k + u] & kNone) * (uint32_t)cu, r0, cu);
+                }
+            }
+            double p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = fma(gv.x, v[u].x, gv.y * v[u].y);
+            const double r = wave_sum8(p, lane);
+            if (mine) slot[bd] += (es & 0x80000000u) ? -r : r;
+        }
+    }
+}
+
+// Spin-down bonds: a segment of 128 rows belongs to 4 ntile wavefronts that take
+// its columns in turn, so that together they sweep the columns in order (ordered
+// by segment, an eighth per XCD, as k_dn_rows of the product); slots [nb] per
+// wavefront in LDS (the bonds of a column's entries are distinct).  Bound as
+// k_dn_rows by the lines in flight: a segment has as many workgroups as an XCD
+// runs at a time, so that they all read one band of rows out of its L2.
+__global__ __launch_bounds__(256) void k_dn_bonds(const double *__restrict__ g, const double *__restrict__ x, int cu,
+                                                  int cd, int ntile, int nwork, const int32_t *__restrict__ rp,
+                                                  const uint32_t *__restrict__ ent, const int32_t *__restrict__ bond,
+                                                  int nb, double *__restrict__ out)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int per = (nwork + 7) >> 3;
+    const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if ((int)(blockIdx.x >> 3) >= per || blk >= nwork) return;
+    double *slot = reinterpret_cast<double *>(smem_raw) + w * nb;
+    for (int e = lane; e < nb; e += 64) slot[e] = 0.0;
+    const int seg = (int)((uint32_t)blk / (uint32_t)ntile), tile = blk - seg * ntile;
+    const int r0 = seg * 128 + 2 * lane, b0 = tile * 4 + w, step = 4 * ntile;
+    if (seg * 128 + 128 <= cu) dn_columns<true>(slot, g, x, cu, cd, r0, b0, step, rp, ent, bond, lane);
+    else dn_columns<false>(slot, g, x, cu, cd, r0, b0, step, rp, ent, bond, lane);
+    __syncthreads();
+    const double *all = reinterpret_cast<const double *>(smem_raw);
+    for (int e = threadIdx.x; e < nb; e += 256)
+        out[(int64_t)blk * nb + e] = (all[e] + all[nb + e]) + (all[2 * nb + e] + all[3 * nb + e]);
+}
+
+// Site forms: a wavefront takes columns in turn; over a column its lanes sum t_i
+// = sum_a n_i(a) g x and s = sum_a g x, and the column's bits are uniform:
+// U_i gets n_i(b) t_i, eps_i gets t_i + n_i(b) s.  HBM bound (both vectors once).
+template <int MM>
+__global__ __launch_bounds__(256) void k_site_terms(const double *__restrict__ g, const double *__restrict__ x, int cu,
+                                                    int cd, int M, const uint32_t *__restrict__ up,
+                                                    const uint32_t *__restrict__ dn, double *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    double aU[MM], aE[MM];
+#pragma unroll
+    for (int i = 0; i < MM; ++i) aU[i] = aE[i] = 0.0;
+    for (int b = wave; b < cd; b += (int)gridDim.x * 4) {
+        const double *__restrict__ gb = g + (int64_t)b * cu, *__restrict__ xb = x + (int64_t)b * cu;
+        double t[MM], s = 0.0;
+#pragma unroll
+        for (int i = 0; i < MM; ++i) t[i] = 0.0;
+        for (int r = 0; r < cu; r += 256) {
+            double gx[4];
+            uint32_t ua[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int a = r + u * 64 + lane;
+                gx[u] = a < cu ? gb[a] * xb[a] : 0.0;
+                ua[u] = a < cu ? up[a] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                s += gx[u];
+#pragma unroll
+                for (int i = 0; i < MM; ++i) t[i] += ((ua[u] >> i) & 1u) ? gx[u] : 0.0;
+            }
+        }
+        const uint32_t db = dn[b];
+#pragma unroll
+        for (int i = 0; i < MM; ++i) {
+            aE[i] += t[i];
+            if ((db >> i) & 1u) {
+                aU[i] += t[i];
+                aE[i] += s;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < MM; ++i) {
+        const double rU = wave_sum_a(aU[i]), rE = wave_sum_a(aE[i]);
+        if (lane == 0 && i < M) {
+            out[(int64_t)wave * 2 * kMaxSites + i] = rU;
+            out[(int64_t)wave * 2 * kMaxSites + kMaxSites + i] = rE;
+        }
+    }
+}
+
+// out[j] (+)= sum over rows r of part[r * stride + j], one workgroup per j, in a fixed order
+__global__ __launch_bounds__(1024) void k_column_sum(const double *__restrict__ part, int64_t rows, int stride,
+                                                     double *__restrict__ out, int add)
+{
+    __shared__ double s[16];
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    const double *__restrict__ p = part + blockIdx.x;
+    int64_t r = threadIdx.x;
+    for (; r + 3 * 1024 < rows; r += 4 * 1024)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] += p[(r + u * 1024) * stride];
+    for (; r < rows; r += 1024) a[0] += p[r * stride];
+    const double acc = wave_sum_a((a[0] + a[1]) + (a[2] + a[3]));
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) t += s[w];
+        out[blockIdx.x] = add ? out[blockIdx.x] + t : t;
+    }
+}
+
+hub_status allow_up_lds(size_t bytes)
+{
+    HUB_HIP(hipFuncSetAttribute((const void *)k_up_bonds<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)bytes));
+    HUB_HIP(hipFuncSetAttribute((const void *)k_up_bonds<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)bytes));
+    return HUB_OK;
 }
 
 }  // namespace
@@ -159,60 +371,80 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
 {
     const SpinTables &U = s->spin[0];
     const SpinTables &D = s->spin[1];
-    const int cu = (int)U.count, cd = (int)D.count, M = s->M;
-    const int nsite_blocks = cd < 1024 ? cd : 1024;
-    const int nchunk = cd < 64 ? cd : 64;
-    const int64_t nnz_u = U.nnz, nnz_d = D.nnz;
+    const int cu = (int)U.count, cd = (int)D.count, M = s->M, nb = s->nb;
+    // site forms: 4 wavefronts a workgroup, at most 8 workgroups per CU
+    const int site_grid = (int)std::min<int64_t>((cd + 3) / 4, 2048);
+    // spin-up bonds: one workgroup per CU or two, each with its share of the columns
+    const int up_grid = std::min(cd, 512);
+    const size_t lds = s->lds_max;
+    const int chunk = (int)std::min<int64_t>(cu, (int64_t)(lds / sizeof(double)) - 1);
+    const size_t up_lds = std::max<size_t>((size_t)chunk + 1, (UPB / 64) * NB) * sizeof(double);
+    // spin-down bonds: workgroups per segment of 128 rows (k_dn_bonds)
+    const int nseg = (cu + 127) / 128;
+    const int ntile = std::min((cd + 3) / 4, 256);
+    const int64_t nwork = (int64_t)nseg * ntile;
+    if (nwork > INT32_MAX / 8) {
+        set_error("bilinear forms: sector too large");
+        return HUB_ERR_RANGE;
+    }
 
-    struct Buf {
-        void *p = nullptr;
-    } b_site, b_wu, b_wd, b_part;
     Workspace mem(st);
-    HUB_TRY(mem.alloc(&b_site.p, sizeof(double) * (size_t)nsite_blocks * 2 * kMaxSites));
-    HUB_TRY(mem.alloc(&b_wu.p, sizeof(double) * (size_t)(nnz_u > 0 ? nnz_u : 1)));
-    HUB_TRY(mem.alloc(&b_wd.p, sizeof(double) * (size_t)(nnz_d > 0 ? nnz_d : 1)));
-    HUB_TRY(mem.alloc(&b_part.p, sizeof(double) * (size_t)nchunk * (size_t)(nnz_u > 0 ? nnz_u : 1)));
-
-    hipLaunchKernelGGL(k_site_terms, dim3(nsite_blocks), dim3(AB), 0, st, g, x, cu, cd, M, U.basis, D.basis,
-                       (double *)b_site.p);
-    if (nnz_d > 0)
-        hipLaunchKernelGGL(k_dn_terms, dim3(cd), dim3(AB), 0, st, g, x, cu, D.rp, D.col, D.bond, D.basis, s->d_bi,
-                           s->d_bj, (double *)b_wd.p);
-    if (nnz_u > 0) {
-        const int gy = (cu + AB - 1) / AB < 64 ? (cu + AB - 1) / AB : 64;
-        hipLaunchKernelGGL(k_up_terms, dim3(nchunk, gy), dim3(AB), 0, st, g, x, cu, cd, U.rp, U.col, U.max_row,
-                           nchunk, (double *)b_part.p, nnz_u);
-        hipLaunchKernelGGL(k_up_finish, dim3((cu + 255) / 256), dim3(256), 0, st, (const double *)b_part.p, nchunk,
-                           nnz_u, cu, U.rp, U.bond, U.basis, s->d_bi, s->d_bj, (double *)b_wu.p);
+    double *res = nullptr, *site = nullptr, *pu = nullptr, *pd = nullptr;  // res: bonds, then U and eps forms
+    uint32_t *tu = nullptr, *td = nullptr, *tp = nullptr;
+    const bool pairs = chunk == cu && cu <= 32767;
+    const int nres = nb + 2 * kMaxSites;
+    HUB_TRY(mem.alloc((void **)&res, sizeof(double) * (size_t)nres));
+    HUB_TRY(mem.alloc((void **)&site, sizeof(double) * (size_t)site_grid * 4 * 2 * kMaxSites));
+    if (nb > 0) {
+        HUB_TRY(mem.alloc((void **)&pu, sizeof(double) * (size_t)up_grid * NB));
+        HUB_TRY(mem.alloc((void **)&pd, sizeof(double) * (size_t)nwork * (size_t)nb));
+        HUB_TRY(mem.alloc((void **)&tu, sizeof(uint32_t) * (size_t)cu * NB));
+        HUB_TRY(mem.alloc((void **)&td, sizeof(uint32_t) * (size_t)std::max<int64_t>(D.nnz, 1)));
+        if (pairs) HUB_TRY(mem.alloc((void **)&tp, sizeof(uint32_t) * (size_t)cu * (NB / 2)));
+        HUB_TRY(allow_up_lds(lds));
+    }
+#define HUB_SITE(MMV)                                                                                           \
+    hipLaunchKernelGGL(k_site_terms<MMV>, dim3(site_grid), dim3(256), 0, st, g, x, cu, cd, M, U.basis, D.basis, site)
+    if (M <= 8) HUB_SITE(8);
+    else if (M <= 16) HUB_SITE(16);
+    else if (M <= 24) HUB_SITE(24);
+    else HUB_SITE(32);
+#undef HUB_SITE
+    hipLaunchKernelGGL(k_column_sum, dim3(2 * kMaxSites), dim3(1024), 0, st, (const double *)site,
+                       (int64_t)site_grid * 4, 2 * kMaxSites, res + nb, 0);
+    if (nb > 0) {
+        hipLaunchKernelGGL(k_entries, dim3((cd + 255) / 256), dim3(256), 0, st, (int64_t)cd, D.rp, D.col, D.bond,
+                           D.basis, s->d_bi, s->d_bj, td);
+        hipLaunchKernelGGL(k_dn_bonds, dim3((unsigned)(8 * ((nwork + 7) / 8))), dim3(256), 4 * nb * sizeof(double), st,
+                           g, x, cu, cd, ntile, (int)nwork, D.rp, (const uint32_t *)td, D.bond, nb, pd);
+        hipLaunchKernelGGL(k_column_sum, dim3(nb), dim3(1024), 0, st, (const double *)pd, nwork, nb, res, 0);
+    }
+    for (int e0 = 0; e0 < nb; e0 += NB) {
+        const int n = std::min(NB, nb - e0);
+        hipLaunchKernelGGL(k_partners, dim3((cu + 255) / 256), dim3(256), 0, st, (int64_t)cu, U.rp, U.col, U.bond,
+                           U.basis, s->d_bi, s->d_bj, e0, tu);
+        for (int c0 = 0; c0 < cu; c0 += chunk) {
+            if (pairs) {
+                hipLaunchKernelGGL(k_partner_pairs, dim3((cu + 255) / 256, NB / 2), dim3(256), 0, st, cu,
+                                   (const uint32_t *)tu, tp);
+                hipLaunchKernelGGL(k_up_bonds<true>, dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, 0, cu,
+                                   (const uint32_t *)tp, n, pu);
+            } else {
+                hipLaunchKernelGGL(k_up_bonds<false>, dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, c0,
+                                   std::min(chunk, cu - c0), (const uint32_t *)tu, n, pu);
+            }
+            hipLaunchKernelGGL(k_column_sum, dim3(n), dim3(1024), 0, st, (const double *)pu, (int64_t)up_grid, NB,
+                               res + e0, 1);
+        }
     }
     HUB_HIP(hipGetLastError());
-
-    std::vector<double> site((size_t)nsite_blocks * 2 * kMaxSites), wu((size_t)nnz_u), wd((size_t)nnz_d);
-    std::vector<int32_t> bu((size_t)nnz_u), bd((size_t)nnz_d);
-    HUB_HIP(hipMemcpyAsync(site.data(), b_site.p, sizeof(double) * site.size(), hipMemcpyDeviceToHost, st));
-    if (nnz_u > 0) {
-        HUB_HIP(hipMemcpyAsync(wu.data(), b_wu.p, sizeof(double) * nnz_u, hipMemcpyDeviceToHost, st));
-        HUB_HIP(hipMemcpyAsync(bu.data(), U.bond, sizeof(int32_t) * nnz_u, hipMemcpyDeviceToHost, st));
-    }
-    if (nnz_d > 0) {
-        HUB_HIP(hipMemcpyAsync(wd.data(), b_wd.p, sizeof(double) * nnz_d, hipMemcpyDeviceToHost, st));
-        HUB_HIP(hipMemcpyAsync(bd.data(), D.bond, sizeof(int32_t) * nnz_d, hipMemcpyDeviceToHost, st));
-    }
+    std::vector<double> h((size_t)nres);
+    HUB_HIP(hipMemcpyAsync(h.data(), res, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
     HUB_HIP(hipStreamSynchronize(st));
-
-    std::vector<double> acc_b((size_t)s->nb, 0.0);
-    for (int64_t k = 0; k < nnz_u; ++k) acc_b[bu[k]] += wu[k];
-    for (int64_t k = 0; k < nnz_d; ++k) acc_b[bd[k]] += wd[k];
-    if (dbond)
-        for (int b = 0; b < s->nb; ++b) dbond[b] = acc_b[b];
+    for (int b = 0; dbond && b < nb; ++b) dbond[b] = h[(size_t)b];
     for (int i = 0; i < M; ++i) {
-        double su = 0.0, se = 0.0;
-        for (int blk = 0; blk < nsite_blocks; ++blk) {
-            su += site[(size_t)blk * 2 * kMaxSites + i];
-            se += site[(size_t)blk * 2 * kMaxSites + kMaxSites + i];
-        }
-        if (dU) dU[i] = su;
-        if (deps) deps[i] = se;
+        if (dU) dU[i] = h[(size_t)nb + i];
+        if (deps) deps[i] = h[(size_t)nb + kMaxSites + i];
     }
     return HUB_OK;
 }
