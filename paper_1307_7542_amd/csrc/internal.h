@@ -78,12 +78,14 @@ struct K0Tables {
     int32_t *period = nullptr;  // [R] period P_i (in steps of G)
     double *rep_e64 = nullptr;  // [R] sum_i eps_i n_i of R_i
     float *rep_e32 = nullptr;
-    int32_t *hop_rp = nullptr;  // [R + 1] up hops from each representative
-    int32_t *hop_row = nullptr; // [nnz] row of the hopped state's representative
-    int32_t *hop_s = nullptr;   // [nnz] translation of the hopped state w.r.t. it
-    double *hop_c64 = nullptr;  // [nnz] -t esign * phase * sqrt(P_i / P_i')
+    int32_t *hop_n = nullptr;    // [R] up hops from each representative
+    int hop_max = 0;             // most of one row
+    // hop k of row i at [k R + i]: {translation of the hopped state w.r.t. its
+    // representative : 5, the representative's row : 27}, and -t esign * phase *
+    // sqrt(P_i / P_i')
+    uint32_t *hop_to = nullptr;
+    double *hop_c64 = nullptr;
     float *hop_c32 = nullptr;
-    int64_t hop_nnz = 0;
     int32_t *orb_off = nullptr;   // [n_orb + 1] start of each down cycle in orb_cols
     int32_t *orb_cols = nullptr;  // [count_dn] member a of cycle j -> down basis index
     int32_t *orb_sign = nullptr;  // [count_dn] c_a with G^a |D_j> = c_a |member a>
@@ -249,6 +251,8 @@ hub_status launch_matvec_lz(const hub_sector *s, int dtype, const void *x, void 
                             const double *beta_prev = nullptr, int unnorm = 0);
 // sum of np partials in a fixed order into *out (one block); sqrt_result: its square root
 hub_status launch_sum(const double *partial, int64_t np, double *out, hipStream_t st, int sqrt_result = 0);
+// y = V H_dn^T alone, for `rows` rows of any basis (at least 16 bytes of them)
+hub_status launch_dn_term(const hub_sector *s, int dtype, const void *x, void *y, int64_t rows, hipStream_t st);
 hub_status launch_diagonal(const hub_sector *s, int dtype, void *out, hipStream_t st);
 int64_t matvec_bytes(const hub_sector *s, int dtype);
 // force a product schedule (NULL: back to the tuned one); the schedule in use

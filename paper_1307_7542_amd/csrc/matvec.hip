@@ -1624,6 +1624,27 @@ hub_status launch_diagonal(const hub_sector *s, int dtype, void *out, hipStream_
     return HUB_OK;
 }
 
+// y = V H_dn^T for a state matrix of `rows` x count_dn (any row basis)
+hub_status launch_dn_term(const hub_sector *s, int dtype, const void *x, void *y, int64_t rows, hipStream_t st)
+{
+    const SpinTables &D = s->spin[1];
+    auto run = [&](auto zero) -> hub_status {
+        using T = decltype(zero);
+        MvArgs<T> A = {};
+        A.x = (const T *)x;
+        A.y = (T *)y;
+        A.cu = (int32_t)rows;
+        A.cd = (int32_t)D.count;
+        A.dn_rp = D.rp;
+        A.dn_col = D.col;
+        if constexpr (sizeof(T) == 8) A.dn_val = D.val64;
+        else A.dn_val = D.val32;
+        A.stream = (double)rows * (double)D.count * sizeof(T) > 128.0 * 1024 * 1024;
+        return launch_dn_rows<T>(A, st);
+    };
+    return dtype == HUB_F64 ? run(0.0) : run(0.0f);
+}
+
 int64_t matvec_bytes(const hub_sector *s, int dtype)
 {
     const int64_t es = (dtype == HUB_F64) ? 8 : 4;

@@ -143,13 +143,12 @@ __global__ void k_hop_fill(const uint32_t *__restrict__ reps, int64_t R, const i
                            const double *__restrict__ t, int nb, const uint64_t *__restrict__ C,
                            const int32_t *__restrict__ rep_idx, const int32_t *__restrict__ shift,
                            const int32_t *__restrict__ phase, const int32_t *__restrict__ row,
-                           const int32_t *__restrict__ rp, int32_t *__restrict__ hrow, int32_t *__restrict__ hs,
-                           double *__restrict__ hc64, float *__restrict__ hc32)
+                           uint32_t *__restrict__ hto, double *__restrict__ hc64, float *__restrict__ hc32)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= R) return;
     const uint32_t x = reps[r];
-    int o = rp[r];
+    int64_t o = r;
     for (int e = 0; e < nb; ++e) {
         const int i = bi[e], j = bj[e];
         if ((((x >> i) ^ (x >> j)) & 1u) == 0) continue;
@@ -158,11 +157,10 @@ __global__ void k_hop_fill(const uint32_t *__restrict__ reps, int64_t R, const i
         const int64_t k2 = t_rank(x2, C);
         const int r2 = row[rep_idx[k2]];
         const double c = -t[e] * (double)es * (double)phase[k2] * sqrt((double)rper[r] / (double)rper[r2]);
-        hrow[o] = r2;
-        hs[o] = shift[k2];
+        hto[o] = (uint32_t)r2 | ((uint32_t)shift[k2] << 27);
         hc64[o] = c;
         hc32[o] = (float)c;
-        ++o;
+        o += R;
     }
 }
 
@@ -206,7 +204,8 @@ struct K0Args {
     T U;
     uint32_t umask;
     const T *Us;
-    const int32_t *hop_rp, *hop_row, *hop_s;
+    const int32_t *hop_n;
+    const uint32_t *hop_to;
     const T *hop_c;
     const int32_t *dn_rp, *dn_col;
     const T *dn_val;
@@ -226,65 +225,119 @@ __device__ __forceinline__ T k0_diag(const K0Args<T> &A, uint32_t both)
     return d;
 }
 
-// One workgroup per down cycle j: the cycle's q columns are staged in LDS
-// (STAGE; R x q values) or read from global memory; wave w takes members
-// m = w, w + NW, ... and its lanes take rows i = lane + 64 r.  Each lane
-// computes whole output elements: diagonal, the H_up hops of row i (source
-// member (m - s) mod q with its phase, from per-cycle tables in LDS) and the
-// H_dn neighbour columns.
-template <typename T, int BS, bool STAGE>
+// One workgroup per down cycle j.  STAGE: the cycle's q columns are staged in
+// LDS (R x q values, member a times its phase c_a), else read from global memory.
+// A wavefront takes 64 rows of TM members at a time: the hops of a row
+// (coalesced, entry-major) are read once for all of them, hop (r2, s) of member m
+// coming from member (m - s) mod q at row r2, with the sign of the wrap around the
+// cycle (q = L; the few shorter cycles look member and sign up in a table).
+// Bound by the LDS gathers where staged.  DN: the H_dn term is already in y (its
+// own pass, k_dn_rows); else it is gathered here.
+// k = 0 block of the 16-site ring (10.4e6 states, FP64), warm: 557 us with one
+// member at a time, two byte tables in LDS and row-major hop lists; 199 us with
+// four (two: 233 us), of which the pass for H_dn takes 56.
+// vectors from this size on take the H_dn term in its own pass (15-site ring,
+// FP64, 22 MB: 60 us; below, a launch costs as much as the pass saves)
+constexpr double kK0SplitBytes = 16.0 * 1024 * 1024;
+
+template <typename T, int BS, int TM, bool STAGE, bool DN>
 __global__ __launch_bounds__(BS) void k_k0_product(K0Args<T> A)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int NW = BS / 64;
     __shared__ int32_t cols[32], csg[32];
-    __shared__ int8_t sg[32 * 32];
-    __shared__ int8_t srcm[32 * 32];
+    __shared__ int32_t from[32 * 32];  // [m][s]: source member * 2 + (sign < 0), short cycles
     T *xs = reinterpret_cast<T *>(smem_raw);
     const int j = blockIdx.x;
     const int o0 = A.orb_off[j];
     const int q = A.orb_off[j + 1] - o0;
     const int sigma = A.orb_sigma[j];
     const int64_t R = A.R;
+    const bool full = STAGE && q == A.L;
     if ((int)threadIdx.x < q) {
         cols[threadIdx.x] = A.orb_cols[o0 + threadIdx.x];
         csg[threadIdx.x] = A.orb_sign[o0 + threadIdx.x];
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < q * A.L; t += BS) {
-        const int m = t / A.L, s = t - (t / A.L) * A.L;
-        int a;
-        sg[m * 32 + s] = (int8_t)cyc_sign(csg, q, sigma, m, s, &a);
-        srcm[m * 32 + s] = (int8_t)a;
-    }
-    if (STAGE) {
+    if (!full)
+        for (int t = threadIdx.x; t < q * A.L; t += BS) {
+            const int m = t / A.L, s = t - (t / A.L) * A.L;
+            int a;
+            int g = cyc_sign(csg, q, sigma, m, s, &a);
+            if (STAGE) g *= csg[a] * csg[m];  // the staged values carry c_a, the sum gets c_m
+            from[m * 32 + s] = 2 * a + (g < 0 ? 1 : 0);
+        }
+    if (STAGE)
         for (int m = 0; m < q; ++m) {
             const T *xc = A.x + (int64_t)cols[m] * R;
-            for (int64_t i = threadIdx.x; i < R; i += BS) xs[(int64_t)m * R + i] = xc[i];
+            const T c = (T)csg[m];
+            for (int64_t i = threadIdx.x; i < R; i += BS) xs[(int64_t)m * R + i] = c * xc[i];
         }
-    }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int m = wave; m < q; m += NW) {
-        const int b = cols[m];
-        const uint32_t db = A.dn_basis[b];
-        const T eb = A.e_dn[b];
-        const int ks = A.dn_rp[b], ke = A.dn_rp[b + 1];
-        for (int64_t i = lane; i < R; i += 64) {
-            const T xv = STAGE ? xs[(int64_t)m * R + i] : A.x[(int64_t)b * R + i];
-            T acc = (k0_diag(A, A.reps[i] & db) + A.rep_e[i] + eb) * xv;
-            for (int h = A.hop_rp[i]; h < A.hop_rp[i + 1]; ++h) {
-                const int s = A.hop_s[h];
-                const int a = srcm[m * 32 + s];
-                const int64_t r2 = A.hop_row[h];
-                const T c = A.hop_c[h];
-                const T xs2 = STAGE ? xs[(int64_t)a * R + r2] : A.x[(int64_t)cols[a] * R + r2];
-                acc += (sg[m * 32 + s] < 0 ? -c : c) * xs2;
+    const int nrb = (int)((R + 63) / 64), ng = (q + TM - 1) / TM;
+    for (int task = wave; task < nrb * ng; task += NW) {
+        const int gi = task / nrb, m0 = gi * TM;
+        const int64_t i = (int64_t)(task - gi * nrb) * 64 + lane;
+        if (i >= R) continue;
+        const uint32_t up = A.reps[i];
+        const T eu = A.rep_e[i];
+        T dn[TM], acc[TM];
+#pragma unroll
+        for (int t = 0; t < TM; ++t) {
+            const int m = min(m0 + t, q - 1), b = cols[m];
+            const T *__restrict__ xc = A.x + (int64_t)b * R + i;
+            dn[t] = (T)0;
+            acc[t] = (T)0;
+            if (DN) {
+                dn[t] = A.y[(int64_t)b * R + i];
+            } else {
+                int k = A.dn_rp[b];
+                const int ke = A.dn_rp[b + 1];
+                for (; k + 4 <= ke; k += 4) {
+                    T v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = A.x[(int64_t)A.dn_col[k + u] * R + i];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) dn[t] += A.dn_val[k + u] * v[u];
+                }
+                for (; k < ke; ++k) dn[t] += A.dn_val[k] * A.x[(int64_t)A.dn_col[k] * R + i];
             }
-            T s2 = (T)0;
-            for (int k = ks; k < ke; ++k) s2 += A.dn_val[k] * A.x[(int64_t)A.dn_col[k] * R + i];
-            A.y[(int64_t)b * R + i] = acc + s2;
+            dn[t] += (k0_diag(A, up & A.dn_basis[b]) + eu + A.e_dn[b]) * *xc;
         }
+        int mo[TM];
+#pragma unroll
+        for (int t = 0; t < TM; ++t) mo[t] = min(m0 + t, q - 1) * (int)R;
+        const int n = A.hop_n[i];
+        for (int h = 0; h < n; ++h) {
+            const uint32_t to = A.hop_to[h * R + i];
+            const T c = A.hop_c[h * R + i];
+            const int s = (int)(to >> 27);
+            const int64_t r2 = to & 0x7FFFFFFu;
+            const int so = s * (int)R;  // (only used where q R values fit the LDS)
+            if (full) {
+#pragma unroll
+                for (int t = 0; t < TM; ++t) {
+                    int o = mo[t] - so;
+                    const T cw = o < 0 && sigma < 0 ? -c : c;
+                    o += o < 0 ? q * (int)R : 0;
+                    acc[t] += cw * xs[o + (int)r2];
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < TM; ++t) {
+                    const int f = from[min(m0 + t, q - 1) * 32 + s];
+                    const T v = STAGE ? xs[(int64_t)(f >> 1) * R + r2] : A.x[(int64_t)cols[f >> 1] * R + r2];
+                    acc[t] += ((f & 1) ? -c : c) * v;
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+            if (m0 + t < q) {
+                const T u = STAGE && csg[m0 + t] < 0 ? -acc[t] : acc[t];
+                A.y[(int64_t)cols[m0 + t] * R + i] = dn[t] + u;
+            }
     }
 }
 
@@ -348,9 +401,8 @@ K0Args<T> k0_args(const hub_sector *s, const void *x, void *y)
     A.uniform = s->uniformU;
     A.U = (T)s->U0;
     A.umask = s->umask;
-    A.hop_rp = K.hop_rp;
-    A.hop_row = K.hop_row;
-    A.hop_s = K.hop_s;
+    A.hop_n = K.hop_n;
+    A.hop_to = K.hop_to;
     A.dn_rp = Dn.rp;
     A.dn_col = Dn.col;
     A.orb_off = K.orb_off;
@@ -385,27 +437,42 @@ hub_status k0_project_t(const hub_sector *s, void *x, hipStream_t st)
     return HUB_OK;
 }
 
-template <typename T>
-hub_status k0_product_t(const hub_sector *s, const void *x, void *y, hipStream_t st)
+template <typename T, int TM, bool STAGE, bool DN>
+hub_status k0_launch(const hub_sector *s, const K0Args<T> &A, size_t lds, size_t dyn_max, hipStream_t st)
 {
     constexpr int BS = 1024;
-    const K0Tables &K = *s->k0;
-    const K0Args<T> A = k0_args<T>(s, x, y);
-    const size_t lds = (size_t)K.max_q * (size_t)K.R * sizeof(T);
-    // the kernel also holds up to 2.2 KB of static LDS (cycle tables)
-    const size_t dyn_max = s->lds_max - 4096;
-    if (lds <= dyn_max) {
+    if (STAGE) {
         static std::atomic<bool> attr{false};
         if (!attr) {
-            HUB_HIP(hipFuncSetAttribute((const void *)k_k0_product<T, BS, true>,
+            HUB_HIP(hipFuncSetAttribute((const void *)k_k0_product<T, BS, TM, STAGE, DN>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_max));
             attr = true;
         }
-        hipLaunchKernelGGL((k_k0_product<T, BS, true>), dim3((unsigned)K.n_orb), dim3(BS), lds, st, A);
-    } else {
-        hipLaunchKernelGGL((k_k0_product<T, BS, false>), dim3((unsigned)K.n_orb), dim3(BS), 0, st, A);
     }
+    hipLaunchKernelGGL((k_k0_product<T, BS, TM, STAGE, DN>), dim3((unsigned)s->k0->n_orb), dim3(BS), STAGE ? lds : 0, st,
+                       A);
     HUB_HIP(hipGetLastError());
+    return HUB_OK;
+}
+
+template <typename T>
+hub_status k0_product_t(const hub_sector *s, const void *x, void *y, hipStream_t st)
+{
+    const K0Tables &K = *s->k0;
+    const K0Args<T> A = k0_args<T>(s, x, y);
+    const size_t lds = (size_t)K.max_q * (size_t)K.R * sizeof(T);
+    // the kernel also holds 4.3 KB of static LDS (cycle tables)
+    const size_t dyn_max = s->lds_max - 8192;
+    const bool stage = lds <= dyn_max;
+    const bool dn = (double)s->dim * sizeof(T) > kK0SplitBytes && K.R >= 64 && K.R <= INT32_MAX;
+    if (dn) HUB_TRY(launch_dn_term(s, sizeof(T) == 8 ? HUB_F64 : HUB_F32, x, y, K.R, st));
+    // four members share a row's hops where that leaves every wavefront a task
+    const bool four = (K.R + 63) / 64 * ((K.L + 3) / 4) >= 16;
+#define HUB_K0(TMV)                                                                                                  \
+    (stage ? (dn ? k0_launch<T, TMV, true, true> : k0_launch<T, TMV, true, false>)                                  \
+           : (dn ? k0_launch<T, TMV, false, true> : k0_launch<T, TMV, false, false>))(s, A, lds, dyn_max, st)
+    HUB_TRY(four ? HUB_K0(4) : HUB_K0(1));
+#undef HUB_K0
     return k0_project_t<T>(s, y, st);
 }
 
@@ -500,24 +567,21 @@ hub_status build_k0(hub_sector *s, int w, hipStream_t st)
     hipLaunchKernelGGL(k_rep_fill, dim3(gu), dim3(256), 0, st, s->spin[0].basis, cu.is_rep, cu.row, cu.period,
                        cu.sigma, s->spin[0].e64, nu, K->reps, K->period, rsig, K->rep_e64, K->rep_e32);
     // up hops
-    int32_t *len = nullptr;
-    HUB_TRY(talloc(s, &len, R));
-    HUB_TRY(talloc(s, &K->hop_rp, R + 1));
+    HUB_TRY(talloc(s, &K->hop_n, R));
     const unsigned gr = (unsigned)((R + 255) / 256);
-    hipLaunchKernelGGL(k_hop_count, dim3(gr), dim3(256), 0, st, K->reps, R, s->d_bi, s->d_bj, s->nb, len);
+    hipLaunchKernelGGL(k_hop_count, dim3(gr), dim3(256), 0, st, K->reps, R, s->d_bi, s->d_bj, s->nb, K->hop_n);
     HUB_HIP(hipGetLastError());
-    HUB_TRY(scan_lengths(s, len, R, K->hop_rp, st));
-    int32_t nnz = 0;
-    HUB_HIP(hipMemcpyAsync(&nnz, K->hop_rp + R, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    std::vector<int32_t> hn(R);
+    HUB_HIP(hipMemcpyAsync(hn.data(), K->hop_n, sizeof(int32_t) * R, hipMemcpyDeviceToHost, st));
     HUB_HIP(hipStreamSynchronize(st));
-    K->hop_nnz = nnz;
-    HUB_TRY(talloc(s, &K->hop_row, nnz));
-    HUB_TRY(talloc(s, &K->hop_s, nnz));
-    HUB_TRY(talloc(s, &K->hop_c64, nnz));
-    HUB_TRY(talloc(s, &K->hop_c32, nnz));
+    for (int32_t n : hn) K->hop_max = std::max(K->hop_max, (int)n);
+    if (R >= (1 << 27)) return tfail(HUB_ERR_RANGE, "more than 2^27 representatives");
+    HUB_TRY(talloc(s, &K->hop_to, (size_t)K->hop_max * R));
+    HUB_TRY(talloc(s, &K->hop_c64, (size_t)K->hop_max * R));
+    HUB_TRY(talloc(s, &K->hop_c32, (size_t)K->hop_max * R));
     hipLaunchKernelGGL(k_hop_fill, dim3(gr), dim3(256), 0, st, K->reps, R, K->period, s->d_bi, s->d_bj, s->d_t,
-                       s->nb, (const uint64_t *)s->d_binom, cu.rep_idx, cu.shift, cu.phase, cu.row, K->hop_rp,
-                       K->hop_row, K->hop_s, K->hop_c64, K->hop_c32);
+                       s->nb, (const uint64_t *)s->d_binom, cu.rep_idx, cu.shift, cu.phase, cu.row,
+                       K->hop_to, K->hop_c64, K->hop_c32);
     HUB_HIP(hipGetLastError());
     // down cycles: offsets from the representatives' periods
     uint32_t *dreps = nullptr;
