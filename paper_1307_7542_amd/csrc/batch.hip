@@ -1036,7 +1036,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     } gg{graph, gexec}, gg_group{graph_g, gexec_g};
 
     std::vector<int> m_final(P, 0), conv(P, 0);
-    std::vector<double> theta(P, 0.0);
+    std::vector<double> theta(P, 0.0), ritz_res(P, 0.0);
     std::vector<std::vector<double>> ys(P);
     std::vector<double> tmax(P, 0.0);
     int replays = 0, nactive = P;
@@ -1130,14 +1130,21 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
                     break;
                 }
             }
-            std::vector<double> y;
-            const double th = tri_lowest(a, bb + 1, m, y);
-            const double res = brk ? 0.0 : std::fabs(bb[m]) * std::fabs(y[m - 1]);
+            double th = theta[p], ylast = 0.0;
+            const int mt = m_final[p];  // theta and ritz_res are those of T of this size
+            if (mt == 0 || mt >= m ||
+                !tri_lowest_below(a, bb + 1, m, ritz_bound(theta[p], ritz_res[p], a[mt]), th, ylast)) {
+                std::vector<double> y;
+                th = tri_lowest(a, bb + 1, m, y);
+                ylast = std::fabs(y[m - 1]);
+            }
+            ritz_res[p] = std::fabs(bb[m]) * ylast;
+            const double res = brk ? 0.0 : ritz_res[p];
             const double scale = std::fabs(th) > 0 ? std::fabs(th) : 1.0;
             theta[p] = th;
             m_final[p] = m;
-            ys[p] = std::move(y);
             if (brk || res <= tol * scale || (int64_t)m >= dimp) conv[p] = 1;
+            if (conv[p] || kk >= max_iter) theta[p] = tri_lowest(a, bb + 1, m, ys[p]);  // the values used
         };
         pool.run((int)act.size(), one);
         for (const int p : act)

@@ -235,6 +235,21 @@ hub_status chunk_set(const hub_sector *s, int spin, int rows, const ChunkSet **o
 hub_status rank_device(const hub_sector *s, int spin, const uint64_t *dx, int64_t n, int64_t *dout,
                        hipStream_t st);
 
+// Where the beta of a Lanczos step comes from, for the product that needs it
+// first: the square root of the sum of `np` partials, in the fixed order of the
+// single-workgroup sums, stored at *out and published to host memory with the
+// step's alpha (ab: alpha[0 .. kmax) then beta[0 .. kmax], or NULL; then step
+// count k + 1 at *step).
+struct BetaSource {
+    const double *partial = nullptr;  // NULL: beta is already in memory
+    int np = 0;
+    double *out = nullptr;
+    double *ab = nullptr;
+    int *step = nullptr;
+    const double *alpha = nullptr;
+    int k = 0, kmax = 0;
+};
+
 // ---- product (matvec.hip) ----------------------------------------------
 hub_status launch_matvec(const hub_sector *s, int dtype, const void *x, void *y, hipStream_t st);
 // Product fused with the first Lanczos update: w = H x - beta v_prev (v_prev may
@@ -242,13 +257,15 @@ hub_status launch_matvec(const hub_sector *s, int dtype, const void *x, void *y,
 // they give alpha).  unnorm: x and v_prev are the unnormalised vectors
 // beta_k v_k and beta_{k-1} v_{k-1} (beta NULL at the first step, beta_prev
 // NULL for beta_0 = 1), w = (H x) / beta_k - (beta_k / beta_{k-1}) v_prev and
-// the partials sum to beta_k alpha_k.  Available when matvec_lz_available(s, dtype).
+// the partials sum to beta_k alpha_k.  source (or NULL): beta_k is not in memory
+// yet, form it first (inside the product where its kernel can).  Available when matvec_lz_available(s, dtype).
 bool matvec_lz_available(const hub_sector *s, int dtype);
 int64_t matvec_lz_partials(const hub_sector *s);
 int64_t matvec_lz_workspace(const hub_sector *s);  // doubles of the apart buffer launch_matvec_lz needs
 hub_status launch_matvec_lz(const hub_sector *s, int dtype, const void *x, void *w, const void *vprev,
                             const double *beta, double *apart, int64_t *npart, hipStream_t st,
-                            const double *beta_prev = nullptr, int unnorm = 0);
+                            const double *beta_prev = nullptr, int unnorm = 0,
+                            const BetaSource *source = nullptr);
 // sum of np partials in a fixed order into *out (one block); sqrt_result: its square root
 hub_status launch_sum(const double *partial, int64_t np, double *out, hipStream_t st, int sqrt_result = 0);
 // y = V H_dn^T alone, for `rows` rows of any basis (at least 16 bytes of them)
@@ -290,9 +307,8 @@ hub_status launch_lz_next(int dtype, const void *w, void *vnext, const double *b
 hub_status launch_lz_b_sum(int dtype, void *w, const void *v, const double *apart, int64_t np, double *alpha_out,
                           int64_t n, double *partial, hipStream_t st, const double *beta_k = nullptr,
                           int unnorm = 0);
-// beta = sqrt(sum of the red_grid(n) partials) into *beta_out, published like launch_lz_next_sum (one block)
-hub_status launch_beta_pub(const double *partial, int64_t n, double *beta_out, hipStream_t st, double *host_ab,
-                           int *host_step, const double *alpha_k, int k, int kmax);
+// beta from its source (one block)
+hub_status launch_beta(const BetaSource &b, hipStream_t st);
 hub_status launch_lz_next_sum(int dtype, const void *w, void *vnext, const double *partial, double *beta_out,
                               int64_t n, hipStream_t st, double *host_ab = nullptr, int *host_step = nullptr,
                               const double *alpha_k = nullptr, int k = 0, int kmax = 0);
@@ -334,6 +350,8 @@ hub_status k0_project(const hub_sector *s, int dtype, void *x, hipStream_t st);
 
 // ---- Lanczos (lanczos.cpp) ---------------------------------------------
 double tri_lowest(const double *a, const double *b, int m, std::vector<double> &y);
+double ritz_bound(double theta, double r, double alpha_next);
+bool tri_lowest_below(const double *a, const double *b, int m, double x0, double &theta, double &ylast);
 hub_status lanczos_coefficients(const hub_sector *s, const double *f, int max_steps, double *alpha, double *beta,
                                 double *norm2, int32_t *steps, hipStream_t st);
 hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *e0_out, void *dev_psi,

@@ -125,6 +125,80 @@ double tri_lowest(const double *a, const double *b, int m, std::vector<double> &
 
 namespace {
 
+// Newton steps for the lowest eigenvalue of T_m from x0 above it, on the last
+// pivot of T - x eliminated from one end (`up`: from the bottom to the top row,
+// else from the top to the bottom); ylast: the magnitude of the eigenvector's
+// entry m.
+bool newton_lowest(const double *a, const double *b, int m, bool up, double x0, double &theta, double &ylast,
+                   std::vector<double> &piv)
+{
+    auto A = [&](int i) { return up ? a[i] : a[m - 1 - i]; };  // row i, 0 = where the elimination ends
+    auto Bf = [&](int i) { return up ? b[i] : b[m - 2 - i]; };  // between rows i and i + 1
+    double x = x0;
+    for (int it = 0; it < 24; ++it) {
+        double inv = 1.0 / (A(m - 1) - x), slope = -1.0;
+        if (!(inv > 0.0)) return false;
+        for (int i = m - 2; i >= 1; --i) {
+            const double q = Bf(i) * inv;
+            slope = q * q * slope - 1.0;
+            inv = 1.0 / ((A(i) - x) - Bf(i) * q);
+            if (!(inv > 0.0)) return false;
+        }
+        const double q = Bf(0) * inv, step = ((A(0) - x) - Bf(0) * q) / (q * q * slope - 1.0);
+        if (!std::isfinite(step)) return false;
+        const double eps = DBL_EPSILON * std::fabs(x);
+        if (step < -64.0 * eps) return false;  // x0 was below the eigenvalue
+        if (step > 2.0 * eps) {
+            x -= step;
+            continue;
+        }
+        theta = step > 0.0 ? x - step : x;
+        // y_{i+1} = -b_i y_i / pivot_{i+1}, from the end of the elimination
+        piv.resize((size_t)m);
+        piv[(size_t)m - 1] = A(m - 1) - theta;
+        for (int i = m - 2; i >= 1; --i) piv[(size_t)i] = (A(i) - theta) - Bf(i) * (Bf(i) / piv[(size_t)i + 1]);
+        double y = 1.0, n2 = 1.0;
+        for (int i = 0; i + 1 < m; ++i) {
+            y *= -Bf(i) / piv[(size_t)i + 1];
+            n2 += y * y;
+        }
+        ylast = (up ? std::fabs(y) : 1.0) / std::sqrt(n2);
+        return std::isfinite(n2) && std::isfinite(ylast);
+    }
+    return false;
+}
+
+}  // namespace
+
+// The lowest eigenvalue of T_m and the magnitude of its eigenvector's last
+// entry, from x0, an upper bound: what the convergence test of every step needs,
+// at a fraction of tri_lowest's cost (150 steps: about 2 against 44 us, more than
+// a whole step of a small sector takes).
+//
+// The pivots of T - x count the eigenvalues below x by their signs.  With all but
+// the last positive, the last falls monotonically and is concave up to its zero,
+// the lowest eigenvalue, and beyond it up to the next pole (the lowest eigenvalue
+// of the rows eliminated before), so Newton steps from above come down to the zero
+// without passing it.  Elimination from the bottom suits the later steps (the
+// eigenvector has decayed towards the last row), from the top the first ones.
+// False (use tri_lowest) if the signs are not these or the steps do not settle.
+bool tri_lowest_below(const double *a, const double *b, int m, double x0, double &theta, double &ylast)
+{
+    if (m < 3 || !std::isfinite(x0)) return false;
+    std::vector<double> piv;
+    return newton_lowest(a, b, m, true, x0, theta, ylast, piv) || newton_lowest(a, b, m, false, x0, theta, ylast, piv);
+}
+
+// Upper bound of the lowest eigenvalue of T_m from that of T_k, k < m (theta, with
+// residual r = beta_k |y_k|): the Rayleigh-Ritz value of its vector and e_{k+1}.
+double ritz_bound(double theta, double r, double alpha_next)
+{
+    const double d = 0.5 * (alpha_next - theta), h = d + std::sqrt(d * d + r * r);
+    return h > 0.0 ? theta - r * r / h : theta;
+}
+
+namespace {
+
 // HIP events around sampled product launches: every `every`-th product when
 // on (an event record between two kernels delays the second by a few
 // microseconds, so timing every launch of a short product slows the solve).
@@ -306,11 +380,11 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     // summed by the w -= alpha v update (lz_b below); otherwise alpha goes to aout
     int64_t np_alpha = 0;
     auto product_lz = [&](const void *x, void *y, const void *vp, const double *bk, double *aout,
-                          const double *bprev = nullptr, int un = 0) -> hub_status {
+                          const double *bprev = nullptr, int un = 0, const BetaSource *src = nullptr) -> hub_status {
         if (fused) {
             const bool timed = tm.sample();
             if (timed) HUB_TRY(tm.mark());
-            HUB_TRY(launch_matvec_lz(s, dt, x, y, vp, bk, apart, &np_alpha, st, bprev, un));
+            HUB_TRY(launch_matvec_lz(s, dt, x, y, vp, bk, apart, &np_alpha, st, bprev, un, src));
             if (timed) HUB_TRY(tm.mark());
             inf.matvec_count++;
             return HUB_OK;
@@ -379,8 +453,8 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     const bool publish = !reorth && !reproject;
     // Plain fused path: the vectors stay unnormalised, u_k = beta_k v_k (u_0 = v_0).
     // The product's epilogue and the update scale by 1 / beta_k in FP64, so no
-    // normalisation pass is needed; a step is the fused product, the update and a
-    // one-block kernel that forms and publishes beta_{k+1}.
+    // normalisation pass is needed; a step is the fused product, which first forms
+    // and publishes beta_k from the last update's partials, and the update.
     const bool unnorm = fused && publish && matvec_lz_partials(s) <= kSumInUpdate;
     const double *ha = hpin, *hb = hpin + kmax;
     hipEvent_t copied;
@@ -392,6 +466,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     std::vector<double> y;
     int m_final = 0;
     double theta = 0.0, res = 0.0;
+    int m_tested = 0;  // theta and res are those of T of this size
     bool converged = false, breakdown = false;
     double t_e0 = -1.0;
     double tmax = 0.0;
@@ -408,8 +483,16 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
                 break;
             }
         }
-        theta = tri_lowest(ha, hb + 1, mm, y);
-        res = std::fabs(hb[mm]) * std::fabs(y[mm - 1]);
+        double ylast = 0.0;
+        const bool more = m_tested > 0 && m_tested < mm;
+        if (more && tri_lowest_below(ha, hb + 1, mm, ritz_bound(theta, res, ha[m_tested]), theta, ylast)) {
+            y.clear();  // formed below, for the step that ends the solve
+        } else {
+            theta = tri_lowest(ha, hb + 1, mm, y);
+            ylast = std::fabs(y[mm - 1]);
+        }
+        m_tested = mm;
+        res = std::fabs(hb[mm]) * ylast;
         if (want_target && inf.iters_to_target < 0 &&
             std::fabs(theta - o->e0_target) <= o->e0_target_rel * std::fabs(o->e0_target)) {
             inf.iters_to_target = mm;
@@ -470,7 +553,9 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
         if (!W) W = free_buffer(v, v_prev);
         const bool check_now = k >= 1 && (k % check_every) == 0;
         const double *bk = k >= 1 ? d_beta + k : nullptr, *bprev = k >= 2 ? d_beta + k - 1 : nullptr;
-        HUB_TRY(product_lz(v, W, v_prev, bk, nullptr, bprev, 1));
+        // beta_k from the previous update's partials, published with alpha_{k-1}
+        const BetaSource src{partial, red_grid(n), d_beta + k, dpin, dflag, d_alpha + k - 1, k - 1, kmax};
+        HUB_TRY(product_lz(v, W, v_prev, bk, nullptr, bprev, 1, k >= 1 ? &src : nullptr));
         HUB_TRY(launch_lz_b_sum(dt, W, v, apart, np_alpha, d_alpha + k, n, partial, st, bk, 1));
         if (check_now) {
             HUB_TRY(wait_published(k));  // step k keeps running meanwhile
@@ -483,7 +568,6 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
             check(k + 1);
             break;
         }
-        HUB_TRY(launch_beta_pub(partial, n, d_beta + k + 1, st, dpin, dflag, d_alpha + k, k, kmax));
         v_prev = v;
         v = W;  // u_{k+1}
     }
@@ -570,6 +654,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
         v_prev = v;
         v = vn;
     }
+    if (m_final > 0 && y.empty()) theta = tri_lowest(ha, hb + 1, m_final, y);
     inf.iters = m_final;
     inf.orth_loss = -1.0;
     inf.reorth_steps = 0;
@@ -732,15 +817,27 @@ hub_status lanczos_coefficients(const hub_sector *s, const double *f, int max_st
     double tmax = 0.0;
     // the product with the first update in its epilogue where available (its
     // per-column partials of alpha summed inside the next kernel), else the
-    // product and a separate first update
+    // product, a separate first update and the normalisation
     const bool fused = matvec_lz_available(s, HUB_F64) && matvec_lz_partials(s) <= kSumInUpdate;
     double *apart = nullptr;
     if (fused) HUB_TRY(mem.alloc((void **)&apart, sizeof(double) * (size_t)matvec_lz_workspace(s)));
+    // fused: unnormalised vectors u_k = beta_k v_k as in the ground-state solve (two
+    // kernels a step); B: the three buffers
+    void *const B[3] = {Va, Vb, W};
+    bool beta_ready = true;  // beta_k is in memory (k = 0: not needed)
     for (int k = 0; k < kmax; ++k) {
         if (fused) {
             int64_t np = 0;
-            HUB_TRY(launch_matvec_lz(s, HUB_F64, v, W, v_prev, d_beta + k, apart, &np, st));
-            HUB_TRY(launch_lz_b_sum(HUB_F64, W, v, apart, np, d_alpha + k, n, partial, st));
+            const double *bk = k >= 1 ? d_beta + k : nullptr, *bprev = k >= 2 ? d_beta + k - 1 : nullptr;
+            BetaSource src;
+            src.partial = partial;
+            src.np = red_grid(n);
+            src.out = d_beta + k;
+            for (void *q : B)
+                if (q != v && q != v_prev) W = q;
+            HUB_TRY(launch_matvec_lz(s, HUB_F64, v, W, v_prev, bk, apart, &np, st, bprev, 1,
+                                     beta_ready ? nullptr : &src));
+            HUB_TRY(launch_lz_b_sum(HUB_F64, W, v, apart, np, d_alpha + k, n, partial, st, bk, 1));
         } else {
             HUB_TRY(apply_h(s, HUB_F64, v, W, st));
             // alpha's partials beside beta's; both summed inside the kernels that use them
@@ -768,6 +865,12 @@ hub_status lanczos_coefficients(const hub_sector *s, const double *f, int max_st
             if (brk) break;
         }
         if (last) break;
+        if (fused) {
+            beta_ready = check_now;
+            v_prev = v;
+            v = W;
+            continue;
+        }
         void *vn = v_prev ? v_prev : spare;
         if (check_now) {
             HUB_TRY(launch_lz_next(HUB_F64, W, vn, d_beta + k + 1, n, st));

@@ -424,6 +424,7 @@ struct LzEpi {
     const double *beta_prev;  // unnorm: beta_{k-1} (device), NULL for beta_0
     int unnorm;
     double *gpart;            // row-chunked product: [cd][G] group partials (summed into apart per column)
+    BetaSource source;        // columns schedule: beta_k from its partials (partial NULL: in *beta)
 };
 
 __device__ __forceinline__ double inv_beta(const double *b)
@@ -445,13 +446,30 @@ struct EpiCoef {
     double sx = 1.0, bt = 0.0;
 };
 
+// The sum of np <= 1024 partials by one wavefront, in the order of the
+// 256-thread single-workgroup sums (each thread's strided terms, then the tree).
+__device__ __forceinline__ double wave_total(const double *__restrict__ p, int np, int lane)
+{
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = lane + 64 * u + 256 * j;
+            if (i < np) a[u] += p[i];
+        }
+    return quad_wave_sum((a[0] + a[2]) + (a[1] + a[3]));
+}
+
+// beta_now: beta_k formed in this launch, or NULL (then it is in *E.beta)
 template <typename T>
-__device__ __forceinline__ EpiCoef<T> epi_coef(const LzEpi<T> &E)
+__device__ __forceinline__ EpiCoef<T> epi_coef(const LzEpi<T> &E, const double *beta_now = nullptr)
 {
     EpiCoef<T> c;
     if (E.unnorm) {
-        c.sx = inv_beta(E.beta);
-        c.bt = E.vprev ? *E.beta * inv_beta(E.beta_prev) : 0.0;
+        const double *bk = beta_now ? beta_now : E.beta;
+        c.sx = inv_beta(bk);
+        c.bt = E.vprev ? *bk * inv_beta(E.beta_prev) : 0.0;
     } else if (E.vprev) {
         c.bt = *E.beta;
     }
@@ -488,7 +506,7 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     extern __shared__ __align__(16) unsigned char smem_raw[];
     T *tab = reinterpret_cast<T *>(smem_raw);  // 256 code values
     T *xs = tab + 256;                         // TB staged columns, interleaved
-    double *gpart = reinterpret_cast<double *>(xs + TB * ((A.cu + 3) & ~3));  // EPI: TB x G group partials
+    double *gpart = reinterpret_cast<double *>(xs + TB * ((A.cu + 3) & ~3));  // EPI: TB x G group partials, beta_k
     int tile;
     if (XC) {
         tile = xcd_tile(ntiles);
@@ -505,6 +523,25 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
         for (int t = 0; t < TB; ++t) xb[t] = A.x + (int64_t)min(b0 + t, cd - 1) * cu;
         stage_quads<T, TB, RAG>(xs, xb, 0, nq, cu, BS);
     }
+    // the step's beta, formed by one wavefront of every workgroup while the others
+    // stage (a launch of its own for it cost 4.7 us and a gap)
+    double *const beta_now = gpart + TB * E.G;
+    if (EPI && E.source.partial && threadIdx.x < 64) {
+        const double bt = sqrt(wave_total(E.source.partial, E.source.np, (int)threadIdx.x));
+        if (threadIdx.x == 0) {
+            *beta_now = bt;
+            if (tile == 0) {
+                *E.source.out = bt;
+                if (E.source.ab) {
+                    volatile double *ab = E.source.ab;
+                    ab[E.source.k] = *E.source.alpha;
+                    ab[E.source.kmax + E.source.k + 1] = bt;
+                    __threadfence_system();
+                    *(volatile int *)E.source.step = E.source.k + 1;
+                }
+            }
+        }
+    }
     __syncthreads();
     int ds[TB], de[TB];
     uint32_t dnb[TB];
@@ -520,7 +557,7 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     const int64_t cu64 = cu;
     const int lane = threadIdx.x & 63;
     EpiCoef<T> ec;
-    if (EPI) ec = epi_coef(E);
+    if (EPI) ec = epi_coef(E, E.source.partial ? beta_now : nullptr);
     // with the epilogue every lane of a wavefront runs the same iterations (it
     // reduces over the wavefront); without it a lane stops after its last quad
     for (int q = threadIdx.x; EPI ? (q - lane < nq) : (q < nq); q += BS) {
@@ -1072,7 +1109,7 @@ hub_status allow_lds(K kernel, size_t bytes)
 template <typename T>
 LzEpi<T> no_epi()
 {
-    return LzEpi<T>{nullptr, nullptr, nullptr, 0, nullptr, 0, nullptr};
+    return LzEpi<T>{nullptr, nullptr, nullptr, 0, nullptr, 0, nullptr, {}};
 }
 
 // ---- geometry -------------------------------------------------------------
@@ -1104,7 +1141,7 @@ bool column_fits(const hub_sector *s, int tb, bool epi)
 {
     const int64_t cu = 4 * quads(s->spin[0].count);
     const size_t g = (size_t)((cu / 4 + 63) / 64);
-    return (size_t)(cu * tb + 256) * sizeof(T) + (epi ? (size_t)tb * g * sizeof(double) : 0) <= s->lds_max;
+    return (size_t)(cu * tb + 256) * sizeof(T) + (epi ? ((size_t)tb * g + 1) * sizeof(double) : 0) <= s->lds_max;
 }
 
 // balanced chunks of at most `maxc` (a multiple of 64) for `n` rows
@@ -1158,7 +1195,7 @@ hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st
     const int ntiles = (A.cd + TB - 1) / TB;
     const unsigned grid = XC ? 8u * (unsigned)((ntiles + 7) / 8) : (unsigned)ntiles;
     const size_t lds = (size_t)(4 * quads(A.cu) * TB + 256) * sizeof(T) +
-                       (EPI ? (size_t)TB * E.G * sizeof(double) : 0);
+                       (EPI ? ((size_t)TB * E.G + 1) * sizeof(double) : 0);
     if (lds > s->lds_max) {
         set_error("column product: tile does not fit in LDS");
         return HUB_ERR_UNSUPPORTED;
@@ -1449,7 +1486,7 @@ hub_status tune(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, bool ep
         HUB_HIP(hipMalloc((void **)&zero, sizeof(double)));
         zb.p = zero;
         HUB_HIP(hipMemsetAsync(zero, 0, sizeof(double), st));
-        E = LzEpi<T>{A.x, zero, apart, (int)((quads(A.cu) + 63) / 64), nullptr, 0, apart + A.cd};
+        E = LzEpi<T>{A.x, zero, apart, (int)((quads(A.cu) + 63) / 64), nullptr, 0, apart + A.cd, {}};
     }
     std::vector<Sched> c = candidates<T>(s, epi);
     if (c.empty()) {
@@ -1558,7 +1595,8 @@ bool lz_fusable(const hub_sector *s)
 
 template <typename T>
 hub_status run_kron_lz(const hub_sector *s, const void *x, void *w, const void *vprev, const double *beta,
-                       const double *beta_prev, int unnorm, double *apart, int64_t *npart, hipStream_t st)
+                       const double *beta_prev, int unnorm, double *apart, int64_t *npart, hipStream_t st,
+                       const BetaSource *source)
 {
     if (!lz_fusable<T>(s)) return HUB_ERR_UNSUPPORTED;
     MvArgs<T> A = make_args<T>(s, x, w);
@@ -1568,8 +1606,12 @@ hub_status run_kron_lz(const hub_sector *s, const void *x, void *w, const void *
     } else {
         q.fam = HUB_SCHED_ROWS;  // the only fused shape without four-row quads
     }
-    const LzEpi<T> E{(const T *)vprev, beta, apart, (int)((quads(A.cu) + 63) / 64), beta_prev, unnorm,
-                     apart + A.cd};
+    LzEpi<T> E{(const T *)vprev, beta, apart, (int)((quads(A.cu) + 63) / 64), beta_prev, unnorm,
+               apart + A.cd, {}};
+    if (source) {
+        if (q.fam == HUB_SCHED_COLUMNS && unnorm && source->np <= 1024) E.source = *source;
+        else HUB_TRY(launch_beta(*source, st));
+    }
     *npart = (int64_t)A.cd;
     std::lock_guard<std::mutex> lk(s->mu);
     return launch_sched<T>(s, A, st, q, &E);
@@ -1604,10 +1646,11 @@ int64_t matvec_lz_workspace(const hub_sector *s)
 
 hub_status launch_matvec_lz(const hub_sector *s, int dtype, const void *x, void *w, const void *vprev,
                             const double *beta, double *apart, int64_t *npart, hipStream_t st,
-                            const double *beta_prev, int unnorm)
+                            const double *beta_prev, int unnorm, const BetaSource *source)
 {
-    if (dtype == HUB_F64) return run_kron_lz<double>(s, x, w, vprev, beta, beta_prev, unnorm, apart, npart, st);
-    return run_kron_lz<float>(s, x, w, vprev, beta, beta_prev, unnorm, apart, npart, st);
+    if (dtype == HUB_F64)
+        return run_kron_lz<double>(s, x, w, vprev, beta, beta_prev, unnorm, apart, npart, st, source);
+    return run_kron_lz<float>(s, x, w, vprev, beta, beta_prev, unnorm, apart, npart, st, source);
 }
 
 hub_status launch_diagonal(const hub_sector *s, int dtype, void *out, hipStream_t st)

@@ -306,21 +306,19 @@ __global__ __launch_bounds__(RB) void k_lz_next_sum(const T *__restrict__ w, T *
         for (int64_t i = 4 * n4 + threadIdx.x; i < n; i += RB) vnext[i] = (bt > 0.0) ? (T)((double)w[i] / bt) : (T)0;
 }
 
-// beta_{k+1} = sqrt(sum of the update's partials) into *beta_out, and the same
-// publication to host memory as k_lz_next_sum (one block)
-__global__ __launch_bounds__(RB) void k_beta_pub(const double *__restrict__ partial, int np,
-                                                 double *__restrict__ beta_out, HostPublish pub)
+// beta of a step from its partials, stored and published (one block)
+__global__ __launch_bounds__(RB) void k_beta(BetaSource b)
 {
     __shared__ double s[RB];
-    const double bt = sqrt(block_total(partial, np, s));
+    const double bt = sqrt(block_total(b.partial, b.np, s));
     if (threadIdx.x == 0) {
-        *beta_out = bt;
-        if (pub.ab) {
-            volatile double *ab = pub.ab;
-            ab[pub.k] = *pub.alpha;
-            ab[pub.kmax + pub.k + 1] = bt;
+        *b.out = bt;
+        if (b.ab) {
+            volatile double *ab = b.ab;
+            ab[b.k] = *b.alpha;
+            ab[b.kmax + b.k + 1] = bt;
             __threadfence_system();
-            *(volatile int *)pub.step = pub.k + 1;
+            *(volatile int *)b.step = b.k + 1;
         }
     }
 }
@@ -755,11 +753,9 @@ hub_status launch_lz_next_sum(int dtype, const void *w, void *vnext, const doubl
     return HUB_OK;
 }
 
-hub_status launch_beta_pub(const double *partial, int64_t n, double *beta_out, hipStream_t st, double *host_ab,
-                           int *host_step, const double *alpha_k, int k, int kmax)
+hub_status launch_beta(const BetaSource &b, hipStream_t st)
 {
-    const HostPublish pub{host_ab, host_step, alpha_k, k, kmax};
-    hipLaunchKernelGGL(k_beta_pub, dim3(1), dim3(RB), 0, st, partial, red_grid(n), beta_out, pub);
+    hipLaunchKernelGGL(k_beta, dim3(1), dim3(RB), 0, st, b);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
 }
