@@ -42,6 +42,7 @@ struct SpinTables {
     double *val64 = nullptr;     // [nnz] -t_b * esign
     float *val32 = nullptr;      // [nnz] FP32 copy of val64 (exact: a negated / rounded t)
     int32_t *bond = nullptr;     // [nnz] canonical bond id of the entry
+    int32_t *order = nullptr;    // [count] the rows in breadth-first order (H_dn of larger sectors, else NULL)
     double *e64 = nullptr;       // [count] sum_i eps_i n_i (FP64, ascending i)
     float *e32 = nullptr;        // [count] FP32 copy
     int32_t max_row = 0;         // longest row of H_sigma
@@ -228,6 +229,7 @@ struct KeptVectors {
 
 // ---- setup (setup.hip) -------------------------------------------------
 hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st);
+hub_status build_dn_order(hub_sector *s);
 // rp[0] = 0, rp[k + 1] = len[0] + ... + len[k] (temporaries owned by s)
 hub_status scan_lengths(hub_sector *s, const int32_t *len, int64_t n, int32_t *rp, hipStream_t st);
 // chunk tables of H_spin with `rows` columns per chunk (built once, then cached)

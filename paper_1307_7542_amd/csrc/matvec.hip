@@ -56,6 +56,7 @@ struct MvArgs {
     const int32_t *__restrict__ dn_rp;
     const int32_t *__restrict__ dn_col;
     const T *__restrict__ dn_val;
+    const int32_t *__restrict__ dn_order;  // order of the columns in k_dn_rows, or NULL: ascending
     const uint32_t *__restrict__ up_basis;
     const uint32_t *__restrict__ dn_basis;
     const T *__restrict__ e_up;
@@ -934,6 +935,11 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
 // instead of from whole columns, of which it keeps 44 (4x4 torus FP64) or 10
 // (2x9 ladder FP64).  The last lane of a segment overlaps the one before where
 // count_up is no multiple of the 16 bytes (both store the same values).
+// Columns come in breadth-first order of the graph of H_dn where the sector has
+// that list (SpinTables::order): a column's neighbours are then gathered near
+// each other in time, and of the 14 of a 2x9-ladder column 3.9 instead of 6.1
+// miss the L2 (least-recently-used model): 24.5 -> 21.6 ms FP64; 4x4 torus FP32
+// 572 -> 560 us.
 // Bound: lines in flight per CU (about 90 of 128 bytes, 415 cycles each by the
 // counters, so 15 to 20 TB/s over the chip).  Segments of 256 and 512 bytes hit
 // the L2 more often (4x4 torus FP64: 18 and 28 instead of 44 million reads from
@@ -952,8 +958,9 @@ __global__ __launch_bounds__(64 * kDnWaves) void k_dn_rows(MvArgs<T> A, int ntil
     const int wk = xcd_tile(nwork);
     if (wk < 0) return;
     const int seg = (int)((uint32_t)wk / (uint32_t)ntile), tile = wk - seg * ntile;
-    const int b = tile * kDnWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (b >= A.cd) return;
+    const int place = tile * kDnWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (place >= A.cd) return;
+    const int b = A.dn_order ? A.dn_order[place] : place;
     const uint32_t cu = (uint32_t)A.cu;
     const int a0 = min((seg * 64 + ((int)threadIdx.x & 63)) * RL, A.cu - RL);
     const int ks = A.dn_rp[b], n = A.dn_rp[b + 1] - ks;
@@ -1063,12 +1070,14 @@ MvArgs<T> make_args(const hub_sector *s, const void *x, void *y)
     A.stream = (double)U.count * (double)D.count * sizeof(T) > 128.0 * 1024 * 1024;
     if constexpr (sizeof(T) == 8) {
         A.up_val = (const T *)U.val64;
+        A.dn_order = D.order;
         A.dn_val = (const T *)D.val64;
         A.e_up = (const T *)U.e64;
         A.e_dn = (const T *)D.e64;
         A.Us = (const T *)s->d_U64;
     } else {
         A.up_val = (const T *)U.val32;
+        A.dn_order = D.order;
         A.dn_val = (const T *)D.val32;
         A.e_up = (const T *)U.e32;
         A.e_dn = (const T *)D.e32;
@@ -1667,7 +1676,8 @@ hub_status launch_diagonal(const hub_sector *s, int dtype, void *out, hipStream_
     return HUB_OK;
 }
 
-// y = V H_dn^T for a state matrix of `rows` x count_dn (any row basis)
+// y = V H_dn^T for a state matrix of `rows` x count_dn (any row basis); columns in
+// ascending order (k = 0 16-site ring, 810 rows: 238 us, breadth-first 245)
 hub_status launch_dn_term(const hub_sector *s, int dtype, const void *x, void *y, int64_t rows, hipStream_t st)
 {
     const SpinTables &D = s->spin[1];

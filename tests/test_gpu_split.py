@@ -72,3 +72,26 @@ def test_ragged_columns(hub, M, n_up, n_dn):
     assert abs(g.e0 - e_ref) <= 1e-10 * abs(e_ref)
     assert g.info["true_residual"] <= 1e-9 * abs(e_ref)
     s.close()
+
+
+# 11440 x 12870: the order of the columns spans one component, or (sites 0-9 a
+# chain, 10-13 a ring, 14 and 15 alone) many of different sizes
+@pytest.mark.parametrize("whole", [True, False])
+def test_column_order_of_dn_pass_bitwise(hub, whole):
+    """The H_dn pass in breadth-first order of the columns reaches every column
+    once: the two-pass product equals the one-pass one bit for bit."""
+    import torch
+    from types import SimpleNamespace
+    M = 16
+    bonds = [(i, (i + 1) % M) for i in range(M)]
+    if not whole:
+        bonds = [(i, i + 1) for i in range(9)] + [(10, 11), (11, 12), (12, 13), (10, 13)]
+    m = SimpleNamespace(n_sites=M, bonds=bonds, t=[1.0 + 0.01 * i for i in range(len(bonds))], U=[4.0] * M,
+                        eps=[0.0] * M, n_up=7, n_dn=8)
+    s = hub.Sector(m)
+    x = s.start_vector(seed=5, dtype=hub.F32)
+    s.set_schedule(hub.F32, hub.SCHED_COLUMNS, tile_cols=1, block=1024, order=1)
+    y0 = s.matvec(x)
+    s.set_schedule(hub.F32, hub.SCHED_COLUMNS, tile_cols=2, block=1024, order=2)
+    assert torch.equal(s.matvec(x), y0)
+    s.close()
