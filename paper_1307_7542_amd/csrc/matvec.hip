@@ -354,25 +354,32 @@ __device__ __forceinline__ Vec<T, N> ld_vec(const T *p)
     return reinterpret_cast<const V *>(p)->v;
 }
 
-// Stage quads q0 .. q1-1 of TB columns xb of cu rows, interleaved by column, at their lds_slot
-template <typename T, int TB, bool RAG>
-__device__ __forceinline__ void stage_quads(T *xs, const T *const (&xb)[TB], int q0, int q1, int cu, int bs)
+// Quad q of nq staged quads of TB columns, interleaved by column, to its lds_slot
+template <typename T, int TB>
+__device__ __forceinline__ void put_quad(T *xs, const Q4<T> (&v)[TB], int q, int nq)
 {
     struct alignas((TB & (TB - 1)) == 0 && sizeof(T) * TB <= 16 ? sizeof(T) * TB : sizeof(T)) V {
         Vec<T, TB> v;
     };
-    for (int q = q0 + threadIdx.x; q < q1; q += bs) {
+    const int s0 = lds_slot(4 * q, 4 * nq), sw = quad_pitch(q, nq);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        V o;
+#pragma unroll
+        for (int t = 0; t < TB; ++t) o.v.v[t] = v[t].v[r];
+        *reinterpret_cast<V *>(xs + (s0 + r * sw) * TB) = o;
+    }
+}
+
+// Stage quads q0 + from .. q1-1 of TB columns xb of cu rows as quads from .. of xs
+template <typename T, int TB, bool RAG>
+__device__ __forceinline__ void stage_quads(T *xs, const T *const (&xb)[TB], int from, int q0, int q1, int cu, int bs)
+{
+    for (int q = q0 + from + threadIdx.x; q < q1; q += bs) {
         Q4<T> v[TB];
 #pragma unroll
         for (int t = 0; t < TB; ++t) v[t] = ldq<T, RAG>(xb[t] + 4 * q, cu - 4 * q);
-        const int s0 = lds_slot(4 * (q - q0), 4 * (q1 - q0)), sw = quad_pitch(q - q0, q1 - q0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            V o;
-#pragma unroll
-            for (int t = 0; t < TB; ++t) o.v.v[t] = v[t].v[r];
-            *reinterpret_cast<V *>(xs + (s0 + r * sw) * TB) = o;
-        }
+        put_quad<T, TB>(xs, v, q - q0, q1 - q0);
     }
 }
 
@@ -517,13 +524,90 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     if (tile < 0) return;
     const int cu = A.cu, cd = A.cd, nq = (cu + 3) >> 2;
     const int b0 = tile * TB;
-    for (int i = threadIdx.x; i < 256; i += BS) tab[i] = code_v[i];
-    {
-        const T *xb[TB];
+    const int64_t cu64 = cu;
+    const int lane = threadIdx.x & 63;
+    const T *xb[TB];
+    int ds[TB], de[TB];
+    uint32_t dnb[TB];
+    T edn[TB];
 #pragma unroll
-        for (int t = 0; t < TB; ++t) xb[t] = A.x + (int64_t)min(b0 + t, cd - 1) * cu;
-        stage_quads<T, TB, RAG>(xs, xb, 0, nq, cu, BS);
+    for (int t = 0; t < TB; ++t) {
+        const int b = min(b0 + t, cd - 1);
+        xb[t] = A.x + (int64_t)b * cu;
+        ds[t] = A.dn_rp[b];
+        de[t] = (b0 + t < cd) ? A.dn_rp[b + 1] : ds[t];
+        dnb[t] = A.dn_basis[b];
+        edn[t] = A.e_dn[b];
     }
+    // what a quad reads from global memory: v_prev, basis states and energies of
+    // its rows, and the H_dn term: from y (SPLIT), else whole neighbour columns,
+    // four rows per load
+    struct Head {
+        T acc[4][TB];
+        Q4<T> vp[EPI ? TB : 1];
+        uint32_t up[4];
+        Q4<T> eu;
+    };
+    auto head = [&](Head &h, int a0, int nv) {
+        if (EPI && E.vprev) {
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                h.vp[t] = ldq_once<T, RAG>(E.vprev + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
+        }
+        const uint4 ub = *reinterpret_cast<const uint4 *>(A.up_basis + a0);
+        h.up[0] = ub.x;
+        h.up[1] = ub.y;
+        h.up[2] = ub.z;
+        h.up[3] = ub.w;
+        h.eu = ld_q4(A.e_up + a0);
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            if (SPLIT) {
+                const Q4<T> v = ldq_once<T, RAG>(A.y + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) h.acc[r][t] = v.v[r];
+                continue;
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h.acc[r][t] = (T)0;
+            int kk = ds[t];
+            for (; kk + 4 <= de[t]; kk += 4) {
+                Q4<T> v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0, nv);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const T w = A.dn_val[kk + u];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v[u].v[r], h.acc[r][t]);
+                }
+            }
+            for (; kk < de[t]; ++kk) {
+                const Q4<T> v = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk] * cu64 + a0, nv);
+                const T w = A.dn_val[kk];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v.v[r], h.acc[r][t]);
+            }
+        }
+    };
+    // The lane's first quad's reads run together with the staging, before the
+    // barrier: a workgroup of a column that fits its lanes has one chain of
+    // latencies less (12-site ring FP64 9.5 -> 8.8 us, its solve 28.4 -> 25.9 us a
+    // step; 14-site ring 99.4 -> 95.7 us).  Not after a pass of its own for the H_dn
+    // term: with several quads a lane the staging only waits for it (4x4 torus FP32
+    // 1.219 instead of 1.205 ms).
+    Head h;
+    const int qf = threadIdx.x;
+    for (int i = threadIdx.x; i < 256; i += BS) tab[i] = code_v[i];
+    if (!SPLIT && qf - lane < nq) {  // not for wavefronts beyond the column
+        const int af = 4 * (qf < nq ? qf : 0);
+        Q4<T> xq[TB];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) xq[t] = ldq<T, RAG>(xb[t] + af, cu - af);
+        head(h, af, cu - af);
+        if (qf < nq) put_quad<T, TB>(xs, xq, qf, nq);
+    }
+    stage_quads<T, TB, RAG>(xs, xb, SPLIT ? 0 : BS, 0, nq, cu, BS);
     // the step's beta, formed by one wavefront of every workgroup while the others
     // stage (a launch of its own for it cost 4.7 us and a gap)
     double *const beta_now = gpart + TB * E.G;
@@ -544,89 +628,36 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
         }
     }
     __syncthreads();
-    int ds[TB], de[TB];
-    uint32_t dnb[TB];
-    T edn[TB];
-#pragma unroll
-    for (int t = 0; t < TB; ++t) {
-        const int b = min(b0 + t, cd - 1);
-        ds[t] = A.dn_rp[b];
-        de[t] = (b0 + t < cd) ? A.dn_rp[b + 1] : ds[t];
-        dnb[t] = A.dn_basis[b];
-        edn[t] = A.e_dn[b];
-    }
-    const int64_t cu64 = cu;
-    const int lane = threadIdx.x & 63;
     EpiCoef<T> ec;
     if (EPI) ec = epi_coef(E, E.source.partial ? beta_now : nullptr);
     // with the epilogue every lane of a wavefront runs the same iterations (it
     // reduces over the wavefront); without it a lane stops after its last quad
-    for (int q = threadIdx.x; EPI ? (q - lane < nq) : (q < nq); q += BS) {
+    for (int q = qf; EPI ? (q - lane < nq) : (q < nq); q += BS) {
         const bool live = !EPI || q < nq;
         const int a0 = 4 * (live ? q : 0);
         const int s0 = lds_slot(a0, cu), sw = quad_pitch(a0 >> 2, nq);  // rows a0 .. a0+3 at s0 + r sw
         const int nv = cu - a0;
-        T acc[4][TB];
-        // the epilogue's v_prev rows are loaded first: a lane runs only one or
-        // two iterations, so a load issued after the gathers leaves its latency exposed
-        Q4<T> vpq[EPI ? TB : 1];
-        if (EPI && live && E.vprev) {
-#pragma unroll
-            for (int t = 0; t < TB; ++t)
-                vpq[t] = ldq_once<T, RAG>(E.vprev + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
-        }
-        const uint4 ub = *reinterpret_cast<const uint4 *>(A.up_basis + a0);
-        const uint32_t uu[4] = {ub.x, ub.y, ub.z, ub.w};
-        const Q4<T> eu = ld_q4(A.e_up + a0);
-        // H_dn term: from y (SPLIT), else whole neighbour columns, four rows per load
-#pragma unroll
-        for (int t = 0; t < TB; ++t) {
-            if (SPLIT) {
-                const Q4<T> v = ldq_once<T, RAG>(A.y + (int64_t)min(b0 + t, cd - 1) * cu64 + a0, nv, A.stream);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r][t] = v.v[r];
-                continue;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r][t] = (T)0;
-            int kk = ds[t];
-            for (; kk + 4 <= de[t]; kk += 4) {
-                Q4<T> v[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0, nv);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const T w = A.dn_val[kk + u];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[r][t] = mad(w, v[u].v[r], acc[r][t]);
-                }
-            }
-            for (; kk < de[t]; ++kk) {
-                const Q4<T> v = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk] * cu64 + a0, nv);
-                const T w = A.dn_val[kk];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r][t] = mad(w, v.v[r], acc[r][t]);
-            }
-        }
+        if (SPLIT || q != qf) head(h, a0, nv);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int t = 0; t < TB; ++t)
-                acc[r][t] = mad(diag_u(A, uu[r] & dnb[t]) + eu.v[r] + edn[t], xs[(s0 + r * sw) * TB + t], acc[r][t]);
+                h.acc[r][t] =
+                    mad(diag_u(A, h.up[r] & dnb[t]) + h.eu.v[r] + edn[t], xs[(s0 + r * sw) * TB + t], h.acc[r][t]);
         // H_up term: entries k of rows a0 .. a0+3 are lanes (a0 & 63) .. +3 of slice a0 >> 6
         const int s = a0 >> 6;
         const uint4 *__restrict__ e4 = reinterpret_cast<const uint4 *>(ellc + (int64_t)sl_off[s] * 64 + (a0 & 63));
         const int len = sl_off[s + 1] - sl_off[s];
-        up_quad<T, TB>(acc, xs, tab, e4, len);
+        up_quad<T, TB>(h.acc, xs, tab, e4, len);
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             if (b0 + t >= cd) continue;
-            T o[4] = {acc[0][t], acc[1][t], acc[2][t], acc[3][t]};
+            T o[4] = {h.acc[0][t], h.acc[1][t], h.acc[2][t], h.acc[3][t]};
             if (EPI) {
                 double part = 0.0;
                 if (live) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) o[r] = epi_w(E, ec, o[r], E.vprev ? vpq[t].v[r] : (T)0);
+                    for (int r = 0; r < 4; ++r) o[r] = epi_w(E, ec, o[r], E.vprev ? h.vp[t].v[r] : (T)0);
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         if (!RAG || r < nv) part += (double)o[r] * (double)xs[(s0 + r * sw) * TB + t];
@@ -751,7 +782,7 @@ __global__ __launch_bounds__(BS) void k_kron_chunked_parts(MvArgs<T> A, const in
         const int q0 = (p * chunk_rows) >> 2;
         const int q1 = min(nq, q0 + (chunk_rows >> 2));
         __syncthreads();  // previous chunk done with xs
-        stage_quads<T, TB, RAG>(xs, xb, q0, q1, cu, BS);
+        stage_quads<T, TB, RAG>(xs, xb, 0, q0, q1, cu, BS);
         __syncthreads();
         const int32_t *off = ch_off + (int64_t)p * (nslices + 1);
         const uint32_t *ell = ch_ell + ch_base[p];
