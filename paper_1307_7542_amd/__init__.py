@@ -156,9 +156,12 @@ def _torch():
 
 
 def _stream(stream=None):
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
+    # the current stream's handle without a Stream object around it: 0.3 instead of
+    # 2.7 us, of the 8 us a small product takes to launch
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev_ptr(t, dtype_code: int, n: int, name: str):
