@@ -29,11 +29,15 @@
 #include <vector>
 
 #include "internal.h"
+#include "quad.h"
 
 namespace hub {
 namespace {
 
 constexpr int BRB = 256;  // segment block size
+// Quads of a column from which a wavefront keeps to one group of columns: at 48 a
+// quarter of its lanes idle, about what the scalar H_dn rows save
+constexpr int kWaveQuads = 48;
 
 template <typename T>
 struct BDesc {
@@ -50,7 +54,7 @@ struct BDesc {
     T U;
     int32_t uniform;
     uint32_t umask;
-    uint64_t cu_magic;  // ceil(2^32 / cu): e / cu = (e * cu_magic) >> 32 for e * cu < 2^32
+    uint64_t nq_magic;  // nq = ceil(cu / 4), ceil(2^32 / nq): f / nq = (f * nq_magic) >> 32 for f * nq < 2^32
 };
 
 template <typename T>
@@ -66,12 +70,6 @@ __device__ __forceinline__ T bdiag(const BDesc<T> &D, uint32_t both)
     }
     return d;
 }
-
-// TB consecutive LDS values read as one access (aligned to their size, at most 16 bytes)
-template <typename T, int N>
-struct __attribute__((aligned(sizeof(T) * N < 16 ? sizeof(T) * N : 16))) BVec {
-    T v[N];
-};
 
 // The lockstep recurrence keeps its vectors unnormalised, u_k = beta_k v_k
 // (u_0 = v_0, beta_0 taken as 1), at the places of a pointer table: at step k,
@@ -95,26 +93,60 @@ __device__ __forceinline__ Roles<T> roles(T *const *ptrs, int k)
 // 1 / beta (0 after a breakdown)
 __device__ __forceinline__ double binv(double b) { return b > 0.0 ? 1.0 / b : 0.0; }
 
+// Rows a0 .. a0+3 of N columns c of a vector whose columns have cu rows (nv = cu -
+// a0: with nv < 4 rows of the columns behind follow).  inside, uniform over the
+// wavefront: every one of them has those four elements in the vector; else rows
+// past the column read as 0.
+template <typename T, int N>
+__device__ __forceinline__ void ld_rows(Q4<T> (&v)[N], const T *__restrict__ x, const int (&c)[N], int cu, int a0, int nv,
+                                        bool inside)
+{
+    if (inside) {
+#pragma unroll
+        for (int t = 0; t < N; ++t) v[t] = ld_q4e(x + ((uint64_t)(uint32_t)c[t] * (uint32_t)cu + a0), 4);
+    } else {
+#pragma unroll
+        for (int t = 0; t < N; ++t) v[t] = ld_q4e(x + ((uint64_t)(uint32_t)c[t] * (uint32_t)cu + a0), nv);
+    }
+}
+
+// p[i] of a table that no launch of the product writes, i uniform over the
+// wavefront: a scalar load (the compiler cannot tell that y is not the table)
+template <typename V>
+__device__ __forceinline__ V ld_uniform(const V *p, int i)
+{
+    typedef const __attribute__((address_space(4))) V *Const;
+    return ((Const)(uintptr_t)p)[i];
+}
+
 // Batched product.  A work item is `ncol` consecutive columns of one sector,
 // taken in groups of TB columns (the last group padded).  The item's columns
-// are staged in LDS interleaved by group (element (a, column g TB + t) at
-// (g cu + a) TB + t), and its H_dn rows, e_dn and bit patterns beside them.  A
-// lane owns TB columns of one row of one group: position f = g cu + a, the
-// quotient by a multiply-high with ceil(2^32 / cu) (exact while f cu < 2^32),
-// so a sector smaller than the workgroup fills it with several groups; each
-// H_up entry is read once for the TB columns (one LDS access gathers them),
-// and each lane takes R positions BS apart at a time, so that their loads are
-// in flight together (loads unconditional: a position past the end, or an
-// entry past its row's length, re-reads a valid one and only the update is
-// selected).  Every element is formed as in the single-sector product
-// (the H_dn entries in CSR order, then the diagonal, then the H_up entries in
-// sliced-ELL order, one fused multiply-add each): the two agree bit for bit.
+// are staged in LDS interleaved by group (row a of column g TB + t at
+// (4 g nq + lds_slot(a)) TB + t), and its H_dn rows, e_dn and bit patterns beside
+// them.  A lane owns the four rows 4q .. 4q+3 of TB columns of one group, so that
+// neighbour columns, v_prev and stores are 16-byte accesses (of any alignment) and
+// an H_dn entry, like the 16 bytes of an H_up entry of the four rows, is read once
+// for them; the last quad of a column whose length is no multiple of 4 reads on
+// into the next column and stores its own rows only.  Columns of kWaveQuads quads
+// or more: a wavefront keeps to one group, the H_dn rows are scalar loads, four
+// neighbour columns in flight, and the first quad's run with the staging.  Shorter
+// ones: lane f holds position f = g nq + q, so that several groups fill a
+// wavefront (quotient by a multiply-high with ceil(2^32 / nq), exact while f nq <
+// 2^32), each lane with its own H_dn rows from LDS; U entries in flight, an entry
+// past its row's length re-reading a valid one with only the update selected.
+// Every element is formed as in the single-sector product (the H_dn entries in
+// CSR order, then the diagonal, then the H_up entries in sliced-ELL order, one
+// fused multiply-add each): the two agree bit for bit.
+// Bound: the gathers' traffic between L1 and L2, the vector once per entry of
+// H_dn.  64 impurities of 20 x 20 to 924 x 924: one row per lane 62.6 us FP32
+// (FP64 80); four rows 51 (88); every sector's items on one or two XCDs instead
+// of all eight (build_items) 43 (68); a wavefront to a group 40 (66).
 // SEL (the Lanczos step): x = u_k and y = w from the pointer table at the device
 // step counter, and the first update fused in: w = (H u_k) / beta_k -
 // (beta_k / beta_{k-1}) u_{k-1}, evaluated in FP64 and rounded once, and this
 // item's partial of <w, u_k> = beta_k alpha_k in ipart[it.w] (a fixed-order
 // block sum, at the item's place in sector-major order); otherwise x, y as given.
-template <typename T, int BS, int R, int TB, bool SEL>
+template <typename T, int BS, int TB, bool SEL>
 __global__ __launch_bounds__(BS) void k_batch_kron(const BDesc<T> *__restrict__ desc, const int4 *__restrict__ items,
                                                    const T *xg, T *yg, T *const *ptrs, const int *step,
                                                    const int *__restrict__ active, const double *__restrict__ beta,
@@ -122,14 +154,13 @@ __global__ __launch_bounds__(BS) void k_batch_kron(const BDesc<T> *__restrict__ 
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[SEL ? BS : 1];
+    constexpr int U = TB >= 4 ? 1 : 4 / TB;  // H_dn entries of a column in flight
     T *tab = reinterpret_cast<T *>(smem_raw);
     T *xs = tab + 256;
-    // items in launch order (costliest first): with converged sectors masked
-    // out, the remaining work stays spread over every XCD
     const int item = (int)blockIdx.x;
     if (item >= nitems) return;
     const int4 it = items[item];
-    if (active && !active[it.x]) return;
+    if (it.z == 0 || (active && !active[it.x])) return;
     const BDesc<T> D = desc[it.x];
     const T *x = xg;
     T *y = yg;
@@ -150,124 +181,186 @@ __global__ __launch_bounds__(BS) void k_batch_kron(const BDesc<T> *__restrict__ 
     }
     x += D.off;
     y += D.off;
-    const int cu = D.cu, b0 = it.y, ncol = it.z;
-    const int ng = (ncol + TB - 1) / TB, F = ng * cu;
+    const int cu = D.cu, cd = D.cd, b0 = it.y, ncol = it.z, nq = (cu + 3) >> 2;
+    const int ng = (ncol + TB - 1) / TB, F = ng * nq;
     const int64_t t0 = (int64_t)b0 * cu;
+    // columns below clim have three rows of other columns behind them
+    const int clim = cu > 1 ? cd - 1 : cd - 3;
+    const bool whole = (cu & 3) == 0, inside = whole || b0 + ncol <= clim;
     const int rp0 = D.dn_rp[b0], nnz = D.dn_rp[b0 + ncol] - rp0;
-    T *lval = xs + (int64_t)F * TB;
+    T *lval = xs + (int64_t)F * 4 * TB;
     T *ledn = lval + nnz;
     int *lcol = reinterpret_cast<int *>(ledn + ncol);
     int *lrp = lcol + nnz;
     uint32_t *ldnb = reinterpret_cast<uint32_t *>(lrp + ncol + 1);
+    // what a position reads from global memory besides the H_dn term
+    struct Head {
+        T acc[4][TB];
+        Q4<T> vp[SEL ? TB : 1];
+        uint32_t up[4];
+        Q4<T> eu;
+    };
+    auto rows = [&](Head &h, int g, int a0) {
+        if constexpr (SEL) {
+            if (ks > 0) {
+                int c[TB];
+#pragma unroll
+                for (int t = 0; t < TB; ++t) c[t] = b0 + min(g * TB + t, ncol - 1);
+                ld_rows(h.vp, vp, c, cu, a0, cu - a0, inside);
+            }
+        }
+        const uint4 ub = *reinterpret_cast<const uint4 *>(D.up_basis + a0);
+        h.up[0] = ub.x;
+        h.up[1] = ub.y;
+        h.up[2] = ub.z;
+        h.up[3] = ub.w;
+        h.eu = ld_q4(D.e_up + a0);
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h.acc[r][t] = (T)0;
+    };
+    double dacc = 0.0;
+    // diagonal, H_up, update and store of a position whose H_dn term is done
+    auto finish = [&](Head &h, int g, int q) {
+        const int a0 = 4 * q, nv = cu - a0;
+        const T *xg4 = xs + 4 * g * nq * TB;                            // the group's staged columns
+        const int s0 = lds_slot(a0, cu), sw = quad_pitch(q, nq);  // rows a0 .. a0+3 at s0 + r sw
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const int c = min(g * TB + t, ncol - 1);
+            const uint32_t db = ldnb[c];
+            const T edn = ledn[c];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                h.acc[r][t] = mad(bdiag(D, h.up[r] & db) + h.eu.v[r] + edn, xg4[(s0 + r * sw) * TB + t], h.acc[r][t]);
+        }
+        // H_up: entries k of rows a0 .. a0+3 are lanes (a0 & 63) .. +3 of slice a0 >> 6
+        const int s = a0 >> 6;
+        const uint4 *__restrict__ e4 = reinterpret_cast<const uint4 *>(D.ell + (int64_t)D.sl_off[s] * 64 + (a0 & 63));
+        up_quad<T, TB>(h.acc, xg4, tab, e4, D.sl_off[s + 1] - D.sl_off[s]);
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            const int cc = g * TB + t;
+            if (cc >= ncol) continue;
+            T o[4] = {h.acc[0][t], h.acc[1][t], h.acc[2][t], h.acc[3][t]};
+            if (SEL) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    o[r] = (ks > 0) ? (T)fma(sx, (double)o[r], -(bt * (double)h.vp[t].v[r])) : (T)(sx * (double)o[r]);
+                    if (r < nv) dacc += (double)o[r] * (double)xg4[(s0 + r * sw) * TB + t];
+                }
+            }
+            st_q4e(y + t0 + (int64_t)cc * cu + a0, o, nv);
+        }
+    };
     for (int i = threadIdx.x; i < 256; i += BS) tab[i] = D.code_v[i];
-    for (int e = threadIdx.x; e < ng * TB * cu; e += BS) {
-        const int c = (int)(((uint64_t)(uint32_t)e * D.cu_magic) >> 32);  // column in the item
-        const int a = e - c * cu;
-        xs[((c / TB) * cu + a) * TB + c % TB] = (c < ncol) ? x[t0 + e] : (T)0;
+    for (int f = threadIdx.x; f < F; f += BS) {
+        const int g = (int)(((uint64_t)(uint32_t)f * D.nq_magic) >> 32), q = f - g * nq;
+        Q4<T> v[TB];
+        int c[TB];
+#pragma unroll
+        for (int t = 0; t < TB; ++t) c[t] = b0 + min(g * TB + t, ncol - 1);  // a padded group repeats its last column
+        ld_rows(v, x, c, cu, 4 * q, cu - 4 * q, inside);
+        put_quad<T, TB>(xs + 4 * g * nq * TB, v, q, nq);
     }
-    for (int q = threadIdx.x; q < nnz; q += BS) {
-        lval[q] = D.dn_val[rp0 + q];
-        lcol[q] = D.dn_col[rp0 + q];
-    }
-    for (int t = threadIdx.x; t <= ncol; t += BS) lrp[t] = D.dn_rp[b0 + t] - rp0;
     for (int t = threadIdx.x; t < ncol; t += BS) {
         ledn[t] = D.e_dn[b0 + t];
         ldnb[t] = D.dn_basis[b0 + t];
     }
-    __syncthreads();
-    double dacc = 0.0;
-    for (int f0 = threadIdx.x; f0 < F; f0 += R * BS) {
-        int ra[R], rg[R];  // row, group
-        T acc[R][TB];
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int f = (f0 + j * BS < F) ? f0 + j * BS : f0;
-            rg[j] = (int)(((uint64_t)(uint32_t)f * D.cu_magic) >> 32);
-            ra[j] = f - rg[j] * cu;
-#pragma unroll
-            for (int t = 0; t < TB; ++t) acc[j][t] = (T)0;
-        }
-        // H_dn: the row of each column's CSR (from LDS), neighbour columns read
-        // from the vector
-        int ds[R][TB], dn[R][TB], nmax = 0;
-#pragma unroll
-        for (int j = 0; j < R; ++j)
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const int cc = rg[j] * TB + t;
-                ds[j][t] = lrp[min(cc, ncol)];
-                dn[j][t] = (cc < ncol) ? lrp[cc + 1] - ds[j][t] : 0;
-                nmax = max(nmax, dn[j][t]);
-            }
-        for (int u = 0; u < nmax; ++u) {
-            T w[R][TB], xv[R][TB];
-#pragma unroll
-            for (int j = 0; j < R; ++j)
+    if (nq >= kWaveQuads) {
+        const int nqb = (nq + 63) >> 6, lane = threadIdx.x & 63;
+        bool staged = false;
+        for (int wb = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);; wb += BS / 64) {
+            const bool some = wb < ng * nqb;
+            if (!some && staged) break;
+            const int g = some ? wb / nqb : 0, q = (wb - g * nqb) * 64 + lane, a0 = 4 * q, nv = cu - a0;
+            const bool live = some && q < nq;
+            Head h;
+            if (live) {
+                rows(h, g, a0);
 #pragma unroll
                 for (int t = 0; t < TB; ++t) {
-                    const int kk = dn[j][t] > 0 ? ds[j][t] + min(u, dn[j][t] - 1) : 0;
-                    w[j][t] = lval[kk];
-                    xv[j][t] = x[(int64_t)lcol[kk] * cu + ra[j]];
-                }
+                    const int c = g * TB + t;
+                    if (c >= ncol) continue;
+                    int kk = ld_uniform(D.dn_rp, b0 + c);
+                    const int ke = ld_uniform(D.dn_rp, b0 + c + 1);
+                    const auto col = [&](int k) { return ld_uniform(D.dn_col, k); };
+                    for (; kk + 4 <= ke; kk += 4) {
+                        Q4<T> v[4];
+                        const int c4[4] = {col(kk), col(kk + 1), col(kk + 2), col(kk + 3)};
+                        ld_rows(v, x, c4, cu, a0, nv, whole || c4[3] < clim);  // (columns ascend)
 #pragma unroll
-            for (int j = 0; j < R; ++j)
+                        for (int u = 0; u < 4; ++u) {
+                            const T w = ld_uniform(D.dn_val, kk + u);
 #pragma unroll
-                for (int t = 0; t < TB; ++t) {
-                    const T f = fma(w[j][t], xv[j][t], acc[j][t]);
-                    acc[j][t] = (u < dn[j][t]) ? f : acc[j][t];
+                            for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v[u].v[r], h.acc[r][t]);
+                        }
+                    }
+                    for (; kk < ke; ++kk) {
+                        Q4<T> v[1];
+                        const int c1[1] = {col(kk)};
+                        ld_rows(v, x, c1, cu, a0, nv, whole || c1[0] < clim);
+                        const T w = ld_uniform(D.dn_val, kk);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v[0].v[r], h.acc[r][t]);
+                    }
                 }
+            }
+            if (!staged) {
+                __syncthreads();
+                staged = true;
+            }
+            if (live) finish(h, g, q);
         }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int f = (f0 + j * BS < F) ? f0 + j * BS : f0;
-            const uint32_t ub = D.up_basis[ra[j]];
-            const T eu = D.e_up[ra[j]];
+    } else {
+        for (int q = threadIdx.x; q < nnz; q += BS) {
+            lval[q] = D.dn_val[rp0 + q];
+            lcol[q] = D.dn_col[rp0 + q];
+        }
+        for (int t = threadIdx.x; t <= ncol; t += BS) lrp[t] = D.dn_rp[b0 + t] - rp0;
+        __syncthreads();
+        for (int f = threadIdx.x; f < F; f += BS) {
+            const int g = (int)(((uint64_t)(uint32_t)f * D.nq_magic) >> 32), q = f - g * nq;
+            const int a0 = 4 * q, nv = cu - a0;
+            Head h;
+            rows(h, g, a0);
+            // H_dn: the row of each column's CSR (from LDS), neighbour columns read
+            // from the vector
+            int ds[TB], dn[TB], nmax = 0;
 #pragma unroll
             for (int t = 0; t < TB; ++t) {
-                const int c = min(rg[j] * TB + t, ncol - 1);
-                acc[j][t] = fma(bdiag(D, ub & ldnb[c]) + eu + ledn[c], xs[f * TB + t], acc[j][t]);
+                const int cc = g * TB + t;
+                ds[t] = lrp[min(cc, ncol)];
+                dn[t] = (cc < ncol) ? lrp[cc + 1] - ds[t] : 0;
+                nmax = max(nmax, dn[t]);
             }
-        }
-        // H_up: entry k of row a at ell[64 sl_off[a / 64] + a % 64 + 64 k]
-        int eo[R], el_n[R], lmax = 0;
+            for (int u0 = 0; u0 < nmax; u0 += U) {
+                T w[U * TB];
+                Q4<T> xv[U * TB];
+                int c[U * TB];
+                bool last = false;
 #pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int s = ra[j] >> 6;
-            eo[j] = D.sl_off[s] * 64 + (ra[j] & 63);
-            el_n[j] = D.sl_off[s + 1] - D.sl_off[s];
-            lmax = max(lmax, el_n[j]);
-        }
-        for (int k = 0; k < lmax; ++k) {
-            uint32_t c[R];
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int j = 0; j < R; ++j) c[j] = D.ell[el_n[j] > 0 ? eo[j] + 64 * min(k, el_n[j] - 1) : 0];
+                    for (int t = 0; t < TB; ++t) {
+                        const int kk = dn[t] > 0 ? ds[t] + min(u0 + u, dn[t] - 1) : 0;
+                        w[u * TB + t] = lval[kk];
+                        c[u * TB + t] = lcol[kk];
+                        last |= lcol[kk] >= clim;
+                    }
+                ld_rows(xv, x, c, cu, a0, nv, whole || !__any(last));
 #pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const T v = tab[c[j] >> 24];
-                const BVec<T, TB> xv =
-                    *reinterpret_cast<const BVec<T, TB> *>(xs + (rg[j] * cu + (int)(c[j] & 0xFFFFFFu)) * TB);
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int t = 0; t < TB; ++t) {
-                    const T f = fma(v, xv.v[t], acc[j][t]);
-                    acc[j][t] = (k < el_n[j]) ? f : acc[j][t];
+                    for (int t = 0; t < TB; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const T f1 = mad(w[u * TB + t], xv[u * TB + t].v[r], h.acc[r][t]);
+                            h.acc[r][t] = (u0 + u < dn[t]) ? f1 : h.acc[r][t];
+                        }
                 }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            if (f0 + j * BS >= F) continue;
-#pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                const int cc = rg[j] * TB + t;
-                if (cc >= ncol) continue;
-                const int64_t o = t0 + (int64_t)cc * cu + ra[j];
-                T r = acc[j][t];
-                if (SEL) {
-                    r = (ks > 0) ? (T)fma(sx, (double)r, -(bt * (double)vp[o])) : (T)(sx * (double)r);
-                    dacc += (double)r * (double)xs[(rg[j] * cu + ra[j]) * TB + t];
-                }
-                y[o] = r;
-            }
+            finish(h, g, q);
         }
     }
     if (SEL) {
@@ -595,7 +688,7 @@ struct hub_batch {
     int64_t *d_off = nullptr;
     // tuned product per dtype
     bool tuned[2] = {false, false};
-    int rr[2] = {1, 1}, bs[2] = {256, 256}, tb[2] = {1, 1};  // rows / columns per lane, workgroup size
+    int rr[2] = {1, 1}, bs[2] = {256, 256}, tb[2] = {1, 1};  // quads / columns per lane, workgroup size
     int4 *items[2] = {nullptr, nullptr};      // {sector, first column, columns, 0}
     int nitems[2] = {0, 0};
     size_t lds_bytes[2] = {0, 0};             // dynamic LDS of the largest item
@@ -650,11 +743,12 @@ BDesc<T> make_desc(const hub_sector *s, int64_t off)
     d.dn_rp = D.rp;
     d.dn_col = D.col;
     d.sl_off = U.sl_off;
-    d.ell = U.ell_c32;
+    d.ell = U.ell_q32;
     d.uniform = s->uniformU;
     d.umask = s->umask;
     d.U = (T)s->U0;
-    d.cu_magic = ((1ull << 32) + (uint64_t)d.cu - 1) / (uint64_t)d.cu;
+    const uint64_t nq = ((uint64_t)d.cu + 3) / 4;
+    d.nq_magic = ((1ull << 32) + nq - 1) / nq;
     if constexpr (sizeof(T) == 8) {
         d.e_up = U.e64;
         d.e_dn = D.e64;
@@ -671,26 +765,27 @@ BDesc<T> make_desc(const hub_sector *s, int64_t off)
     return d;
 }
 
-template <typename T, int BS, int R, int TB, bool SEL>
+template <typename T, int BS, int TB, bool SEL>
 hub_status launch_bk(hub_batch *b, int di, const T *x, T *y, T *const *ptrs, const int *step, const int *active,
                      hipStream_t st, const double *beta, int kmax, double *ipart)
 {
     static std::atomic<bool> attr{false};
     if (!attr) {
-        HUB_HIP(hipFuncSetAttribute((const void *)k_batch_kron<T, BS, R, TB, SEL>,
+        HUB_HIP(hipFuncSetAttribute((const void *)k_batch_kron<T, BS, TB, SEL>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->lds_max));
         attr = true;
     }
     const int n = b->nitems[di];
-    hipLaunchKernelGGL((k_batch_kron<T, BS, R, TB, SEL>), dim3(n), dim3(BS), b->lds_bytes[di], st,
+    hipLaunchKernelGGL((k_batch_kron<T, BS, TB, SEL>), dim3(n), dim3(BS), b->lds_bytes[di], st,
                        (const BDesc<T> *)b->desc[di], b->items[di], x, y, ptrs, step, active, beta, kmax, ipart, n);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
 }
 
-// The product shapes the tuner tries: {workgroup size, rows per lane, columns per lane}
-constexpr int kBatchShapes[][3] = {{256, 4, 1}, {256, 2, 2}, {256, 1, 4}, {256, 2, 4}, {256, 4, 2},
-                                   {512, 4, 1}, {512, 2, 2}, {512, 1, 4}, {512, 2, 4}};
+// The product shapes the tuner tries: {workgroup size, quads per lane, columns
+// per lane}.  More quads per lane or 512 lanes with one column gained nothing
+// (64 impurities of up to 924 x 924, FP32: 40 us with the best of these, 51 to 60).
+constexpr int kBatchShapes[][3] = {{256, 1, 1}, {256, 1, 2}, {256, 1, 4}, {256, 2, 2}, {512, 1, 2}, {512, 1, 4}};
 
 // SEL: the Lanczos step (vectors from the pointer table, first update fused,
 // item partials of alpha in ipart; beta and kmax as in the solver's arrays)
@@ -699,17 +794,16 @@ hub_status launch_batch_product(hub_batch *b, const T *x, T *y, T *const *ptrs, 
                                 hipStream_t st, const double *beta = nullptr, int kmax = 0, double *ipart = nullptr)
 {
     const int di = (sizeof(T) == 8) ? 0 : 1;
-    const int rr = b->rr[di], bs = b->bs[di], tb = b->tb[di];
-#define HUB_BK(BSV, RV, TBV)                                                             \
-    if (bs == BSV && rr == RV && tb == TBV)                                              \
-        return launch_bk<T, BSV, RV, TBV, SEL>(b, di, x, y, ptrs, step, active, st, beta, kmax, ipart);
-    HUB_BK(256, 4, 1) HUB_BK(256, 2, 2) HUB_BK(256, 1, 4) HUB_BK(256, 2, 4) HUB_BK(256, 4, 2)
-    HUB_BK(512, 4, 1) HUB_BK(512, 2, 2) HUB_BK(512, 1, 4) HUB_BK(512, 2, 4)
+    const int bs = b->bs[di], tb = b->tb[di];
+#define HUB_BK(BSV, TBV)        \
+    if (bs == BSV && tb == TBV) \
+        return launch_bk<T, BSV, TBV, SEL>(b, di, x, y, ptrs, step, active, st, beta, kmax, ipart);
+    HUB_BK(256, 1) HUB_BK(256, 2) HUB_BK(256, 4) HUB_BK(512, 2) HUB_BK(512, 4)
 #undef HUB_BK
     return bfail(HUB_ERR_UNSUPPORTED, "untuned product shape");
 }
 
-// Work items: each sector's columns in runs of tb x max(1, target / count_up)
+// Work items: each sector's columns in runs of tb x max(1, target / quads of a column)
 // (the last run shorter), at most kItemDnEntries / (the longest H_dn row)
 // columns, so that their H_dn rows fit the LDS beside them.
 constexpr int kItemDnEntries = 4096;
@@ -722,9 +816,9 @@ hub_status build_items(hub_batch *b, int di, int target, int tb)
     for (int p = 0; p < b->P; ++p) {
         const SpinTables &DN = b->secs[p]->spin[1];
         const int cu = (int)b->secs[p]->spin[0].count, cd = (int)DN.count;
-        const int deg = std::max(1, (int)DN.max_row);
-        const int per = std::max(1, std::min({cd, tb * std::max(1, target / cu), kItemDnEntries / deg}));
-        // the in-kernel quotients by cu are exact while (padded columns of an item) * cu * cu < 2^32
+        const int deg = std::max(1, (int)DN.max_row), nq = (cu + 3) / 4;
+        const int per = std::max(1, std::min({cd, tb * std::max(1, target / nq), kItemDnEntries / deg}));
+        // the in-kernel quotients by nq <= cu are exact while (padded columns of an item) * cu * cu < 2^32
         const uint64_t padded = (uint64_t)((per + tb - 1) / tb * tb);
         if (padded * (uint64_t)cu * (uint64_t)cu >= (1ull << 32))
             return bfail(HUB_ERR_UNSUPPORTED, "sector too large for the batched product");
@@ -733,7 +827,7 @@ hub_status build_items(hub_batch *b, int di, int target, int tb)
             it.push_back(make_int4(p, b0, n, (int)it.size()));
             const size_t nnz = (size_t)n * (size_t)deg;
             const size_t ncp = (size_t)((n + tb - 1) / tb * tb);
-            lds = std::max(lds, (256 + ncp * cu + nnz + n) * es + (nnz + 2 * (size_t)n + 1) * 4);
+            lds = std::max(lds, (256 + ncp * 4 * nq + nnz + n) * es + (nnz + 2 * (size_t)n + 1) * 4);
         }
     }
     if (b->items[di]) {
@@ -742,19 +836,34 @@ hub_status build_items(hub_batch *b, int di, int target, int tb)
             if (q == (void *)b->items[di]) q = nullptr;
         b->items[di] = nullptr;
     }
-    // launch order: costliest items first (elements times the entries per
-    // element), so the last wave of workgroups holds the cheapest ones; .w keeps
-    // the item's sector-major index, where its alpha partial goes
-    std::vector<int4> lo(it);
+    // Launch order: workgroup i runs on XCD i mod 8, and every XCD takes an eighth
+    // of the work (elements times the entries per element) as one run of the list
+    // of items, sectors with the costliest items first: a sector's columns are then
+    // gathered through one or two L2s, not through all eight.  Empty places (no
+    // columns) fill the shorter runs; .w keeps the item's sector-major index,
+    // where its alpha partial goes.
+    std::vector<int4> by_cost(it);
     auto cost = [&](const int4 &q) {
         const hub_sector *sp = b->secs[q.x];
         const double cu = (double)sp->spin[0].count, cd = (double)sp->spin[1].count;
         return (double)q.z * cu * (1.0 + (double)sp->spin[0].nnz / cu + (double)sp->spin[1].nnz / cd);
     };
-    std::stable_sort(lo.begin(), lo.end(), [&](const int4 &a, const int4 &c) { return cost(a) > cost(c); });
+    std::stable_sort(by_cost.begin(), by_cost.end(), [&](const int4 &a, const int4 &c) { return cost(a) > cost(c); });
+    double total = 0.0, sum = 0.0;
+    for (const int4 &q : by_cost) total += cost(q);
+    std::vector<int4> run[8];
+    for (const int4 &q : by_cost) {
+        run[std::min(7, (int)(8.0 * (sum + 0.5 * cost(q)) / total))].push_back(q);
+        sum += cost(q);
+    }
+    size_t longest = 0;
+    for (const auto &r : run) longest = std::max(longest, r.size());
+    std::vector<int4> lo(8 * longest, make_int4(0, 0, 0, 0));
+    for (int x = 0; x < 8; ++x)
+        for (size_t k = 0; k < run[x].size(); ++k) lo[8 * k + x] = run[x][k];
     HUB_TRY(balloc(b, &b->items[di], lo.size()));
     HUB_HIP(hipMemcpy(b->items[di], lo.data(), sizeof(int4) * lo.size(), hipMemcpyHostToDevice));
-    b->nitems[di] = (int)it.size();
+    b->nitems[di] = (int)lo.size();
     b->lds_bytes[di] = lds;
     // the items of sector p are [istart[p], istart[p] + icount[p]) (sector-major order)
     std::vector<int> hs(b->P, 0), hc(b->P, 0);
@@ -1258,7 +1367,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
         std::memset(info, 0, sizeof(*info));
         info->steps = k;
         info->graph_replays = replays;
-        info->rows_per_lane = b->rr[di];
+        info->rows_per_lane = 4;
         info->cols_per_lane = b->tb[di];
         info->block_size = b->bs[di];
         info->tune_seconds = b->tune_seconds - tune0;

@@ -229,3 +229,26 @@ def test_batch_mixed_gradients_vs_oracle(hub):
     batch.close()
     for s in secs:
         s.close()
+
+
+# columns of 48 and 43 quads (the two lane layouts), a multiple of 4 long or not,
+# of 1 to 3 rows, and the shortest ones at the end of the vectors
+@pytest.mark.parametrize("last", [(10, 0, 1), (3, 1, 2), (2, 1, 1), (19, 2, 1), (20, 2, 1)])
+def test_batch_product_bitwise_at_layout_edges(hub, last):
+    """Every sector's part of the batched product equals its own product bit for bit."""
+    import torch
+    models = [(W.ring(M) if M > 2 else W.dimer()).with_params(n_up=u, n_dn=d, eps=[0.1 * i for i in range(M)])
+              for M, u, d in [(20, 2, 1), (10, 0, 1), (19, 2, 2), (11, 5, 6), (10, 5, 5), (5, 1, 4)] + [last]]
+    secs = [hub.Sector(m) for m in models]
+    batch = hub.Batch(secs)
+    for dt in (torch.float64, torch.float32):
+        g = torch.Generator(device="cuda").manual_seed(11)
+        x = torch.rand(batch.total, dtype=dt, device="cuda", generator=g) - 0.5
+        y = batch.matvec(x)
+        o = 0
+        for s in secs:
+            assert torch.equal(y[o:o + s.dim], s.matvec(x[o:o + s.dim].clone())), (dt, s.count_up, s.count_dn)
+            o += s.dim
+    batch.close()
+    for s in secs:
+        s.close()
