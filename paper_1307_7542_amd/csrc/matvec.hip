@@ -308,16 +308,23 @@ struct EpiCoef {
 
 // The sum of np <= 1024 partials by one wavefront, in the order of the
 // 256-thread single-workgroup sums (each thread's strided terms, then the tree).
+// Eight loads in flight: one behind the other, each workgroup of a Lanczos step's
+// product waited for up to 16 of them (14-site ring FP64 184 us a step, with this
+// 166; 12-site ring 25.9, 22.7).
 __device__ __forceinline__ double wave_total(const double *__restrict__ p, int np, int lane)
 {
     double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int j0 = 0; j0 < np; j0 += 512) {
+        double v[2][4];  // every load issued before the first sum
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = lane + 64 * u + 256 * j;
-            if (i < np) a[u] += p[i];
-        }
+            for (int u = 0; u < 4; ++u) v[j][u] = p[min(j0 + lane + 64 * u + 256 * j, np - 1)];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) a[u] += j0 + lane + 64 * u + 256 * j < np ? v[j][u] : 0.0;
+    }
     return quad_wave_sum((a[0] + a[2]) + (a[1] + a[3]));
 }
 
@@ -359,7 +366,7 @@ __device__ __forceinline__ T epi_w(const LzEpi<T> &E, const EpiCoef<T> &c, T o, 
 // wavefront in a fixed order, then the groups of a column in increasing order,
 // so the per-column partials do not depend on the tile shape.
 template <typename T, int TB, int BS, bool XC, bool EPI, bool SPLIT, bool RAG>
-__global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__restrict__ sl_off,
+__global__ __launch_bounds__(BS, TB <= 2 ? 4 : 1) void k_kron_quad(MvArgs<T> A, const int32_t *__restrict__ sl_off,
                                                   const uint32_t *__restrict__ ellc, const T *__restrict__ code_v,
                                                   int ntiles, LzEpi<T> E)
 {
@@ -434,12 +441,25 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
                     for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v[u].v[r], h.acc[r][t]);
                 }
             }
-            for (; kk < de[t]; ++kk) {
-                const Q4<T> v = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk] * cu64 + a0, nv);
-                const T w = A.dn_val[kk];
+            // the last n % 4 entries: every load issued before the first update
+            // (12-site ring FP64 9.4 -> 8.9 us, 14-site ring 95.4 -> 93.6 us)
+            const int m = de[t] - kk, k1 = kk + (m & 2);
+            Q4<T> v2[2], v1;
+            auto use = [&](int k, const Q4<T> &v) {
+                const T w = A.dn_val[k];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) h.acc[r][t] = mad(w, v.v[r], h.acc[r][t]);
+            };
+            if (m & 2) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) v2[u] = ldq<T, RAG>(A.x + (int64_t)A.dn_col[kk + u] * cu64 + a0, nv);
             }
+            if (m & 1) v1 = ldq<T, RAG>(A.x + (int64_t)A.dn_col[k1] * cu64 + a0, nv);
+            if (m & 2) {
+                use(kk, v2[0]);
+                use(kk + 1, v2[1]);
+            }
+            if (m & 1) use(k1, v1);
         }
     };
     // The lane's first quad's reads run together with the staging, before the
@@ -461,11 +481,12 @@ __global__ __launch_bounds__(BS) void k_kron_quad(MvArgs<T> A, const int32_t *__
     }
     stage_quads<T, TB, RAG>(xs, xb, SPLIT ? 0 : BS, 0, nq, cu, BS);
     // the step's beta, formed by one wavefront of every workgroup while the others
-    // stage (a launch of its own for it cost 4.7 us and a gap)
+    // finish their first reads (a launch of its own for it cost 4.7 us and a gap;
+    // formed before them, by a wavefront without quads, it was no faster)
     double *const beta_now = gpart + TB * E.G;
     if (EPI && E.source.partial && threadIdx.x < 64) {
-        const double bt = sqrt(wave_total(E.source.partial, E.source.np, (int)threadIdx.x));
-        if (threadIdx.x == 0) {
+        const double bt = sqrt(wave_total(E.source.partial, E.source.np, lane));
+        if (lane == 0) {
             *beta_now = bt;
             if (tile == 0) {
                 *E.source.out = bt;
