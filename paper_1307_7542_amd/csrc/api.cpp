@@ -144,24 +144,39 @@ hub_status create(const hub_model *m, int32_t n_up, int32_t n_dn, hub_sector **o
         C[nn * kBinomN] = 1;
         for (int k = 1; k <= nn; ++k) C[nn * kBinomN + k] = C[(nn - 1) * kBinomN + k - 1] + C[(nn - 1) * kBinomN + k];
     }
-    HUB_TRY(dalloc(s, &s->d_binom, kBinomN * kBinomN));
-    HUB_TRY(dalloc(s, &s->d_bi, s->nb));
-    HUB_TRY(dalloc(s, &s->d_bj, s->nb));
-    HUB_TRY(dalloc(s, &s->d_t, s->nb));
-    HUB_TRY(dalloc(s, &s->d_eps, M));
-    HUB_TRY(dalloc(s, &s->d_U64, M));
-    HUB_TRY(dalloc(s, &s->d_U32, M));
-    std::vector<float> U32(M);
-    for (int i = 0; i < M; ++i) U32[i] = (float)s->U[i];
-    HUB_HIP(hipMemcpy(s->d_binom, C, sizeof(C), hipMemcpyHostToDevice));
-    if (s->nb > 0) {
-        HUB_HIP(hipMemcpy(s->d_bi, s->bi.data(), sizeof(int32_t) * s->nb, hipMemcpyHostToDevice));
-        HUB_HIP(hipMemcpy(s->d_bj, s->bj.data(), sizeof(int32_t) * s->nb, hipMemcpyHostToDevice));
-        HUB_HIP(hipMemcpy(s->d_t, s->t.data(), sizeof(double) * s->nb, hipMemcpyHostToDevice));
+    std::vector<float> U32(s->U.begin(), s->U.end());
+    // values of the compact entries' codes: 2 e for -t_e, 2 e + 1 for t_e, 0 for the rest
+    std::vector<double> code64(256, 0.0);
+    for (int e = 0; e < s->nb && s->nb <= 127; ++e) {
+        code64[2 * e] = -s->t[e];  // esign = +1
+        code64[2 * e + 1] = s->t[e];
     }
-    HUB_HIP(hipMemcpy(s->d_eps, s->eps.data(), sizeof(double) * M, hipMemcpyHostToDevice));
-    HUB_HIP(hipMemcpy(s->d_U64, s->U.data(), sizeof(double) * M, hipMemcpyHostToDevice));
-    HUB_HIP(hipMemcpy(s->d_U32, U32.data(), sizeof(float) * M, hipMemcpyHostToDevice));
+    std::vector<float> code32(code64.begin(), code64.end());
+    // one allocation and one copy for all of them
+    std::vector<unsigned char> blob;
+    struct Part {
+        void **dst;
+        size_t at;
+    };
+    std::vector<Part> parts;
+    auto put = [&](auto **dst, const void *src, size_t bytes) {
+        parts.push_back({(void **)dst, blob.size()});
+        blob.resize((blob.size() + std::max<size_t>(bytes, 1) + 255) / 256 * 256);
+        if (bytes) std::memcpy(blob.data() + parts.back().at, src, bytes);
+    };
+    put(&s->d_binom, C, sizeof(C));
+    put(&s->d_bi, s->bi.data(), sizeof(int32_t) * s->nb);
+    put(&s->d_bj, s->bj.data(), sizeof(int32_t) * s->nb);
+    put(&s->d_t, s->t.data(), sizeof(double) * s->nb);
+    put(&s->d_eps, s->eps.data(), sizeof(double) * M);
+    put(&s->d_U64, s->U.data(), sizeof(double) * M);
+    put(&s->d_U32, U32.data(), sizeof(float) * M);
+    put(&s->d_code64, code64.data(), sizeof(double) * 256);
+    put(&s->d_code32, code32.data(), sizeof(float) * 256);
+    unsigned char *dev = nullptr;
+    HUB_TRY(dalloc(s, &dev, blob.size()));
+    HUB_HIP(hipMemcpy(dev, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    for (const Part &q : parts) *q.dst = dev + q.at;
 
     hipStream_t st = nullptr;
     HUB_TRY(build_spin_tables(s, HUB_SPIN_UP, n_up, st));

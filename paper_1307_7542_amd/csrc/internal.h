@@ -52,9 +52,6 @@ struct SpinTables {
     // 64*sl_off[s] + 64*k + r (padding: column = the row itself, value 0).
     int64_t nslices = 0;
     int32_t *sl_off = nullptr;   // [nslices + 1] slice offsets in units of 64 entries
-    int32_t *ell_col = nullptr;  // [64 sl_off[nslices]]
-    float *ell_v32 = nullptr;
-    double *ell_v64 = nullptr;
     uint2 *ell_pk32 = nullptr;   // packed {column, FP32 value bits}: one 8-byte load per entry
     uint4 *ell_pk64 = nullptr;   // packed {column, 0, FP64 value low, high}: one 16-byte load
     // Compact entries {column : 24 bits, code : 8 bits}, value = code_v[code] with
@@ -62,7 +59,7 @@ struct SpinTables {
     // count < 2^24 and the sector has at most 127 bonds.
     uint32_t *ell_c32 = nullptr;
     uint32_t *ell_q32 = nullptr;  // the same with lds_slot(column) for the column (four-row kernels)
-    double *code_v64 = nullptr;  // [256]
+    double *code_v64 = nullptr;  // [256] (the sector's d_code64)
     float *code_v32 = nullptr;   // [256]
 };
 
@@ -142,6 +139,8 @@ struct hub_sector {
     double *d_eps = nullptr;          // [M]
     double *d_U64 = nullptr;          // [M] per-site U
     float *d_U32 = nullptr;           // [M]
+    double *d_code64 = nullptr;       // [256] values of the compact entries' codes (at most 127 bonds)
+    float *d_code32 = nullptr;        // [256]
     size_t lds_max = 65536;           // dynamic LDS a workgroup may request
     int cu_count = 256;
     bool counted = false;             // in ws_sectors

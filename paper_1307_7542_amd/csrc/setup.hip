@@ -188,7 +188,9 @@ __global__ void k_site_energy(const uint32_t *__restrict__ basis, int64_t count,
     e32[p] = (float)s;
 }
 
-__global__ void k_max_row(const int32_t *__restrict__ rp, int64_t count, int32_t *__restrict__ out)
+// out = {longest row, entries, ELL slots} of H_sigma
+__global__ void k_sizes(const int32_t *__restrict__ rp, int64_t count, const int32_t *__restrict__ sp, int64_t ns,
+                        int32_t *__restrict__ out)
 {
     __shared__ int32_t s[256];
     int32_t m = 0;
@@ -199,7 +201,11 @@ __global__ void k_max_row(const int32_t *__restrict__ rp, int64_t count, int32_t
         if (threadIdx.x < (unsigned)off) s[threadIdx.x] = max(s[threadIdx.x], s[threadIdx.x + off]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out = s[0];
+    if (threadIdx.x == 0) {
+        out[0] = s[0];
+        out[1] = rp[count];
+        out[2] = sp[ns];
+    }
 }
 
 __global__ void k_slice_len(const int32_t *__restrict__ rp, int64_t count, int64_t nslices, int32_t *__restrict__ len)
@@ -215,7 +221,6 @@ __global__ void k_slice_len(const int32_t *__restrict__ rp, int64_t count, int64
 __global__ void k_sell_fill(const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
                             const double *__restrict__ val, const int32_t *__restrict__ bond,
                             const double *__restrict__ t, int64_t count, const int32_t *__restrict__ sp,
-                            int32_t *__restrict__ ecol, float *__restrict__ e32, double *__restrict__ e64,
                             uint2 *__restrict__ pk32, uint4 *__restrict__ pk64, uint32_t *__restrict__ c32,
                             uint32_t *__restrict__ q32)
 {
@@ -240,14 +245,14 @@ __global__ void k_sell_fill(const int32_t *__restrict__ rp, const int32_t *__res
             c = (r < count) ? (int32_t)r : 0;
             v = 0.0;
         }
-        if (c32) c32[o] = ((uint32_t)c & 0xFFFFFFu) | (code << 24);
-        if (q32) q32[o] = ((uint32_t)lds_slot(c, (int)count) & 0xFFFFFFu) | (code << 24);
-        ecol[o] = c;
-        e64[o] = v;
-        e32[o] = (float)v;
-        pk32[o] = make_uint2((uint32_t)c, __float_as_uint((float)v));
-        const unsigned long long vb = (unsigned long long)__double_as_longlong(v);
-        pk64[o] = make_uint4((uint32_t)c, 0u, (uint32_t)(vb & 0xFFFFFFFFull), (uint32_t)(vb >> 32));
+        if (c32) {
+            c32[o] = ((uint32_t)c & 0xFFFFFFu) | (code << 24);
+            q32[o] = ((uint32_t)lds_slot(c, (int)count) & 0xFFFFFFu) | (code << 24);
+        } else {
+            pk32[o] = make_uint2((uint32_t)c, __float_as_uint((float)v));
+            const unsigned long long vb = (unsigned long long)__double_as_longlong(v);
+            pk64[o] = make_uint4((uint32_t)c, 0u, (uint32_t)(vb & 0xFFFFFFFFull), (uint32_t)(vb >> 32));
+        }
     }
 }
 
@@ -355,12 +360,12 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
     HUB_TRY(dalloc(s, &T.e32, count + 3));
     int32_t *rowlen = nullptr;
     int64_t *tmp = nullptr, *bsum = nullptr;
-    int32_t *dmax = nullptr;
+    int32_t *dsizes = nullptr;
     const int64_t nblk = (count + kScanBlock - 1) / kScanBlock;
     HUB_TRY(dalloc(s, &rowlen, count));
     HUB_TRY(dalloc(s, &tmp, count));
     HUB_TRY(dalloc(s, &bsum, nblk));
-    HUB_TRY(dalloc(s, &dmax, 1));
+    HUB_TRY(dalloc(s, &dsizes, 3));
 
     const int B = 256;
     hipLaunchKernelGGL(k_unrank, dim3(grid_for(count, B)), dim3(B), 0, st, T.basis, count, s->M, N, s->d_binom);
@@ -371,22 +376,6 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
     hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)nblk), dim3(kScanBlock), 0, st, rowlen, tmp, bsum, count,
                        T.rp);
     HUB_HIP(hipGetLastError());
-    int32_t nnz32 = 0;
-    HUB_HIP(hipMemcpyAsync(&nnz32, T.rp + count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HUB_HIP(hipStreamSynchronize(st));
-    T.nnz = nnz32;
-    HUB_TRY(dalloc(s, &T.col, T.nnz));
-    HUB_TRY(dalloc(s, &T.val64, T.nnz));
-    HUB_TRY(dalloc(s, &T.val32, T.nnz));
-    HUB_TRY(dalloc(s, &T.bond, T.nnz));
-    hipLaunchKernelGGL(k_csr_fill, dim3(grid_for(count, B)), dim3(B), 0, st, T.basis, count, s->d_bi, s->d_bj,
-                       s->d_t, s->nb, s->d_binom, T.rp, T.col, T.val64, T.val32, T.bond);
-    hipLaunchKernelGGL(k_site_energy, dim3(grid_for(count, B)), dim3(B), 0, st, T.basis, count, s->M, s->d_eps,
-                       T.e64, T.e32);
-    hipLaunchKernelGGL(k_max_row, dim3(1), dim3(256), 0, st, T.rp, count, dmax);
-    HUB_HIP(hipGetLastError());
-    HUB_HIP(hipMemcpyAsync(&T.max_row, dmax, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HUB_HIP(hipStreamSynchronize(st));
 
     // sliced ELL copy (slices of 64 rows)
     T.nslices = (count + 63) / 64;
@@ -402,42 +391,42 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
     hipLaunchKernelGGL(k_scan_local, dim3((unsigned)snblk), dim3(kScanBlock), 0, st, slen, ns, stmp, ssum);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, st, ssum, snblk);
     hipLaunchKernelGGL(k_scan_finish, dim3((unsigned)snblk), dim3(kScanBlock), 0, st, slen, stmp, ssum, ns, sp);
+    // one wait for the three sizes that the tables need
+    hipLaunchKernelGGL(k_sizes, dim3(1), dim3(256), 0, st, T.rp, count, sp, ns, dsizes);
     HUB_HIP(hipGetLastError());
-    int32_t slots = 0;
-    HUB_HIP(hipMemcpyAsync(&slots, sp + ns, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    int32_t sizes[3] = {};
+    HUB_HIP(hipMemcpyAsync(sizes, dsizes, sizeof(sizes), hipMemcpyDeviceToHost, st));
     HUB_HIP(hipStreamSynchronize(st));
+    T.max_row = sizes[0];
+    T.nnz = sizes[1];
+    const int32_t slots = sizes[2];
     if ((int64_t)slots * 64 >= ((int64_t)1 << 31)) {
         set_error("sliced hopping matrix would exceed 2^31 entries");
         return HUB_ERR_RANGE;
     }
     const int64_t nell = 64 * (int64_t)slots;
     T.sl_off = sp;  // in units of 64 entries
-    HUB_TRY(dalloc(s, &T.ell_col, nell));
-    HUB_TRY(dalloc(s, &T.ell_v32, nell));
-    HUB_TRY(dalloc(s, &T.ell_v64, nell));
-    HUB_TRY(dalloc(s, &T.ell_pk32, nell));
-    HUB_TRY(dalloc(s, &T.ell_pk64, nell));
+    HUB_TRY(dalloc(s, &T.col, T.nnz));
+    HUB_TRY(dalloc(s, &T.val64, T.nnz));
+    HUB_TRY(dalloc(s, &T.val32, T.nnz));
+    HUB_TRY(dalloc(s, &T.bond, T.nnz));
+    hipLaunchKernelGGL(k_csr_fill, dim3(grid_for(count, B)), dim3(B), 0, st, T.basis, count, s->d_bi, s->d_bj,
+                       s->d_t, s->nb, s->d_binom, T.rp, T.col, T.val64, T.val32, T.bond);
+    hipLaunchKernelGGL(k_site_energy, dim3(grid_for(count, B)), dim3(B), 0, st, T.basis, count, s->M, s->d_eps,
+                       T.e64, T.e32);
     const bool compact = count < (1 << 24) && s->nb <= 127;
     if (compact) {
         HUB_TRY(dalloc(s, &T.ell_c32, nell));
         HUB_TRY(dalloc(s, &T.ell_q32, nell));
-        HUB_TRY(dalloc(s, &T.code_v64, 256));
-        HUB_TRY(dalloc(s, &T.code_v32, 256));
-        std::vector<double> cv(256, 0.0);
-        std::vector<float> cf(256, 0.0f);
-        for (int e = 0; e < s->nb; ++e) {
-            cv[2 * e] = -s->t[e];  // esign = +1
-            cv[2 * e + 1] = s->t[e];
-            cf[2 * e] = (float)cv[2 * e];
-            cf[2 * e + 1] = (float)cv[2 * e + 1];
-        }
-        HUB_HIP(hipMemcpy(T.code_v64, cv.data(), 256 * sizeof(double), hipMemcpyHostToDevice));
-        HUB_HIP(hipMemcpy(T.code_v32, cf.data(), 256 * sizeof(float), hipMemcpyHostToDevice));
+        T.code_v64 = s->d_code64;
+        T.code_v32 = s->d_code32;
+    } else {
+        HUB_TRY(dalloc(s, &T.ell_pk32, nell));
+        HUB_TRY(dalloc(s, &T.ell_pk64, nell));
     }
     hipLaunchKernelGGL(k_sell_fill, dim3((unsigned)ns), dim3(64), 0, st, T.rp, T.col, T.val64, T.bond, s->d_t, count,
-                       sp, T.ell_col, T.ell_v32, T.ell_v64, T.ell_pk32, T.ell_pk64, T.ell_c32, T.ell_q32);
+                       sp, T.ell_pk32, T.ell_pk64, T.ell_c32, T.ell_q32);
     HUB_HIP(hipGetLastError());
-    HUB_HIP(hipStreamSynchronize(st));
     return HUB_OK;
 }
 
