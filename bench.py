@@ -268,12 +268,14 @@ def k0_timing(hub, torch, model):
 
 
 def kernel_name(sched, es):
-    """Name of the product kernel a tuned schedule launches."""
+    """Name of the product kernels a tuned schedule launches."""
     T = "double" if es == 8 else "float"
+    split = sched["order"] == 2  # the H_dn term in a pass of its own
+    first = f"k_dn_rows<{T}>, " if split else ""
     if sched["family"] == 1:
-        return f"k_kron_quad<{T}, {sched['tile_cols']}, {sched['block']}, {bool(sched['order'])}, false>"
+        return f"{first}k_kron_quad<{T}, {sched['tile_cols']}, {sched['block']}, {sched['order'] == 1}, false>"
     if sched["family"] == 2:
-        return f"k_kron_chunked_parts<{T}, 1024, {sched['quads_per_lane']}, {sched['tile_cols']}, false>"
+        return f"{first}k_kron_chunked_parts<{T}, 1024, {sched['quads_per_lane']}, {sched['tile_cols']}, false>"
     return {3: "k_kron_fused", 4: "k_kron_csr"}.get(sched["family"], "?")
 
 

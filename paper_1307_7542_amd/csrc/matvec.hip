@@ -724,7 +724,7 @@ __global__ void k_epi_colsum(const double *__restrict__ gpart, int G, int cd, do
 // first Lanczos update fused into the store (as in k_kron_quad), each lane
 // summing its rows' products in row order and the workgroup combining the
 // lanes in a fixed tree, one partial per column.
-template <typename T, int TB, int BS, int R, bool CF, bool EPI, bool SPLIT>
+template <typename T, int TB, int BS, int R, bool CF, bool EPI>
 __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *__restrict__ sl_off,
                                                    const Pk<T> *__restrict__ ell, const uint32_t *__restrict__ ellc,
                                                    const T *__restrict__ code_v, int ntiles, LzEpi<T> E)
@@ -764,29 +764,26 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
         for (int j = 0; j < R; ++j) {
             as[j] = min(a0 + j * BS, cu - 1);
 #pragma unroll
-            for (int t = 0; t < TB; ++t)
-                acc[j][t] = SPLIT ? A.y[(int64_t)min(b0 + t, cd - 1) * cu64 + as[j]] : (T)0;
+            for (int t = 0; t < TB; ++t) acc[j][t] = (T)0;
         }
-        if (!SPLIT) {
 #pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                int k = ds[t];
-                for (; k + 4 <= de[t]; k += 4) {
-                    T y[4][R];
+        for (int t = 0; t < TB; ++t) {
+            int k = ds[t];
+            for (; k + 4 <= de[t]; k += 4) {
+                T y[4][R];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < 4; ++u)
 #pragma unroll
-                        for (int j = 0; j < R; ++j) y[u][j] = A.x[(int64_t)A.dn_col[k + u] * cu64 + as[j]];
+                    for (int j = 0; j < R; ++j) y[u][j] = A.x[(int64_t)A.dn_col[k + u] * cu64 + as[j]];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
+                for (int u = 0; u < 4; ++u)
 #pragma unroll
-                        for (int j = 0; j < R; ++j) acc[j][t] = mad(A.dn_val[k + u], y[u][j], acc[j][t]);
-                }
-                for (; k < de[t]; ++k)
-#pragma unroll
-                    for (int j = 0; j < R; ++j)
-                        acc[j][t] = mad(A.dn_val[k], A.x[(int64_t)A.dn_col[k] * cu64 + as[j]], acc[j][t]);
+                    for (int j = 0; j < R; ++j) acc[j][t] = mad(A.dn_val[k + u], y[u][j], acc[j][t]);
             }
+            for (; k < de[t]; ++k)
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    acc[j][t] = mad(A.dn_val[k], A.x[(int64_t)A.dn_col[k] * cu64 + as[j]], acc[j][t]);
         }
 #pragma unroll
         for (int j = 0; j < R; ++j) {
@@ -1203,7 +1200,7 @@ hub_status launch_chunked(const hub_sector *s, const MvArgs<T> &A, hipStream_t s
     return HUB_ERR_UNSUPPORTED;
 }
 
-template <typename T, int TB, int BS, int R, bool EPI, bool SPLIT>
+template <typename T, int TB, int BS, int R, bool EPI>
 hub_status launch_rows(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, const LzEpi<T> &E)
 {
     const SpinTables &U = s->spin[0];
@@ -1212,15 +1209,15 @@ hub_status launch_rows(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, 
     const size_t lim = s->lds_max - (EPI ? (size_t)BS * sizeof(double) : 0);  // beside the static reduction array
     if (U.ell_c32) {
         const size_t lds = (size_t)(A.cu * TB + 256) * sizeof(T);
-        HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, true, EPI, SPLIT>, lim));
-        hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, true, EPI, SPLIT>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
+        HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, true, EPI>, lim));
+        hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, true, EPI>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
                            ell_of<T>(U), U.ell_c32, code_table<T>(U), ntiles, E);
         HUB_HIP(hipGetLastError());
         return HUB_OK;
     }
     const size_t lds = (size_t)A.cu * TB * sizeof(T);
-    HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, false, EPI, SPLIT>, lim));
-    hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, false, EPI, SPLIT>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
+    HUB_TRY(allow_lds(k_kron_fused<T, TB, BS, R, false, EPI>, lim));
+    hipLaunchKernelGGL((k_kron_fused<T, TB, BS, R, false, EPI>), dim3(grid), dim3(BS), lds, st, A, U.sl_off,
                        ell_of<T>(U), (const uint32_t *)nullptr, (const T *)nullptr, ntiles, E);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
@@ -1245,11 +1242,11 @@ hub_status launch_rows_auto(const hub_sector *s, const MvArgs<T> &A, hipStream_t
     const size_t lim = s->lds_max - (E ? 1024 * sizeof(double) : 0);
     const LzEpi<T> ne = no_epi<T>();
     if (2 * col + extra <= lim / 2)
-        return E ? launch_rows<T, 2, 1024, 2, true, false>(s, A, st, *E)
-                 : launch_rows<T, 2, 1024, 2, false, false>(s, A, st, ne);
+        return E ? launch_rows<T, 2, 1024, 2, true>(s, A, st, *E)
+                 : launch_rows<T, 2, 1024, 2, false>(s, A, st, ne);
     if (col + extra <= lim)
-        return E ? launch_rows<T, 1, 1024, 4, true, false>(s, A, st, *E)
-                 : launch_rows<T, 1, 1024, 4, false, false>(s, A, st, ne);
+        return E ? launch_rows<T, 1, 1024, 4, true>(s, A, st, *E)
+                 : launch_rows<T, 1, 1024, 4, false>(s, A, st, ne);
     if (E) {
         set_error("one-row-per-lane product: a column does not fit in LDS beside the update's reduction");
         return HUB_ERR_UNSUPPORTED;
