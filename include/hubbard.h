@@ -36,8 +36,10 @@
  * hub_last_error() gives a thread-local message for the last failure.
  *
  * Threading: a sector is immutable after creation; concurrent hub_matvec calls
- * on one sector from different streams are safe.  hub_ground_state allocates
- * its own workspace per call.
+ * on one sector from different streams are safe.  hub_ground_state takes its
+ * own workspace per call, from blocks that the library keeps between calls (at
+ * most a sixteenth of the device memory while sectors live on the device, 256 MB
+ * otherwise; given back before an allocation of the library fails).
  */
 #ifndef HUBBARD_H
 #define HUBBARD_H
@@ -182,11 +184,12 @@ hub_status hub_matvec(const hub_sector *sec, int32_t dtype, const void *dev_x, v
  * never changes a result.
  *
  *   HUB_SCHED_COLUMNS  whole columns of V staged in LDS, four rows per lane
- *                      (count_up % 4 == 0);
+ *                      (forced: count_up % 4 == 0; tuned: any count_up >= 4);
  *   HUB_SCHED_CHUNKED  columns staged in LDS in chunks of chunk_rows rows, the
  *                      output rows held in registers (columns larger than the
  *                      LDS);
- *   HUB_SCHED_ROWS     one row per lane (count_up % 4 != 0, unaligned vectors);
+ *   HUB_SCHED_ROWS     one row per lane (unaligned vectors, count_up < 4, or no
+ *                      compact entries);
  *   HUB_SCHED_CSR      CSR rows from global memory (no compact entries).
  *
  * By default the first product of each dtype on a sector structure times the
@@ -229,8 +232,9 @@ hub_status hub_get_schedule(const hub_sector *sec, int32_t dtype, int32_t fused,
  *   vec_dtype = HUB_F32: vectors and products in FP32; alpha, beta, the
  *                        reorthogonalisation coefficients, the tridiagonal
  *                        eigenproblem and the optional refinement in FP64.
- *   reorth = 0: plain recurrence; psi by a second pass over the same
- *               recurrence with the stored alpha/beta.
+ *   reorth = 0: plain recurrence; psi from the Lanczos vectors that free
+ *               memory has room to keep, and for the rest by a second pass over
+ *               the same recurrence with the stored alpha/beta.
  *   reorth = 1: full classical Gram-Schmidt against all stored Lanczos
  *               vectors, repeated in the same step when the first pass kept
  *               less than 1/sqrt(2) of the norm (needs max_iter vectors of

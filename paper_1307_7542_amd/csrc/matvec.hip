@@ -18,8 +18,8 @@
 //             are staged chunk by chunk while the output rows stay in registers.
 //   (order 2 of both: the H_dn term in a pass of its own, k_dn_rows, which
 //   leaves it in y; the column kernel then starts from y.)
-//   rows      one row per lane (k_kron_fused), for count_up % 4 != 0 or
-//             vectors that are not 16-byte aligned.
+//   rows      one row per lane (k_kron_fused), for vectors that are not 16-byte
+//             aligned, fewer than four rows or no compact entries.
 //   csr       rows of the CSR gathered from global memory (no compact entries).
 //
 // Every schedule computes each element as: the H_dn entries in column order,
@@ -717,7 +717,7 @@ __global__ void k_epi_colsum(const double *__restrict__ gpart, int G, int cd, do
     apart[b] = sum;
 }
 
-// ---- one row per lane (count_up % 4 != 0, or unaligned vectors) ------------
+// ---- one row per lane (unaligned vectors, fewer than four rows, no compact entries) ----
 // Each lane owns R rows (a, a + BS, ...) at once so the H_dn neighbour reads
 // of all R rows are in flight together.  CF: compact entries (else packed
 // {column, value} entries, for sectors without the compact format).  EPI: the
