@@ -1366,6 +1366,9 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
             for (int xc : {0, 2}) {
                 if (!chunked_shape_ok<T>(tb, qpl) || chunked_rows<T>(s, tb) <= 0) continue;
                 if (xc == 0 && (columns || ragged)) continue;
+                // not worth timing beside the two-pass shapes where rows of H_dn are long (2x9
+                // ladder FP64, 14 entries: 55 to 58 ms against 44; tuning 2.0 s with them, 0.9 without)
+                if (xc == 0 && split && s->spin[1].nnz >= 12 * s->spin[1].count) continue;
                 // two passes: where a tile is not staged whole above, or no one-pass shape exists
                 if (xc == 2 && !(split ? !column_fits<T>(s, tb, epi) : v.empty() || (ragged && !columns))) continue;
                 Sched c;
