@@ -844,9 +844,10 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
 // Bound: lines in flight per CU (about 90 of 128 bytes, 415 cycles each by the
 // counters, so 15 to 20 TB/s over the chip).  Segments of 256 and 512 bytes hit
 // the L2 more often (4x4 torus FP64: 18 and 28 instead of 44 million reads from
-// beyond it) and are no faster.  4x4 torus 0.89 ms FP64, 0.50 ms FP32; 2x9
-// ladder 21.6 / 10.9 ms; re-reading the last entry to fill up the batches of
-// eight cost 1.12 / 0.58 and 23.5 / 11.8 ms.
+// beyond it) and are no faster.  In a product: 4x4 torus FP32 0.56 ms,
+// 2x9 ladder 21.6 / 10.9 ms (FP64 / FP32).  Alone, in ascending order: 4x4 torus
+// 0.89 / 0.50 ms; re-reading the last entry to fill up the batches of eight
+// instead of the tail below, 1.12 / 0.58 ms.
 template <typename T>
 constexpr int kDnRows = 16 / (int)sizeof(T);  // rows per lane
 constexpr int kDnWaves = 4;                   // wavefronts (columns) per workgroup
@@ -1336,7 +1337,7 @@ hub_status time_candidates(hipStream_t st, int n, F launch, int &best, float &be
 // The H_dn term in its own pass reads x and writes y once more, and its
 // gathers run from the L2 instead of from beyond it: worth it where vectors
 // exceed half of the 256 MB MALL (4x4 torus FP64 2.79 -> 2.35 ms, 2x9 ladder
-// FP64 55.4 -> 46.5 ms), not where they stay there (ring M=14 FP64, 94 MB:
+// FP64 55.4 -> 43.7 ms), not where they stay there (ring M=14 FP64, 94 MB:
 // 115 us in one pass, 137 us in two).
 template <typename T>
 bool split_range(const hub_sector *s)
