@@ -18,6 +18,8 @@
 // its bond accumulators in LDS.  Every reduction has a fixed order (lanes
 // over a fixed set of rows and columns, butterflies, in-order sums), so the
 // result is reproducible.
+#include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -102,9 +104,12 @@ __device__ __forceinline__ double signed_by(double v, uint32_t p)
 // each lane adds g[a] x[partner] of its rows to the bond's accumulator.
 // Bound by the LDS gathers, one per row and bond (half of them the broadcast zero).
 // 768 lanes: the accumulators spill at the 128 registers a lane has with 1024.
+// GUARD: the zero place adds nothing, also where g[a] is infinite or NaN and its
+// product with zero would be NaN (the form of a bond without a hop there); slower
+// (4x4 torus 1.65 ms without), so run only when a first run's sums are not finite.
 constexpr int UPB = 768;
 
-template <bool PAIRS>
+template <bool PAIRS, bool GUARD>
 __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, const double *__restrict__ x, int cu,
                                                    int cd, int c0, int n, const uint32_t *__restrict__ part, int nb,
                                                    double *__restrict__ out)
@@ -130,9 +135,11 @@ __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, 
                     for (int u = 0; u < 4; ++u) p[u] = part[(int64_t)(e8 / 2 + u) * cu + a];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        const double v0 = xs[p[u] & 0x7FFFu], v1 = xs[(p[u] >> 16) & 0x7FFFu];
-                        acc[e8 + 2 * u] = fma(signed_by(ga, p[u] << 16), v0, acc[e8 + 2 * u]);
-                        acc[e8 + 2 * u + 1] = fma(signed_by(ga, p[u]), v1, acc[e8 + 2 * u + 1]);
+                        const uint32_t a0 = p[u] & 0x7FFFu, a1 = (p[u] >> 16) & 0x7FFFu;
+                        const double v0 = xs[a0], v1 = xs[a1];
+                        const double g0 = GUARD && a0 == (uint32_t)n ? 0.0 : ga, g1 = GUARD && a1 == (uint32_t)n ? 0.0 : ga;
+                        acc[e8 + 2 * u] = fma(signed_by(g0, p[u] << 16), v0, acc[e8 + 2 * u]);
+                        acc[e8 + 2 * u + 1] = fma(signed_by(g1, p[u]), v1, acc[e8 + 2 * u + 1]);
                     }
                 }
                 continue;
@@ -145,8 +152,9 @@ __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, 
                 for (int u = 0; u < 8; ++u) p[u] = part[(int64_t)min(e8 + u, nb - 1) * cu + a];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const double v = xs[min((p[u] & kNone) - (uint32_t)c0, (uint32_t)n)];
-                    acc[e8 + u] = fma(signed_by(ga, p[u]), v, acc[e8 + u]);
+                    const uint32_t at = min((p[u] & kNone) - (uint32_t)c0, (uint32_t)n);
+                    const double v = xs[at], gu = GUARD && at == (uint32_t)n ? 0.0 : ga;
+                    acc[e8 + u] = fma(signed_by(gu, p[u]), v, acc[e8 + u]);
                 }
             }
         }
@@ -357,10 +365,9 @@ __global__ __launch_bounds__(1024) void k_column_sum(const double *__restrict__ 
 
 hub_status allow_up_lds(size_t bytes)
 {
-    HUB_HIP(hipFuncSetAttribute((const void *)k_up_bonds<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)bytes));
-    HUB_HIP(hipFuncSetAttribute((const void *)k_up_bonds<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)bytes));
+    for (const void *k : {(const void *)k_up_bonds<true, false>, (const void *)k_up_bonds<false, false>,
+                          (const void *)k_up_bonds<true, true>, (const void *)k_up_bonds<false, true>})
+        HUB_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
     return HUB_OK;
 }
 
@@ -417,30 +424,39 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
                            D.basis, s->d_bi, s->d_bj, td);
         hipLaunchKernelGGL(k_dn_bonds, dim3((unsigned)(8 * ((nwork + 7) / 8))), dim3(256), 4 * nb * sizeof(double), st,
                            g, x, cu, cd, ntile, (int)nwork, D.rp, (const uint32_t *)td, D.bond, nb, pd);
-        hipLaunchKernelGGL(k_column_sum, dim3(nb), dim3(1024), 0, st, (const double *)pd, nwork, nb, res, 0);
     }
-    for (int e0 = 0; e0 < nb; e0 += NB) {
-        const int n = std::min(NB, nb - e0);
-        hipLaunchKernelGGL(k_partners, dim3((cu + 255) / 256), dim3(256), 0, st, (int64_t)cu, U.rp, U.col, U.bond,
-                           U.basis, s->d_bi, s->d_bj, e0, tu);
-        for (int c0 = 0; c0 < cu; c0 += chunk) {
-            if (pairs) {
-                hipLaunchKernelGGL(k_partner_pairs, dim3((cu + 255) / 256, NB / 2), dim3(256), 0, st, cu,
-                                   (const uint32_t *)tu, tp);
-                hipLaunchKernelGGL(k_up_bonds<true>, dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, 0, cu,
-                                   (const uint32_t *)tp, n, pu);
-            } else {
-                hipLaunchKernelGGL(k_up_bonds<false>, dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, c0,
-                                   std::min(chunk, cu - c0), (const uint32_t *)tu, n, pu);
-            }
-            hipLaunchKernelGGL(k_column_sum, dim3(n), dim3(1024), 0, st, (const double *)pu, (int64_t)up_grid, NB,
-                               res + e0, 1);
-        }
-    }
-    HUB_HIP(hipGetLastError());
     std::vector<double> h((size_t)nres);
-    HUB_HIP(hipMemcpyAsync(h.data(), res, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
-    HUB_HIP(hipStreamSynchronize(st));
+    auto bonds = [&](auto guard) -> hub_status {
+        constexpr bool G = decltype(guard)::value;
+        if (nb > 0)
+            hipLaunchKernelGGL(k_column_sum, dim3(nb), dim3(1024), 0, st, (const double *)pd, nwork, nb, res, 0);
+        for (int e0 = 0; e0 < nb; e0 += NB) {
+            const int n = std::min(NB, nb - e0);
+            hipLaunchKernelGGL(k_partners, dim3((cu + 255) / 256), dim3(256), 0, st, (int64_t)cu, U.rp, U.col, U.bond,
+                               U.basis, s->d_bi, s->d_bj, e0, tu);
+            for (int c0 = 0; c0 < cu; c0 += chunk) {
+                if (pairs) {
+                    hipLaunchKernelGGL(k_partner_pairs, dim3((cu + 255) / 256, NB / 2), dim3(256), 0, st, cu,
+                                       (const uint32_t *)tu, tp);
+                    hipLaunchKernelGGL((k_up_bonds<true, G>), dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, 0, cu,
+                                       (const uint32_t *)tp, n, pu);
+                } else {
+                    hipLaunchKernelGGL((k_up_bonds<false, G>), dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, c0,
+                                       std::min(chunk, cu - c0), (const uint32_t *)tu, n, pu);
+                }
+                hipLaunchKernelGGL(k_column_sum, dim3(n), dim3(1024), 0, st, (const double *)pu, (int64_t)up_grid, NB,
+                                   res + e0, 1);
+            }
+        }
+        HUB_HIP(hipGetLastError());
+        HUB_HIP(hipMemcpyAsync(h.data(), res, sizeof(double) * h.size(), hipMemcpyDeviceToHost, st));
+        HUB_HIP(hipStreamSynchronize(st));
+        return HUB_OK;
+    };
+    HUB_TRY(bonds(std::false_type{}));
+    bool finite = true;
+    for (int b = 0; b < nb; ++b) finite = finite && std::isfinite(h[(size_t)b]);
+    if (!finite) HUB_TRY(bonds(std::true_type{}));
     for (int b = 0; dbond && b < nb; ++b) dbond[b] = h[(size_t)b];
     for (int i = 0; i < M; ++i) {
         if (dU) dU[i] = h[(size_t)nb + i];

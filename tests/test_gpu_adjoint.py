@@ -45,3 +45,28 @@ def test_bilinear_edges(hub, which):
     assert np.max(np.abs(db - rb), initial=0.0) <= tol
     assert np.max(np.abs(du - ru)) <= tol and np.max(np.abs(de - re)) <= tol
     s.close()
+
+
+# one chunk of a column with paired partners (70 rows), and two chunks (24310 rows)
+@pytest.mark.parametrize("M,n_up,n_dn", [(8, 4, 3), (17, 8, 1)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_bilinear_non_finite_entry(hub, M, n_up, n_dn, bad):
+    """One infinite or NaN entry of g spoils the forms that contain it and no others."""
+    import torch
+    m = W.ring(M, U=3.0, n_up=n_up, n_dn=n_dn)
+    s = hub.Sector(m)
+    up, dn = s.basis(0), s.basis(1)
+    a, b = s.count_up // 3, s.count_dn // 2
+    g, x = s.start_vector(seed=3), s.start_vector(seed=4)
+    ref = s.param_bilinear(g, x)
+    g[b * s.count_up + a] = bad
+    got = s.param_bilinear(g, x)
+    bi, bj, _ = s.bonds()
+    bit = lambda v, i: (int(v) >> int(i)) & 1  # noqa: E731
+    hop = np.array([bit(up[a], i) != bit(up[a], j) or bit(dn[b], i) != bit(dn[b], j) for i, j in zip(bi, bj)])
+    both = np.array([bit(up[a], i) & bit(dn[b], i) for i in range(M)], dtype=bool)
+    assert hop.any() and not hop.all()
+    for r, v, hit in ((ref[0], got[0], hop), (ref[1], got[1], both)):
+        assert not np.isfinite(v[hit]).any()
+        assert np.array_equal(v[~hit], r[~hit])
+    s.close()
