@@ -388,12 +388,9 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
     const size_t up_lds = std::max<size_t>((size_t)chunk + 1, (UPB / 64) * NB) * sizeof(double);
     // spin-down bonds: workgroups per segment of 128 rows (k_dn_bonds)
     const int nseg = (cu + 127) / 128;
-    const int ntile = std::min((cd + 3) / 4, 256);
+    // (fewer where a launch of 256 lanes each would not hold them: below 2^24 in all)
+    const int ntile = std::min(std::min((cd + 3) / 4, 256), ((1 << 24) - 8) / nseg);
     const int64_t nwork = (int64_t)nseg * ntile;
-    if (nwork > INT32_MAX / 8) {
-        set_error("bilinear forms: sector too large");
-        return HUB_ERR_RANGE;
-    }
 
     Workspace mem(st);
     double *res = nullptr, *site = nullptr, *pu = nullptr, *pd = nullptr;  // res: bonds, then U and eps forms

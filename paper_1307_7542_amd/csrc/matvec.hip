@@ -174,10 +174,10 @@ __device__ __forceinline__ void dn_term(T &acc, const MvArgs<T> &A, int ks, int 
 
 // Block -> tile with every XCD (workgroup i runs on XCD i mod 8) owning a
 // contiguous range of tiles; returns -1 for the padding blocks.
-__device__ __forceinline__ int xcd_tile(int ntiles)
+__device__ __forceinline__ int xcd_tile(int ntiles, int block)
 {
     const int per = (ntiles + 7) >> 3;
-    const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    const int t = (block & 7) * per + (block >> 3);
     return t < ntiles ? t : -1;
 }
 
@@ -376,7 +376,7 @@ __global__ __launch_bounds__(BS, TB <= 2 ? 4 : 1) void k_kron_quad(MvArgs<T> A, 
     double *gpart = reinterpret_cast<double *>(xs + TB * ((A.cu + 3) & ~3));  // EPI: TB x G group partials, beta_k
     int tile;
     if (XC) {
-        tile = xcd_tile(ntiles);
+        tile = xcd_tile(ntiles, (int)blockIdx.x);
     } else {
         tile = (int)blockIdx.x < ntiles ? (int)blockIdx.x : -1;
     }
@@ -733,7 +733,7 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
     __shared__ double red[EPI ? BS : 1];
     T *tab = reinterpret_cast<T *>(smem_raw);       // 256 code values (compact format)
     T *xs = tab + (CF ? 256 : 0);
-    const int tile = xcd_tile(ntiles);
+    const int tile = xcd_tile(ntiles, (int)blockIdx.x);
     if (tile < 0) return;
     const int cu = A.cu, cd = A.cd;
     const int b0 = tile * TB;
@@ -853,11 +853,11 @@ constexpr int kDnRows = 16 / (int)sizeof(T);  // rows per lane
 constexpr int kDnWaves = 4;                   // wavefronts (columns) per workgroup
 
 template <typename T>
-__global__ __launch_bounds__(64 * kDnWaves) void k_dn_rows(MvArgs<T> A, int ntile, int nwork)
+__global__ __launch_bounds__(64 * kDnWaves) void k_dn_rows(MvArgs<T> A, int ntile, int nwork, int first)
 {
     typedef T VecU __attribute__((ext_vector_type(kDnRows<T>), aligned(sizeof(T))));
     constexpr int RL = kDnRows<T>;
-    const int wk = xcd_tile(nwork);
+    const int wk = xcd_tile(nwork, first + (int)blockIdx.x);
     if (wk < 0) return;
     const int seg = (int)((uint32_t)wk / (uint32_t)ntile), tile = wk - seg * ntile;
     const int place = tile * kDnWaves + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -1083,7 +1083,21 @@ bool chunked_shape_ok(int tb, int qpl)
 
 // ---- launchers --------------------------------------------------------------
 
-// y = V H_dn^T (count_up >= kDnRows, n = count of segments times columns in blocks)
+// A launch holds fewer than 2^32 lanes (HIP's limit on gridDim.x * blockDim.x).
+bool launchable(int64_t blocks, int lanes) { return blocks * lanes < ((int64_t)1 << 32); }
+
+hub_status check_launch(int64_t blocks, int lanes)
+{
+    if (launchable(blocks, lanes)) return HUB_OK;
+    set_error("product: more work items than one launch holds");
+    return HUB_ERR_UNSUPPORTED;
+}
+
+// y = V H_dn^T (count_up >= kDnRows, n = count of segments times columns in
+// blocks), in launches of kDnLaunch workgroups, 2^31 lanes: beyond 8.6e9 (FP64)
+// or 1.7e10 (FP32) elements the whole list is more than one launch holds.
+constexpr int64_t kDnLaunch = (int64_t)1 << 23;
+
 template <typename T>
 hub_status launch_dn_rows(const MvArgs<T> &A, hipStream_t st)
 {
@@ -1094,9 +1108,24 @@ hub_status launch_dn_rows(const MvArgs<T> &A, hipStream_t st)
         set_error("row-segment pass: the sector is outside its range");
         return HUB_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL((k_dn_rows<T>), dim3((unsigned)grid), dim3(64 * kDnWaves), 0, st, A, ntile, (int)nwork);
+    for (int64_t first = 0; first < grid; first += kDnLaunch)
+        hipLaunchKernelGGL((k_dn_rows<T>), dim3((unsigned)std::min(kDnLaunch, grid - first)), dim3(64 * kDnWaves), 0,
+                           st, A, ntile, (int)nwork, (int)first);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
+}
+
+int64_t quad_blocks(int64_t cd, int tb, int xc)
+{
+    const int64_t ntiles = (cd + tb - 1) / tb;
+    return xc == 1 ? 8 * ((ntiles + 7) / 8) : ntiles;
+}
+
+// row parts of a column, and workgroups, of the row-chunked product
+int64_t chunk_parts(int64_t cu, int qpl) { return (quads(cu) + 1024 * qpl - 1) / (1024 * qpl); }
+int64_t chunk_blocks(int64_t cu, int64_t cd, int tb, int qpl)
+{
+    return 8 * chunk_parts(cu, qpl) * (((cd + tb - 1) / tb + 7) / 8);
 }
 
 template <typename T, int TB, int BS, bool XC, bool EPI, bool SPLIT, bool RAG>
@@ -1104,7 +1133,8 @@ hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st
 {
     const SpinTables &U = s->spin[0];
     const int ntiles = (A.cd + TB - 1) / TB;
-    const unsigned grid = XC ? 8u * (unsigned)((ntiles + 7) / 8) : (unsigned)ntiles;
+    const int64_t grid = quad_blocks(A.cd, TB, XC);
+    HUB_TRY(check_launch(grid, BS));
     const size_t lds = (size_t)(4 * quads(A.cu) * TB + 256) * sizeof(T) +
                        (EPI ? ((size_t)TB * E.G + 1) * sizeof(double) : 0);
     if (lds > s->lds_max) {
@@ -1112,7 +1142,7 @@ hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st
         return HUB_ERR_UNSUPPORTED;
     }
     HUB_TRY(allow_lds(k_kron_quad<T, TB, BS, XC, EPI, SPLIT, RAG>, s->lds_max));
-    hipLaunchKernelGGL((k_kron_quad<T, TB, BS, XC, EPI, SPLIT, RAG>), dim3(grid), dim3(BS), lds, st, A, U.sl_off, U.ell_q32,
+    hipLaunchKernelGGL((k_kron_quad<T, TB, BS, XC, EPI, SPLIT, RAG>), dim3((unsigned)grid), dim3(BS), lds, st, A, U.sl_off, U.ell_q32,
                        code_table<T>(U), ntiles, E);
     HUB_HIP(hipGetLastError());
     return HUB_OK;
@@ -1154,12 +1184,11 @@ hub_status launch_chunked_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t
         set_error("row-chunked product: chunk does not fit in LDS");
         return HUB_ERR_UNSUPPORTED;
     }
-    const int nq = (int)quads(A.cu);
-    const int P = (nq + BSC * QPL - 1) / (BSC * QPL);
-    const int ntiles = (A.cd + TB - 1) / TB;
+    const int P = (int)chunk_parts(A.cu, QPL);
+    const int64_t grid = chunk_blocks(A.cu, A.cd, TB, QPL);
+    HUB_TRY(check_launch(grid, BSC));
     HUB_TRY(allow_lds(k_kron_chunked_parts<T, BSC, QPL, TB, EPI, SPLIT, RAG>, s->lds_max));
-    const unsigned grid = 8u * (unsigned)P * (unsigned)((ntiles + 7) / 8);
-    hipLaunchKernelGGL((k_kron_chunked_parts<T, BSC, QPL, TB, EPI, SPLIT, RAG>), dim3(grid), dim3(BSC), lds, st, A, C.off,
+    hipLaunchKernelGGL((k_kron_chunked_parts<T, BSC, QPL, TB, EPI, SPLIT, RAG>), dim3((unsigned)grid), dim3(BSC), lds, st, A, C.off,
                        C.base, C.ell, code_table<T>(U), C.n, C.rows, (int)U.nslices, P, E);
     if (EPI)
         hipLaunchKernelGGL(k_epi_colsum, dim3((unsigned)((A.cd + 255) / 256)), dim3(256), 0, st,
@@ -1355,6 +1384,7 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
             for (int xc : {0, 1, 2}) {
                 if (xc == 2 && !split) continue;
                 if (ragged && (xc == 0 || (tb == 2 && bs == 1024 && xc == 1))) continue;
+                if (!launchable(quad_blocks(s->spin[1].count, tb, xc), bs)) continue;
                 Sched c;
                 c.fam = HUB_SCHED_COLUMNS;
                 c.tb = tb;
@@ -1366,6 +1396,7 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
         for (int qpl : {4, 8})
             for (int xc : {0, 2}) {
                 if (!chunked_shape_ok<T>(tb, qpl) || chunked_rows<T>(s, tb) <= 0) continue;
+                if (!launchable(chunk_blocks(s->spin[0].count, s->spin[1].count, tb, qpl), 1024)) continue;
                 if (xc == 0 && (columns || ragged)) continue;
                 // not worth timing beside the two-pass shapes where rows of H_dn are long (2x9
                 // ladder FP64, 14 entries: 55 to 58 ms against 44; tuning 2.0 s with them, 0.9 without)
