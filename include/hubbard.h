@@ -36,14 +36,13 @@
  * hub_last_error() gives a thread-local message for the last failure.
  *
  * Threading: a sector is immutable after creation; concurrent hub_matvec calls
- * on one sector from different streams are safe.  hub_ground_state takes its
- * own workspace per call, from blocks that the library keeps between calls (at
- * most a sixteenth of the device memory while sectors live on the device, 256 MB
- * otherwise; given back before an allocation of the library fails).
+ * on one sector from different streams are safe.  A call that needs workspace
+ * takes its own and gives it back when it ends (hub_set_allocator).
  */
 #ifndef HUBBARD_H
 #define HUBBARD_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -256,7 +255,8 @@ hub_status hub_get_schedule(const hub_sector *sec, int32_t dtype, int32_t fused,
  * Returns NOT_CONVERGED (with the best estimate written) when max_iter is hit,
  * and OOM, before allocating anything, when the vectors it needs (three, or
  * max_iter + 2 with reorth = 1, plus FP64 psi and refinement buffers) exceed
- * the free device memory (hipMemGetInfo).
+ * the free device memory (hipMemGetInfo, after the idle memory of the library
+ * and of its allocator has gone back to the driver).
  */
 typedef struct hub_lanczos_opts {
     int32_t max_iter;      /* default 400 when <= 0 */
@@ -457,6 +457,30 @@ hub_status hub_matvec_bytes(const hub_sector *sec, int32_t dtype, int64_t *bytes
 const char *hub_status_str(hub_status s);
 const char *hub_last_error(void);
 const char *hub_version(void);
+
+/*
+ * Where calls take their workspace from.  alloc(bytes, device, stream) returns
+ * device memory whose earlier uses are all queued on `stream`, or NULL;
+ * release(ptr) takes it back after all work on it has finished.  idle(device) and
+ * trim(), which may be NULL, say how much memory the allocator holds idle and
+ * return it to the driver; that is done before the library reports that device
+ * memory has run out, where it would be enough.  They are called
+ * from the thread of the call that needs the memory, for blocks of more than
+ * 32 MB; a block goes back to the functions that it came from.  With alloc and
+ * release NULL (the default) such blocks come from the driver and go back to it,
+ * and solves keep their Lanczos vectors in 256 MB at most.  The Python binding
+ * sets PyTorch's caching allocator.
+ *
+ * Idle smaller blocks (without an allocator, any) stay with the library for the
+ * next call, at most 256 MB a device; hub_workspace_trim gives them back to the
+ * driver (bytes, or NULL: how much that was).
+ */
+typedef void *(*hub_alloc_fn)(size_t bytes, int32_t device, void *stream);
+typedef void (*hub_release_fn)(void *ptr);
+typedef size_t (*hub_idle_fn)(int32_t device);
+typedef void (*hub_trim_fn)(void);
+hub_status hub_set_allocator(hub_alloc_fn alloc, hub_release_fn release, hub_idle_fn idle, hub_trim_fn trim);
+hub_status hub_workspace_trim(int64_t *bytes);
 
 #ifdef __cplusplus
 }

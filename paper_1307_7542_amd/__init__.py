@@ -30,6 +30,7 @@ EXPORTED = [
     "hub_batch_matvec", "hub_batch_ground_state", "hub_apply_fermion", "hub_lanczos_coefficients",
     "hub_continued_fraction", "hub_greens_function", "hub_sector_create_k0", "hub_k0_layout",
     "hub_set_schedule", "hub_get_schedule", "hub_start_vector_noalloc", "hub_gram",
+    "hub_set_allocator", "hub_workspace_trim",
 ]
 
 SCHED_AUTO, SCHED_COLUMNS, SCHED_CHUNKED, SCHED_ROWS, SCHED_CSR = 0, 1, 2, 3, 4
@@ -85,6 +86,37 @@ class LanczosInfo(ctypes.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+# Workspace blocks come from PyTorch's caching allocator: the program's tensors
+# and the library's calls then share one pool, which PyTorch sees and empties.
+# (What torch.cuda.caching_allocator_alloc and _delete call; the library has made
+# `device` current; the wrappers take 5 us more a block.)
+@ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int32, ctypes.c_void_p)
+def _ws_alloc(size, device, stream):
+    torch = _torch()
+    try:
+        if not torch.cuda.is_initialized():
+            torch.cuda.init()
+        return torch._C._cuda_cudaCachingAllocator_raw_alloc(size, stream or 0)
+    except Exception:  # out of memory: the library reports it
+        return None
+
+
+@ctypes.CFUNCTYPE(None, ctypes.c_void_p)
+def _ws_release(ptr):
+    _torch()._C._cuda_cudaCachingAllocator_raw_delete(ptr)
+
+
+@ctypes.CFUNCTYPE(ctypes.c_size_t, ctypes.c_int32)
+def _ws_idle(device):
+    cuda = _torch().cuda
+    return max(0, cuda.memory_reserved(device) - cuda.memory_allocated(device))
+
+
+@ctypes.CFUNCTYPE(None)
+def _ws_trim():
+    _torch().cuda.empty_cache()
+
+
 _lib = None
 
 
@@ -127,6 +159,8 @@ def lib():
             "hub_k0_layout": (i32, [P, P, P, P]),
             "hub_set_schedule": (i32, [P, i32, P]),
             "hub_get_schedule": (i32, [P, i32, i32, P]),
+            "hub_set_allocator": (i32, [P, P, P, P]),
+            "hub_workspace_trim": (i32, [P]),
             "hub_status_str": (ctypes.c_char_p, [i32]),
             "hub_last_error": (ctypes.c_char_p, []),
             "hub_version": (ctypes.c_char_p, []),
@@ -135,6 +169,8 @@ def lib():
             f = getattr(L, name)
             f.restype = res
             f.argtypes = args
+        if L.hub_set_allocator(_ws_alloc, _ws_release, _ws_idle, _ws_trim) != HUB_OK:
+            raise RuntimeError("hub_set_allocator failed")
         _lib = L
     return _lib
 
@@ -485,6 +521,14 @@ class Batch:
                                             _dev_ptr(psi, F64, self.total, "psi") if want else None,
                                             _stream(stream), ctypes.byref(info)), "hub_batch_ground_state", allow)
         return e0, it, psi, info.as_dict()
+
+
+def workspace_trim() -> int:
+    """Give the library's idle workspace blocks back to the driver; returns their
+    bytes.  (Blocks above 32 MB are PyTorch's: ``torch.cuda.empty_cache()``.)"""
+    n = ctypes.c_int64()
+    _check(lib().hub_workspace_trim(ctypes.byref(n)), "hub_workspace_trim")
+    return n.value
 
 
 def version() -> str:

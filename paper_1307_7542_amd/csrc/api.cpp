@@ -37,7 +37,6 @@ void free_sector(hub_sector *s)
 {
     if (!s) return;
     for (void *p : s->owned) (void)hipFree(p);
-    if (s->counted) ws_sectors(s->device, -1);
     s->owned.clear();
     delete s->k0;
     delete s;
@@ -191,8 +190,6 @@ hub_status create(const hub_model *m, int32_t n_up, int32_t n_dn, hub_sector **o
     s->dim = cu * cd;
     HUB_TRY(build_dn_order(s));
     HUB_HIP(hipDeviceSynchronize());
-    ws_sectors(s->device, 1);
-    s->counted = true;
     guard.s = nullptr;
     *out = s;
     return HUB_OK;
@@ -257,22 +254,14 @@ hub_status hub_rank(const hub_sector *sec, int32_t spin, const uint64_t *host_x,
     if (n < 0) return fail(HUB_ERR_INVALID_ARG, "n < 0");
     if (n == 0) return HUB_OK;
     if (!host_x || !host_out) return fail(HUB_ERR_INVALID_ARG, "NULL array");
+    Workspace mem(nullptr);
     void *dx = nullptr, *dout = nullptr;
-    hipError_t e1 = hipMalloc(&dx, sizeof(uint64_t) * n);
-    hipError_t e2 = hipMalloc(&dout, sizeof(int64_t) * n);
-    hub_status st = HUB_OK;
-    if (e1 != hipSuccess || e2 != hipSuccess) {
-        (void)hipGetLastError();
-        st = fail(HUB_ERR_OOM, "hipMalloc failed in hub_rank");
-    }
-    if (st == HUB_OK && hipMemcpy(dx, host_x, sizeof(uint64_t) * n, hipMemcpyHostToDevice) != hipSuccess)
-        st = fail(HUB_ERR_DEVICE, "copy to device failed");
-    if (st == HUB_OK) st = rank_device(sec, spin, (const uint64_t *)dx, n, (int64_t *)dout, nullptr);
-    if (st == HUB_OK && hipMemcpy(host_out, dout, sizeof(int64_t) * n, hipMemcpyDeviceToHost) != hipSuccess)
-        st = fail(HUB_ERR_DEVICE, "copy to host failed");
-    if (dx) (void)hipFree(dx);
-    if (dout) (void)hipFree(dout);
-    return st;
+    HUB_TRY(mem.alloc(&dx, sizeof(uint64_t) * (size_t)n));
+    HUB_TRY(mem.alloc(&dout, sizeof(int64_t) * (size_t)n));
+    HUB_HIP(hipMemcpy(dx, host_x, sizeof(uint64_t) * n, hipMemcpyHostToDevice));
+    HUB_TRY(rank_device(sec, spin, (const uint64_t *)dx, n, (int64_t *)dout, nullptr));
+    HUB_HIP(hipMemcpy(host_out, dout, sizeof(int64_t) * n, hipMemcpyDeviceToHost));
+    return HUB_OK;
 }
 
 hub_status hub_hopping_nnz(const hub_sector *sec, int32_t spin, int64_t *nnz)
@@ -322,14 +311,12 @@ hub_status hub_start_vector(const hub_sector *sec, int32_t dtype, uint64_t seed,
     HUB_TRY(launch_start_vector(HUB_F64 == dtype ? HUB_F64 : HUB_F32, seed, dev_out, sec->dim, st));
     HUB_TRY(k0_project(sec, dtype, dev_out, st));
     if (normalize) {
+        Workspace mem(st);
         double *tmp = nullptr;
-        const size_t nb = sizeof(double) * (kRedGrid + 4);
-        HUB_HIP(hipMalloc((void **)&tmp, nb));
-        hub_status r = launch_dot(dtype, dev_out, dev_out, sec->dim, tmp + 4, tmp, 1, st);
-        if (r == HUB_OK) r = launch_convert(dtype, dev_out, dtype, dev_out, sec->dim, tmp, 1, st);
-        if (r == HUB_OK && hipStreamSynchronize(st) != hipSuccess) r = fail(HUB_ERR_DEVICE, "synchronize failed");
-        (void)hipFree(tmp);
-        return r;
+        HUB_TRY(mem.alloc((void **)&tmp, sizeof(double) * (kRedGrid + 4)));
+        HUB_TRY(launch_dot(dtype, dev_out, dev_out, sec->dim, tmp + 4, tmp, 1, st));
+        HUB_TRY(launch_convert(dtype, dev_out, dtype, dev_out, sec->dim, tmp, 1, st));
+        HUB_HIP(hipStreamSynchronize(st));
     }
     return HUB_OK;
 }
@@ -385,18 +372,9 @@ hub_status hub_gram(int32_t dtype, const void *const *dev_q, int32_t m, int64_t 
     const int ld = 16 * ((m + 15) / 16);
     void **dq = nullptr;
     double *dG = nullptr;
-    struct Free {
-        void *a = nullptr, *b = nullptr;
-        ~Free()
-        {
-            (void)hipFree(a);
-            (void)hipFree(b);
-        }
-    } fr;
-    HUB_HIP(hipMalloc((void **)&dq, sizeof(void *) * (size_t)m));
-    fr.a = dq;
-    HUB_HIP(hipMalloc((void **)&dG, sizeof(double) * (size_t)ld * ld));
-    fr.b = dG;
+    Workspace mem(st);
+    HUB_TRY(mem.alloc((void **)&dq, sizeof(void *) * (size_t)m));
+    HUB_TRY(mem.alloc((void **)&dG, sizeof(double) * (size_t)ld * ld));
     HUB_HIP(hipMemcpyAsync(dq, dev_q, sizeof(void *) * (size_t)m, hipMemcpyHostToDevice, st));
     HUB_TRY(gram_mfma(dtype, (const void *const *)dq, m, n, dG, ld, st));
     std::vector<double> G((size_t)ld * ld);

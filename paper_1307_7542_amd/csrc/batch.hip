@@ -882,14 +882,14 @@ hub_status build_items(hub_batch *b, int di, int target, int tb)
 // the LDS on the batch itself; items hold about size x elements-per-lane
 // elements.
 template <typename T>
-hub_status tune(hub_batch *b, hipStream_t st)
+hub_status tune(hub_batch *b, hipStream_t st, hipStream_t caller_st)
 {
     const int di = (sizeof(T) == 8) ? 0 : 1;
     if (b->tuned[di]) return HUB_OK;
     const auto t0 = std::chrono::steady_clock::now();
     const int64_t n = b->off[b->P];
     T *x = nullptr, *y = nullptr;
-    Workspace mem(st);
+    Workspace mem(st, caller_st);
     HUB_TRY(mem.alloc((void **)&x, sizeof(T) * n));
     HUB_TRY(mem.alloc((void **)&y, sizeof(T) * n));
     hipLaunchKernelGGL(k_b_start<T>, dim3(b->nblocks), dim3(BRB), 0, st, seg_of(b), x, (uint64_t)1);
@@ -1029,10 +1029,10 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     HUB_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     HUB_HIP(hipEventRecord(ev, user_st));
     HUB_HIP(hipStreamWaitEvent(st, ev, 0));
-    HUB_TRY(tune<T>(b, st));
-    if (o->refine) HUB_TRY(tune<double>(b, st));
+    HUB_TRY(tune<T>(b, st, user_st));
+    if (o->refine) HUB_TRY(tune<double>(b, st, user_st));
 
-    Workspace mem(st);
+    Workspace mem(st, user_st);
     auto alloc = [&](void **q, size_t bytes) -> hub_status { return mem.alloc(q, bytes); };
     T *V[3];
     for (int i = 0; i < 3; ++i) HUB_TRY(alloc((void **)&V[i], sizeof(T) * n));
@@ -1059,7 +1059,7 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     if (want_psi) {
         size_t free_b = 0, total_b = 0;
         HUB_HIP(hipMemGetInfo(&free_b, &total_b));
-        kept.budget(sizeof(T) * (size_t)n, free_b + ws_idle_bytes(b->device), max_iter + 1);
+        kept.budget(sizeof(T) * (size_t)n, free_b + ws_idle_bytes(b->device), total_b, max_iter + 1);
     }
     std::vector<T *> hptr;
     hptr.reserve((size_t)max_iter + 2);
@@ -1494,11 +1494,11 @@ hub_status hub_batch_matvec(hub_batch *b, int32_t dtype, const void *dev_x, void
     if (x < y + bytes && y < x + bytes) return bfail(HUB_ERR_INVALID_ARG, "x and y overlap");
     hipStream_t st = (hipStream_t)stream;
     if (dtype == HUB_F64) {
-        HUB_TRY(tune<double>(b, st));
+        HUB_TRY(tune<double>(b, st, st));
         return launch_batch_product<double, false>(b, (const double *)dev_x, (double *)dev_y, nullptr, nullptr,
                                                    nullptr, st);
     }
-    HUB_TRY(tune<float>(b, st));
+    HUB_TRY(tune<float>(b, st, st));
     return launch_batch_product<float, false>(b, (const float *)dev_x, (float *)dev_y, nullptr, nullptr, nullptr, st);
 }
 

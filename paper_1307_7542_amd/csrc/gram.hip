@@ -128,11 +128,8 @@ hub_status gram_t(const void *const *dq, int m, int64_t n, double *dG, int ld, h
     nwg = (int)((n + rows - 1) / rows);
     double *part = nullptr;
     const int per_pass = std::min(ntri, kTilesPerPass);
-    HUB_HIP(hipMalloc((void **)&part, sizeof(double) * 256 * (size_t)nwg * (size_t)per_pass));
-    struct Free {
-        void *p;
-        ~Free() { (void)hipFree(p); }
-    } fr{part};
+    Workspace mem(st);
+    HUB_TRY(mem.alloc((void **)&part, sizeof(double) * 256 * (size_t)nwg * (size_t)per_pass));
     HUB_HIP(hipFuncSetAttribute((const void *)k_gram_mfma<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds));
     for (int t0 = 0; t0 < ntri; t0 += per_pass) {
@@ -143,8 +140,6 @@ hub_status gram_t(const void *const *dq, int m, int64_t n, double *dG, int ld, h
                            nti, nt, ld, dG);
         HUB_HIP(hipGetLastError());
     }
-    // the stream must not run past the workspace's free
-    HUB_HIP(hipStreamSynchronize(st));
     return HUB_OK;
 }
 

@@ -143,7 +143,6 @@ struct hub_sector {
     float *d_code32 = nullptr;        // [256]
     size_t lds_max = 65536;           // dynamic LDS a workgroup may request
     int cu_count = 256;
-    bool counted = false;             // in ws_sectors
     std::vector<void *> owned;        // every device allocation, freed by destroy
     hub::K0Tables *k0 = nullptr;      // set for a translation-symmetric k = 0 sector
     // Product schedules per dtype (0: FP64, 1: FP32): the tuner's pick for the
@@ -159,23 +158,25 @@ struct hub_sector {
 namespace hub {
 
 // ---- workspace (workspace.cpp) ------------------------------------------
-// Device memory for one call on the current device, taken from and given back
-// to a bounded list of idle blocks.
-hub_status ws_alloc(void **p, size_t bytes);
+// Device memory for one call on the current device, from the caller's allocator
+// or a bounded list of idle blocks, and back to where it came from.
+hub_status ws_alloc(void **p, size_t bytes, hipStream_t owner, bool &external);
 // all work on the block has finished (reusable), or its state is unknown (back to the driver)
 void ws_free(int device, void *p, bool reusable);
-void ws_trim();  // gives every idle block of the current device back to the driver
-hipError_t device_alloc(void **p, size_t bytes);  // hipMalloc, once more after ws_trim() if it fails
-size_t ws_idle_bytes(int device);  // held by the list, counted as free memory by size checks
-size_t ws_limit(int device);       // most that the list keeps
-void ws_sectors(int device, int delta);  // sectors living on the device (created / destroyed)
+void ws_reclaim();  // idle blocks, and the caller's allocator's idle memory, back to the driver
+hipError_t device_alloc(void **p, size_t bytes);  // hipMalloc, once more after ws_reclaim() if it fails
+size_t ws_idle_bytes(int device);   // held by the list, counted as free memory by size checks
+size_t ws_caller_idle_bytes(int device);  // held idle by the caller's allocator
+size_t ws_limit(size_t total_bytes);  // most memory that finds its way back to a next call cheaply
 
 // The blocks of one call: waits for the stream and gives them back when it ends.
+// owner: the caller's stream (lives on after the call), if `stream` is not it.
 struct Workspace {
-    hipStream_t st;
+    hipStream_t st, owner;
     int device = 0;
     std::vector<void *> ptrs;
-    explicit Workspace(hipStream_t stream);
+    explicit Workspace(hipStream_t stream) : Workspace(stream, stream) {}
+    Workspace(hipStream_t stream, hipStream_t owner);
     Workspace(const Workspace &) = delete;
     Workspace &operator=(const Workspace &) = delete;
     ~Workspace();
@@ -185,10 +186,12 @@ struct Workspace {
 // The unnormalised vectors u_0, u_1, ... of the plain recurrence, kept for the
 // eigenvector: psi = sum_j (y_j / beta_j) u_j is then one pass over them instead
 // of a second run of the recurrence (ring M=14 FP64, 188 steps: 17.7 GB read
-// once, 3.1 ms, against 40 ms).  They live in slabs of 64 vectors, up to what the
-// workspace list keeps for the next solve and an eighth of the device memory
-// that is free; the vectors beyond that (or beyond a slab that cannot be
-// allocated) are run again from the last two kept ones.
+// once, 3.1 ms, against 40 ms).  They live in slabs of up to 64 vectors and 2 GB (so
+// do the stored vectors of a reorthogonalised solve), up to a sixteenth
+// of the device memory and an eighth of what is free of it (without a caller's
+// allocator, up to what the list of idle blocks keeps for the next call); the
+// vectors beyond that (or beyond a slab that cannot be allocated) are run again
+// from the last two kept ones.
 struct KeptVectors {
     Workspace &mem;
     size_t bytes = 0;        // of one vector, rounded up to keep the slab aligned
@@ -197,20 +200,26 @@ struct KeptVectors {
     char *next = nullptr;
     int64_t left = 0;
     explicit KeptVectors(Workspace &m) : mem(m) {}
-    void budget(size_t vec_bytes, size_t free_bytes, int64_t most)
+    void budget(size_t vec_bytes, size_t free_bytes, size_t total_bytes, int64_t most)
     {
         bytes = (vec_bytes + 255) / 256 * 256;
-        const size_t lim = ws_limit(mem.device);
+        const size_t lim = ws_limit(total_bytes);
         cap = (int64_t)(std::min(free_bytes / 8, lim - lim / 32) / bytes);
         if (cap < 8) cap = 0;  // a handful would not pay for the pass over psi
         cap = std::min(cap, most);
+    }
+    // room for `most` vectors that are known to fit
+    void all(size_t vec_bytes, int64_t most)
+    {
+        bytes = (vec_bytes + 255) / 256 * 256;
+        cap = most;
     }
     // the place of the next vector, or NULL once the budget is spent
     void *take()
     {
         if ((int64_t)u.size() >= cap) return nullptr;
         if (left == 0) {
-            const int64_t k = std::min<int64_t>(64, cap - (int64_t)u.size());
+            const int64_t k = std::min({(int64_t)64, cap - (int64_t)u.size(), (int64_t)(((size_t)2 << 30) / bytes) + 1});
             void *p = nullptr;
             if (mem.alloc(&p, bytes * (size_t)k) != HUB_OK) {
                 cap = (int64_t)u.size();

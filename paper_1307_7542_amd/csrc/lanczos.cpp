@@ -295,6 +295,10 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
         if (want_vec && !dev_psi) need += 8.0 * (double)n;
         if (o->refine) need += 8.0 * (double)n;
         if (matvec_lz_available(s, dt)) need += 8.0 * (double)matvec_lz_workspace(s);
+        if (need > (double)free_b && need <= (double)free_b + (double)ws_caller_idle_bytes(s->device)) {
+            ws_reclaim();
+            HUB_HIP(hipMemGetInfo(&free_b, &total_b));
+        }
         if (need > (double)free_b) {
             set_error("Lanczos workspace of " + std::to_string(need / 1e9) + " GB exceeds the " +
                       std::to_string((double)free_b / 1e9) + " GB of free device memory" +
@@ -335,8 +339,11 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     HUB_TRY(mem.alloc(&W, es * (size_t)n));
     std::vector<void *> Q;  // reorth: every Lanczos vector (append-only, never reallocated)
     Q.reserve((size_t)kmax);
+    KeptVectors stored(mem);
+    stored.all(es * (size_t)n, kmax);
     auto new_q = [&](void **p) -> hub_status {
-        HUB_TRY(mem.alloc(p, es * (size_t)n));
+        *p = stored.take();
+        if (!*p) HUB_TRY(mem.alloc(p, es * (size_t)n));
         Q.push_back(*p);
         return HUB_OK;
     };
@@ -538,7 +545,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     KeptVectors kept(mem);
     std::vector<double> kept_coef;
     if (unnorm && want_vec) {
-        kept.budget(es * (size_t)n, free_b, max_iter);
+        kept.budget(es * (size_t)n, free_b, total_b, max_iter);
         if (kept.cap > 0) {
             void *u0 = kept.take();
             if (u0) {

@@ -1422,14 +1422,10 @@ template <typename T>
 hub_status tune(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, bool epi, double *apart, Sched &out)
 {
     double *zero = nullptr;
-    struct Buf {
-        double *p = nullptr;
-        ~Buf() { (void)hipFree(p); }
-    } zb;
+    Workspace mem(st);
     LzEpi<T> E = no_epi<T>();
     if (epi) {
-        HUB_HIP(hipMalloc((void **)&zero, sizeof(double)));
-        zb.p = zero;
+        HUB_TRY(mem.alloc((void **)&zero, sizeof(double)));
         HUB_HIP(hipMemsetAsync(zero, 0, sizeof(double), st));
         E = LzEpi<T>{A.x, zero, apart, (int)((quads(A.cu) + 63) / 64), nullptr, 0, apart + A.cd, {}};
     }

@@ -485,18 +485,8 @@ static hub_status build_chunk_set(hub_sector *s, int spin, int chunk_rows, Chunk
     const int64_t count = T.count, ns = T.nslices;
     const int P = (int)((count + chunk_rows - 1) / chunk_rows);
     // temporaries freed on every path; the tables themselves are owned by the sector
-    struct Tmp {
-        std::vector<void *> p;
-        ~Tmp()
-        {
-            for (void *q : p) (void)hipFree(q);
-        }
-    } tmp;
-    auto talloc = [&](void **q, size_t bytes) -> hub_status {
-        HUB_HIP(hipMalloc(q, bytes == 0 ? 1 : bytes));
-        tmp.p.push_back(*q);
-        return HUB_OK;
-    };
+    Workspace tmp(st);
+    auto talloc = [&](void **q, size_t bytes) -> hub_status { return tmp.alloc(q, bytes); };
     int32_t *rstart = nullptr, *rlen = nullptr, *slen = nullptr, *offs = nullptr;
     int64_t *stmp = nullptr, *ssum = nullptr;
     const int64_t snblk = (ns + kScanBlock - 1) / kScanBlock;

@@ -169,3 +169,11 @@ def test_bench_refuses_several_gpus():
     assert r.returncode == 2
     out = json.loads(r.stdout.strip().splitlines()[-1])
     assert out["n_gpus"] == 2 and "one GPU" in out["error"]
+
+
+def test_allocator_functions_go_together(L):
+    """alloc without release (or the reverse) is refused and changes nothing."""
+    import paper_1307_7542_amd as hub
+    assert L.hub_set_allocator(hub._ws_alloc, None, None, None) == 1
+    assert L.hub_set_allocator(None, hub._ws_release, None, None) == 1
+    assert L.hub_set_allocator(hub._ws_alloc, hub._ws_release, hub._ws_idle, hub._ws_trim) == 0
