@@ -100,33 +100,38 @@ __device__ __forceinline__ double signed_by(double v, uint32_t p)
 }
 
 // Spin-up bonds: a workgroup takes columns in turn, stages rows [c0, c0 + n) of
-// the x column in LDS (place n holds zero, for partners elsewhere or none), and
-// each lane adds g[a] x[partner] of its rows to the bond's accumulator.
-// Bound by the LDS gathers, one per row and bond (half of them the broadcast zero).
+// the x column in LDS (place n holds zero, for partners elsewhere or none) or, with
+// long columns, gathers them from memory, and each lane adds g[a] x[partner] of its
+// rows, `rows` of them from blockIdx.y on, to the bond's accumulator.
+// Bound by the gathers, one per row and bond (half of them the broadcast zero).
 // 768 lanes: the accumulators spill at the 128 registers a lane has with 1024.
 // GUARD: the zero place adds nothing, also where g[a] is infinite or NaN and its
 // product with zero would be NaN (the form of a bond without a hop there); slower
 // (4x4 torus 1.65 ms without), so run only when a first run's sums are not finite.
 constexpr int UPB = 768;
+enum UpMode { kPairs, kChunk, kGather };  // column staged whole (table of pairs), by chunks, or read from memory
 
-template <bool PAIRS, bool GUARD>
+template <int MODE, bool GUARD>
 __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, const double *__restrict__ x, int cu,
-                                                   int cd, int c0, int n, const uint32_t *__restrict__ part, int nb,
-                                                   double *__restrict__ out)
+                                                   int cd, int rows, int c0, int n, const uint32_t *__restrict__ part,
+                                                   int nb, double *__restrict__ out)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double *xs = reinterpret_cast<double *>(smem_raw);
     double acc[NB];
 #pragma unroll
     for (int e = 0; e < NB; ++e) acc[e] = 0.0;
+    const int a_lo = (int)blockIdx.y * rows, a_hi = min(cu, a_lo + rows);
     for (int b = blockIdx.x; b < cd; b += gridDim.x) {
         const double *__restrict__ xb = x + (int64_t)b * cu + c0, *__restrict__ gb = g + (int64_t)b * cu;
-        for (int a = threadIdx.x; a < n; a += UPB) xs[a] = xb[a];
-        if (threadIdx.x == 0) xs[n] = 0.0;
-        __syncthreads();
-        for (int a = threadIdx.x; a < cu; a += UPB) {
+        if (MODE != kGather) {
+            for (int a = threadIdx.x; a < n; a += UPB) xs[a] = xb[a];
+            if (threadIdx.x == 0) xs[n] = 0.0;
+            __syncthreads();
+        }
+        for (int a = a_lo + (int)threadIdx.x; a < a_hi; a += UPB) {
             const double ga = gb[a];
-            if (PAIRS) {
+            if (MODE == kPairs) {
 #pragma unroll
                 for (int e8 = 0; e8 < NB; e8 += 8) {
                     if (e8 >= nb) break;
@@ -152,13 +157,20 @@ __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, 
                 for (int u = 0; u < 8; ++u) p[u] = part[(int64_t)min(e8 + u, nb - 1) * cu + a];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
+                    if (MODE == kGather) {  // no partner: the lane's own row instead, and nothing added
+                        const bool none = (p[u] & kNone) == kNone;
+                        const double v = xb[none ? (uint32_t)a : p[u] & kNone];
+                        const double sum = fma(signed_by(ga, p[u]), v, acc[e8 + u]);
+                        acc[e8 + u] = none ? acc[e8 + u] : sum;
+                        continue;
+                    }
                     const uint32_t at = min((p[u] & kNone) - (uint32_t)c0, (uint32_t)n);
                     const double v = xs[at], gu = GUARD && at == (uint32_t)n ? 0.0 : ga;
                     acc[e8 + u] = fma(signed_by(gu, p[u]), v, acc[e8 + u]);
                 }
             }
         }
-        __syncthreads();
+        if (MODE != kGather) __syncthreads();
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -171,7 +183,7 @@ __global__ __launch_bounds__(UPB) void k_up_bonds(const double *__restrict__ g, 
         double r = 0.0;
 #pragma unroll
         for (int w = 0; w < UPB / 64; ++w) r += xs[w * NB + threadIdx.x];
-        out[(int64_t)blockIdx.x * NB + threadIdx.x] = r;
+        out[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * NB + threadIdx.x] = r;
     }
 }
 
@@ -291,11 +303,12 @@ __global__ __launch_bounds__(256) void k_dn_bonds(const double *__restrict__ g, 
 // U_i gets n_i(b) t_i, eps_i gets t_i + n_i(b) s.  HBM bound (both vectors once).
 template <int MM>
 __global__ __launch_bounds__(256) void k_site_terms(const double *__restrict__ g, const double *__restrict__ x, int cu,
-                                                    int cd, int M, const uint32_t *__restrict__ up,
+                                                    int cd, int rows, int M, const uint32_t *__restrict__ up,
                                                     const uint32_t *__restrict__ dn, double *__restrict__ out)
 {
     const int lane = threadIdx.x & 63;
     const int wave = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lo = (int)blockIdx.y * rows, hi = min(cu, lo + rows);
     double aU[MM], aE[MM];
 #pragma unroll
     for (int i = 0; i < MM; ++i) aU[i] = aE[i] = 0.0;
@@ -304,14 +317,14 @@ __global__ __launch_bounds__(256) void k_site_terms(const double *__restrict__ g
         double t[MM], s = 0.0;
 #pragma unroll
         for (int i = 0; i < MM; ++i) t[i] = 0.0;
-        for (int r = 0; r < cu; r += 256) {
+        for (int r = lo; r < hi; r += 256) {
             double gx[4];
             uint32_t ua[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int a = r + u * 64 + lane;
-                gx[u] = a < cu ? gb[a] * xb[a] : 0.0;
-                ua[u] = a < cu ? up[a] : 0u;
+                gx[u] = a < hi ? gb[a] * xb[a] : 0.0;
+                ua[u] = a < hi ? up[a] : 0u;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -334,8 +347,9 @@ __global__ __launch_bounds__(256) void k_site_terms(const double *__restrict__ g
     for (int i = 0; i < MM; ++i) {
         const double rU = wave_sum_a(aU[i]), rE = wave_sum_a(aE[i]);
         if (lane == 0 && i < M) {
-            out[(int64_t)wave * 2 * kMaxSites + i] = rU;
-            out[(int64_t)wave * 2 * kMaxSites + kMaxSites + i] = rE;
+            double *o = out + ((int64_t)blockIdx.y * gridDim.x * 4 + wave) * 2 * kMaxSites;
+            o[i] = rU;
+            o[kMaxSites + i] = rE;
         }
     }
 }
@@ -365,8 +379,8 @@ __global__ __launch_bounds__(1024) void k_column_sum(const double *__restrict__ 
 
 hub_status allow_up_lds(size_t bytes)
 {
-    for (const void *k : {(const void *)k_up_bonds<true, false>, (const void *)k_up_bonds<false, false>,
-                          (const void *)k_up_bonds<true, true>, (const void *)k_up_bonds<false, true>})
+    for (const void *k : {(const void *)k_up_bonds<kPairs, false>, (const void *)k_up_bonds<kChunk, false>,
+                          (const void *)k_up_bonds<kPairs, true>, (const void *)k_up_bonds<kChunk, true>})
         HUB_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
     return HUB_OK;
 }
@@ -379,13 +393,31 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
     const SpinTables &U = s->spin[0];
     const SpinTables &D = s->spin[1];
     const int cu = (int)U.count, cd = (int)D.count, M = s->M, nb = s->nb;
+    // `want` workgroups over columns and, where these are fewer, parts of the rows
+    // of at least `least` (one column of 2704156 rows: 1027 ms on one workgroup, by
+    // chunks, 12.7 ms on all of them, 0.67 gathered)
+    auto row_part = [&](int columns, int want, int least) {
+        const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(want / columns, cu / least));
+        return (int)(((cu + parts - 1) / parts + 255) / 256 * 256);
+    };
     // site forms: 4 wavefronts a workgroup, at most 8 workgroups per CU
-    const int site_grid = (int)std::min<int64_t>((cd + 3) / 4, 2048);
+    const int site_cols = (int)std::min<int64_t>((cd + 3) / 4, 2048);
+    const int site_rows = row_part(site_cols, 2048, 1024), site_parts = (cu + site_rows - 1) / site_rows;
+    const int64_t site_grid = (int64_t)site_cols * site_parts;
     // spin-up bonds: one workgroup per CU or two, each with its share of the columns
-    const int up_grid = std::min(cd, 512);
     const size_t lds = s->lds_max;
     const int chunk = (int)std::min<int64_t>(cu, (int64_t)(lds / sizeof(double)) - 1);
-    const size_t up_lds = std::max<size_t>((size_t)chunk + 1, (UPB / 64) * NB) * sizeof(double);
+    const int chunks = (cu + chunk - 1) / chunk;
+    // Chunks cost a pass over the whole table and every row each; from three on x is
+    // gathered from memory instead, 20-site ring with 10 + 1 electrons (10 chunks)
+    // 905 -> 222 us, 2x9 ladder with 9 + 3 (3 chunks) 2.58 -> 2.09 ms.  With two the
+    // chunks are better where it counts: 2x9 ladder with 7 + 7 42.6 against 49.3 ms
+    // (17-site ring with 8 + 7 16.0 against 15.2).
+    const int mode = chunks >= 3 ? kGather : chunks == 1 && cu <= 32767 ? kPairs : kChunk;
+    const int up_cols = std::min(cd, 512);
+    const int up_rows = row_part(up_cols, 512, 4 * UPB), up_parts = (cu + up_rows - 1) / up_rows;
+    const int64_t up_grid = (int64_t)up_cols * up_parts;
+    const size_t up_lds = std::max<size_t>(mode == kGather ? 0 : (size_t)chunk + 1, (UPB / 64) * NB) * sizeof(double);
     // spin-down bonds: workgroups per segment of 128 rows (k_dn_bonds)
     const int nseg = (cu + 127) / 128;
     // (fewer where a launch of 256 lanes each would not hold them: below 2^24 in all)
@@ -395,7 +427,6 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
     Workspace mem(st);
     double *res = nullptr, *site = nullptr, *pu = nullptr, *pd = nullptr;  // res: bonds, then U and eps forms
     uint32_t *tu = nullptr, *td = nullptr, *tp = nullptr;
-    const bool pairs = chunk == cu && cu <= 32767;
     const int nres = nb + 2 * kMaxSites;
     HUB_TRY(mem.alloc((void **)&res, sizeof(double) * (size_t)nres));
     HUB_TRY(mem.alloc((void **)&site, sizeof(double) * (size_t)site_grid * 4 * 2 * kMaxSites));
@@ -404,18 +435,19 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
         HUB_TRY(mem.alloc((void **)&pd, sizeof(double) * (size_t)nwork * (size_t)nb));
         HUB_TRY(mem.alloc((void **)&tu, sizeof(uint32_t) * (size_t)cu * NB));
         HUB_TRY(mem.alloc((void **)&td, sizeof(uint32_t) * (size_t)std::max<int64_t>(D.nnz, 1)));
-        if (pairs) HUB_TRY(mem.alloc((void **)&tp, sizeof(uint32_t) * (size_t)cu * (NB / 2)));
+        if (mode == kPairs) HUB_TRY(mem.alloc((void **)&tp, sizeof(uint32_t) * (size_t)cu * (NB / 2)));
         HUB_TRY(allow_up_lds(lds));
     }
 #define HUB_SITE(MMV)                                                                                           \
-    hipLaunchKernelGGL(k_site_terms<MMV>, dim3(site_grid), dim3(256), 0, st, g, x, cu, cd, M, U.basis, D.basis, site)
+    hipLaunchKernelGGL(k_site_terms<MMV>, dim3(site_cols, site_parts), dim3(256), 0, st, g, x, cu, cd, site_rows, M,    \
+                       U.basis, D.basis, site)
     if (M <= 8) HUB_SITE(8);
     else if (M <= 16) HUB_SITE(16);
     else if (M <= 24) HUB_SITE(24);
     else HUB_SITE(32);
 #undef HUB_SITE
     hipLaunchKernelGGL(k_column_sum, dim3(2 * kMaxSites), dim3(1024), 0, st, (const double *)site,
-                       (int64_t)site_grid * 4, 2 * kMaxSites, res + nb, 0);
+                       site_grid * 4, 2 * kMaxSites, res + nb, 0);
     if (nb > 0) {
         hipLaunchKernelGGL(k_entries, dim3((cd + 255) / 256), dim3(256), 0, st, (int64_t)cd, D.rp, D.col, D.bond,
                            D.basis, s->d_bi, s->d_bj, td);
@@ -431,18 +463,20 @@ hub_status param_bilinear(const hub_sector *s, const double *g, const double *x,
             const int n = std::min(NB, nb - e0);
             hipLaunchKernelGGL(k_partners, dim3((cu + 255) / 256), dim3(256), 0, st, (int64_t)cu, U.rp, U.col, U.bond,
                                U.basis, s->d_bi, s->d_bj, e0, tu);
-            for (int c0 = 0; c0 < cu; c0 += chunk) {
-                if (pairs) {
-                    hipLaunchKernelGGL(k_partner_pairs, dim3((cu + 255) / 256, NB / 2), dim3(256), 0, st, cu,
-                                       (const uint32_t *)tu, tp);
-                    hipLaunchKernelGGL((k_up_bonds<true, G>), dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, 0, cu,
-                                       (const uint32_t *)tp, n, pu);
-                } else {
-                    hipLaunchKernelGGL((k_up_bonds<false, G>), dim3(up_grid), dim3(UPB), up_lds, st, g, x, cu, cd, c0,
-                                       std::min(chunk, cu - c0), (const uint32_t *)tu, n, pu);
-                }
-                hipLaunchKernelGGL(k_column_sum, dim3(n), dim3(1024), 0, st, (const double *)pu, (int64_t)up_grid, NB,
-                                   res + e0, 1);
+            if (mode == kPairs)
+                hipLaunchKernelGGL(k_partner_pairs, dim3((cu + 255) / 256, NB / 2), dim3(256), 0, st, cu,
+                                   (const uint32_t *)tu, tp);
+            for (int c0 = 0; c0 < cu; c0 += mode == kGather ? cu : chunk) {
+                const uint32_t *table = mode == kPairs ? tp : tu;
+                auto run = [&](auto kernel) {
+                    hipLaunchKernelGGL(kernel, dim3(up_cols, up_parts), dim3(UPB), up_lds, st, g, x, cu, cd, up_rows, c0,
+                                       std::min(chunk, cu - c0), table, n, pu);
+                };
+                if (mode == kGather) run(k_up_bonds<kGather, false>);
+                else if (mode == kPairs) run(k_up_bonds<kPairs, G>);
+                else run(k_up_bonds<kChunk, G>);
+                hipLaunchKernelGGL(k_column_sum, dim3(n), dim3(1024), 0, st, (const double *)pu, up_grid, NB, res + e0,
+                                   1);
             }
         }
         HUB_HIP(hipGetLastError());

@@ -28,10 +28,14 @@ def _models():
         "rows1": W.ring(7, U=3.0, n_up=0, n_dn=3),
         "columns1": W.ring(7, U=3.0, n_up=3, n_dn=7),
         "sites25": W.ring(25, U=3.0, n_up=2, n_dn=1),
+        "rows48620": W.ring(18, U=3.0, n_up=9, n_dn=1),                               # gathered, rows in parts
+        "rows167960": W.random_graph(20, 40, seed=13, site_U=True, n_up=9, n_dn=0),         # the same, two bond groups
+        "parts7": W.ring(16, U=3.0, n_up=7, n_dn=0),                                  # one staged column, rows in parts
     }
 
 
-@pytest.mark.parametrize("which", ["bonds36", "bonds72", "rows24310", "rows20349", "rows1", "columns1", "sites25"])
+@pytest.mark.parametrize("which", ["bonds36", "bonds72", "rows24310", "rows20349", "rows1", "columns1", "sites25",
+                                   "rows48620", "rows167960", "parts7"])
 def test_bilinear_edges(hub, which):
     import torch
     m = _models()[which]
@@ -47,8 +51,8 @@ def test_bilinear_edges(hub, which):
     s.close()
 
 
-# one chunk of a column with paired partners (70 rows), and two chunks (24310 rows)
-@pytest.mark.parametrize("M,n_up,n_dn", [(8, 4, 3), (17, 8, 1)])
+# a column with paired partners (70 rows), in two chunks (24310 rows), gathered (48620)
+@pytest.mark.parametrize("M,n_up,n_dn", [(8, 4, 3), (17, 8, 1), (18, 9, 1)])
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_bilinear_non_finite_entry(hub, M, n_up, n_dn, bad):
     """One infinite or NaN entry of g spoils the forms that contain it and no others."""
@@ -69,4 +73,30 @@ def test_bilinear_non_finite_entry(hub, M, n_up, n_dn, bad):
     for r, v, hit in ((ref[0], got[0], hop), (ref[1], got[1], both)):
         assert not np.isfinite(v[hit]).any()
         assert np.array_equal(v[~hit], r[~hit])
+    s.close()
+
+
+# one column of 2704156 rows, and 22 of 497420
+@pytest.mark.parametrize("M,n_up,n_dn", [(24, 12, 0), (22, 9, 1)])
+def test_bilinear_of_few_long_columns_uses_the_chip(hub, M, n_up, n_dn):
+    """The forms of a sector with few columns take no more than 30 products' time
+    (rows and bonds are read a few times, not once per part of a column, and by
+    every CU)."""
+    import time
+    import torch
+    s = hub.Sector(W.ring(M, U=3.0, n_up=n_up, n_dn=n_dn))
+    g, x = s.start_vector(seed=3), s.start_vector(seed=4)
+    y = torch.empty_like(x)
+
+    def best(f):
+        t = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    assert best(lambda: s.param_bilinear(g, x)) <= 30 * best(lambda: s.matvec(x, y))
     s.close()
