@@ -209,7 +209,8 @@ hub_status hub_matvec(const hub_sector *sec, int32_t dtype, const void *dev_x, v
 typedef struct hub_schedule {
     int32_t family;          /* HUB_SCHED_* (AUTO in hub_get_schedule: not chosen yet) */
     int32_t tile_cols;       /* COLUMNS: 1..3; CHUNKED: 1, 2 or 4 columns per workgroup */
-    int32_t block;           /* COLUMNS: 512 or 1024 lanes per workgroup (CHUNKED: 1024) */
+    int32_t block;           /* COLUMNS: 512 or 1024 lanes per workgroup, with order 1 also 64 or 256
+                                (CHUNKED: 1024) */
     int32_t order;           /* COLUMNS: 1 = XCD-contiguous tiles, 0 = launch order;
                                 COLUMNS and CHUNKED: 2 = the H_dn term by a pass of its own */
     int32_t quads_per_lane;  /* CHUNKED: 4 or 8 (a work item covers 4096 * quads_per_lane rows);

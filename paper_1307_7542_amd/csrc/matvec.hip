@@ -1148,8 +1148,8 @@ hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st
     return HUB_OK;
 }
 
-// column product of shape (tb in 1..3, bs in {512, 1024}, xc; 2 = from the H_dn
-// term already in y); E: fused Lanczos update or NULL
+// column product of shape (tb in 1..3, bs in {512, 1024} or, xc = 1, {64, 256}, xc;
+// 2 = from the H_dn term already in y); E: fused Lanczos update or NULL
 template <typename T>
 hub_status launch_quad(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, int tb, int bs, int xc,
                        const LzEpi<T> *E)
@@ -1166,6 +1166,9 @@ hub_status launch_quad(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, 
     HUB_QUAD(3, 512, 0, false) HUB_QUAD(3, 512, 1, false) HUB_QUAD(3, 1024, 0, false) HUB_QUAD(3, 1024, 1, false)
     HUB_QUAD(1, 512, 2, false) HUB_QUAD(1, 1024, 2, false) HUB_QUAD(2, 512, 2, false) HUB_QUAD(2, 1024, 2, false)
     HUB_QUAD(3, 512, 2, false) HUB_QUAD(3, 1024, 2, false)
+    HUB_QUAD(1, 64, 1, false) HUB_QUAD(2, 64, 1, false) HUB_QUAD(3, 64, 1, false)
+    HUB_QUAD(1, 256, 1, false) HUB_QUAD(2, 256, 1, false) HUB_QUAD(3, 256, 1, false)
+    HUB_QUAD(1, 64, 1, true) HUB_QUAD(2, 64, 1, true) HUB_QUAD(1, 256, 1, true) HUB_QUAD(2, 256, 1, true)
     HUB_QUAD(1, 512, 1, true) HUB_QUAD(1, 1024, 1, true) HUB_QUAD(2, 512, 1, true)
     HUB_QUAD(1, 512, 2, true) HUB_QUAD(1, 1024, 2, true) HUB_QUAD(2, 512, 2, true) HUB_QUAD(2, 1024, 2, true)
 #undef HUB_QUAD
@@ -1359,7 +1362,7 @@ hub_status time_candidates(hipStream_t st, int n, F launch, int &best, float &be
 }
 
 // Candidate schedules of a sector: whole columns in LDS when one fits (1-3
-// columns per workgroup, 512 or 1024 lanes, XCD or launch tile order; with the
+// columns per workgroup, 64 to 1024 lanes, XCD or launch tile order; with the
 // fused update, the shapes whose partials also fit), else the row-chunked
 // shapes (1, 2 or 4 columns per work item, 4 or 8 lane-quads per lane), with
 // or without the fused update.
@@ -1374,14 +1377,32 @@ bool split_range(const hub_sector *s)
     return (double)s->dim * sizeof(T) > 128.0 * 1024 * 1024 && s->spin[0].count >= 64 * kDnRows<T>;
 }
 
+// Lanes of a workgroup for cd columns of cu rows: up to 1024 rows no more wavefronts
+// than a column fills (the others stage nothing and only hold registers), in the
+// XCDs' order and in one pass, the best of all shapes there.  FP64: 25 x 480700 637
+// us with 64 lanes, 1209 with 256, 2517 with 512; 276 x 42504 98, 102, 175; 455 x
+// 6435 52, 43, 62; 816 x 48620 378, 312, 360; 1140 x 184756 2.77, 2.41, 2.40 ms; 231 x
+// 497420 (919 MB) 1.55 ms in one pass, 1.73 in two.  With few columns, when the chip
+// is not full, idle wavefronts cost nothing and four share the work around the rows
+// (a Lanczos step of 20 x 20 16.4 us with 64 lanes, 16.0 with 256; 252 x 252 15.5, 15.3).
+bool block_suits(int64_t cu, int64_t cd, int bs)
+{
+    const bool few = cd <= 512;
+    if (bs == 64) return cu <= 512 && !few;
+    if (bs == 256) return (cu > 256 || few) && cu <= 1024;
+    return cu > 1024;
+}
+
 template <typename T>
 std::vector<Sched> candidates(const hub_sector *s, bool epi)
 {
     std::vector<Sched> v;
     const bool ragged = !quad_ok(s), columns = column_fits<T>(s, 1, epi), split = split_range<T>(s);
+    const int64_t cu = s->spin[0].count;
     for (int tb = 1; tb <= (ragged ? 2 : 3) && column_fits<T>(s, tb, epi); ++tb)
-        for (int bs : {512, 1024})
+        for (int bs : {64, 256, 512, 1024})
             for (int xc : {0, 1, 2}) {
+                if (!block_suits(cu, s->spin[1].count, bs) || (cu <= 1024 && xc != 1)) continue;
                 if (xc == 2 && !split) continue;
                 if (ragged && (xc == 0 || (tb == 2 && bs == 1024 && xc == 1))) continue;
                 if (!launchable(quad_blocks(s->spin[1].count, tb, xc), bs)) continue;
@@ -1665,8 +1686,9 @@ hub_status check_forced(const hub_sector *s, const hub_schedule &h, Sched &q)
     switch (q.fam) {
     case HUB_SCHED_COLUMNS:
         if (!quad_ok(s)) return bad("columns schedule needs count_up % 4 == 0 and compact entries");
-        if (q.tb < 1 || q.tb > 3 || (q.bs != 512 && q.bs != 1024) || q.xc < 0 || q.xc > 2)
-            return bad("columns schedule: tile_cols 1..3, block 512 or 1024, order 0, 1 or 2");
+        if (q.tb < 1 || q.tb > 3 || q.xc < 0 || q.xc > 2 ||
+            !(q.bs == 512 || q.bs == 1024 || ((q.bs == 64 || q.bs == 256) && q.xc == 1)))
+            return bad("columns schedule: tile_cols 1..3, block 512 or 1024 with order 0, 1 or 2, 64 or 256 with order 1");
         if (!column_fits<T>(s, q.tb, false)) return bad("columns schedule: the tile does not fit in LDS");
         q.qpl = 0;
         q.crows = 0;

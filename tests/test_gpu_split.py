@@ -95,3 +95,58 @@ def test_column_order_of_dn_pass_bitwise(hub, whole):
     s.set_schedule(hub.F32, hub.SCHED_COLUMNS, tile_cols=2, block=1024, order=2)
     assert torch.equal(s.matvec(x), y0)
     s.close()
+
+
+# count_up: 4 (one quad), 20 and 28, 220 and 252 (within one group of 256 rows),
+# 276 and 816 (two and four groups); ragged 25, 231, 455 (tuned shapes)
+@pytest.mark.parametrize("M,n_up,n_dn", [(4, 1, 2), (20, 1, 4), (8, 2, 3), (12, 3, 2), (10, 5, 4), (24, 2, 2), (18, 3, 2),
+                                         (25, 1, 3), (22, 2, 3), (15, 3, 4)])
+def test_short_columns_bitwise(hub, M, n_up, n_dn):
+    """Workgroups of one or four wavefronts give the CSR kernel's product bit for
+    bit, and a solve through them the energy and steps of 512 lanes."""
+    import torch
+    m = W.ring(M, U=3.0, n_up=n_up, n_dn=n_dn).with_params(eps=[0.07 * i for i in range(M)])
+    s = hub.Sector(m)
+    for dt in (hub.F64, hub.F32):
+        x = s.start_vector(seed=3, dtype=dt)
+        s.set_schedule(dt, hub.SCHED_CSR)
+        y0 = s.matvec(x)
+        s.set_schedule(dt, None)
+        assert torch.equal(s.matvec(x), y0), dt
+        assert s.schedule(dt)["block"] in (64, 256)
+        if s.count_up % 4:
+            continue
+        s.set_schedule(dt, hub.SCHED_COLUMNS, tile_cols=1, block=512, order=1)
+        g0 = s.ground_state(dtype=dt, want_vector=False)
+        for bs in (64, 256):
+            for tb in (1, 2, 3):
+                s.set_schedule(dt, hub.SCHED_COLUMNS, tile_cols=tb, block=bs, order=1)
+                assert torch.equal(s.matvec(x), y0), (dt, bs, tb)
+                g = s.ground_state(dtype=dt, want_vector=False)
+                assert (g.e0, g.info["iters"]) == (g0.e0, g0.info["iters"]), (dt, bs, tb)
+        s.set_schedule(dt, None)
+    s.close()
+
+
+def test_short_columns_take_no_idle_lanes(hub):
+    """A product of 25 x 480700 states takes at most 45 times a copy of its vector
+    (25 with one wavefront a column, 94 with eight)."""
+    import time
+    import torch
+    s = hub.Sector(W.ring(25, U=4.0, n_up=1, n_dn=7))
+    x = s.start_vector(seed=1)
+    y = torch.empty_like(x)
+
+    def best(f):
+        t = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(20):
+                f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    assert best(lambda: s.matvec(x, y)) <= 45 * best(lambda: y.copy_(x))
+    s.close()
