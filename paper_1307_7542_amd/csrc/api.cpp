@@ -188,7 +188,6 @@ hub_status create(const hub_model *m, int32_t n_up, int32_t n_dn, hub_sector **o
     const int64_t cu = s->spin[0].count, cd = s->spin[1].count;
     if (cu > INT32_MAX || cd > INT32_MAX) return fail(HUB_ERR_RANGE, "one-spin dimension exceeds 2^31");
     s->dim = cu * cd;
-    HUB_TRY(build_dn_order(s));
     HUB_HIP(hipDeviceSynchronize());
     guard.s = nullptr;
     *out = s;

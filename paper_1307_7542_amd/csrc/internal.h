@@ -42,7 +42,6 @@ struct SpinTables {
     double *val64 = nullptr;     // [nnz] -t_b * esign
     float *val32 = nullptr;      // [nnz] FP32 copy of val64 (exact: a negated / rounded t)
     int32_t *bond = nullptr;     // [nnz] canonical bond id of the entry
-    int32_t *order = nullptr;    // [count] the rows in breadth-first order (H_dn of larger sectors, else NULL)
     double *e64 = nullptr;       // [count] sum_i eps_i n_i (FP64, ascending i)
     float *e32 = nullptr;        // [count] FP32 copy
     int32_t max_row = 0;         // longest row of H_sigma
@@ -153,6 +152,8 @@ struct hub_sector {
     mutable hub::Sched sched[2], sched_lz[2];
     mutable bool forced[2] = {false, false};
     mutable std::deque<hub::ChunkSet> chunks;  // stable addresses
+    const int32_t *dn_order = nullptr;  // [count_dn], see hub::dn_order
+    bool no_dn_order = false;           // could not be made
 };
 
 namespace hub {
@@ -237,7 +238,10 @@ struct KeptVectors {
 
 // ---- setup (setup.hip) -------------------------------------------------
 hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st);
-hub_status build_dn_order(hub_sector *s);
+// the rows of H_dn in breadth-first order, or NULL: ascending (made on first request,
+// then cached)
+const int32_t *dn_order(const hub_sector *s, hipStream_t st);
+bool capturing(hipStream_t st);
 // rp[0] = 0, rp[k + 1] = len[0] + ... + len[k] (temporaries owned by s)
 hub_status scan_lengths(hub_sector *s, const int32_t *len, int64_t n, int32_t *rp, hipStream_t st);
 // chunk tables of H_spin with `rows` columns per chunk (built once, then cached)

@@ -837,7 +837,7 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
 // (2x9 ladder FP64).  The last lane of a segment overlaps the one before where
 // count_up is no multiple of the 16 bytes (both store the same values).
 // Columns come in breadth-first order of the graph of H_dn where the sector has
-// that list (SpinTables::order): a column's neighbours are then gathered near
+// that list (dn_order): a column's neighbours are then gathered near
 // each other in time, and of the 14 of a 2x9-ladder column 3.9 instead of 6.1
 // miss the L2 (least-recently-used model): 24.5 -> 21.6 ms FP64; 4x4 torus FP32
 // 572 -> 560 us.
@@ -972,14 +972,12 @@ MvArgs<T> make_args(const hub_sector *s, const void *x, void *y)
     A.stream = (double)U.count * (double)D.count * sizeof(T) > 128.0 * 1024 * 1024;
     if constexpr (sizeof(T) == 8) {
         A.up_val = (const T *)U.val64;
-        A.dn_order = D.order;
         A.dn_val = (const T *)D.val64;
         A.e_up = (const T *)U.e64;
         A.e_dn = (const T *)D.e64;
         A.Us = (const T *)s->d_U64;
     } else {
         A.up_val = (const T *)U.val32;
-        A.dn_order = D.order;
         A.dn_val = (const T *)D.val32;
         A.e_up = (const T *)U.e32;
         A.e_dn = (const T *)D.e32;
@@ -1289,10 +1287,11 @@ hub_status launch_rows_auto(const hub_sector *s, const MvArgs<T> &A, hipStream_t
     return HUB_OK;
 }
 
-// Run schedule q; E: the fused Lanczos update (COLUMNS schedules only)
+// Run schedule q; E: the fused Lanczos update (not with CSR)
 template <typename T>
-hub_status launch_sched(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, const Sched &q, const LzEpi<T> *E)
+hub_status launch_sched(const hub_sector *s, MvArgs<T> A, hipStream_t st, const Sched &q, const LzEpi<T> *E)
 {
+    if (q.xc == 2) A.dn_order = dn_order(s, st);
     if (E && q.fam == HUB_SCHED_CSR) {
         set_error("the csr schedule has no fused Lanczos update");
         return HUB_ERR_UNSUPPORTED;

@@ -430,6 +430,16 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
     return HUB_OK;
 }
 
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
 // Breadth-first order of the rows of H_dn from row 0 (every component in turn),
 // for sectors whose product gathers neighbour columns in row segments and cannot
 // keep a segment of every column in an L2: 1 KB each, so from 8192 columns on (8
@@ -439,10 +449,9 @@ hub_status build_spin_tables(hub_sector *s, int spin, int N, hipStream_t st)
 // row, so fewer rows than that would need a hundred products to win it back.
 static constexpr int64_t kOrderCount = 8192;
 
-hub_status build_dn_order(hub_sector *s)
+static hub_status build_dn_order(hub_sector *s)
 {
-    SpinTables &T = s->spin[1];
-    if (T.count < kOrderCount || s->spin[0].count < kOrderCount) return HUB_OK;
+    const SpinTables &T = s->spin[1];
     const size_t count = (size_t)T.count;
     std::vector<int32_t> rp(count + 1), col((size_t)T.nnz), order;
     HUB_HIP(hipMemcpy(rp.data(), T.rp, sizeof(int32_t) * (count + 1), hipMemcpyDeviceToHost));
@@ -464,9 +473,30 @@ hub_status build_dn_order(hub_sector *s)
             }
         }
     }
-    HUB_TRY(dalloc(s, &T.order, T.count));
-    HUB_HIP(hipMemcpy(T.order, order.data(), sizeof(int32_t) * count, hipMemcpyHostToDevice));
+    int32_t *dev = nullptr;
+    HUB_TRY(dalloc(s, &dev, T.count));
+    HUB_HIP(hipMemcpy(dev, order.data(), sizeof(int32_t) * count, hipMemcpyHostToDevice));
+    s->dn_order = dev;
     return HUB_OK;
+}
+
+// Made by the first product that gathers in row segments, under the sector's cache
+// mutex: creating a sector does without (2x9 ladder 0.5 instead of 2.3 ms), and so
+// do k = 0 sectors, forms and short-lived Green's function sectors.  Products come
+// out the same in any order, so without the memory for it, or while the stream is
+// captured (the copies wait), the order is ascending.
+const int32_t *dn_order(const hub_sector *cs, hipStream_t st)
+{
+    hub_sector *s = const_cast<hub_sector *>(cs);  // a cache, not part of the sector's value
+    if (s->dn_order || s->spin[1].count < kOrderCount || s->spin[0].count < kOrderCount || s->no_dn_order ||
+        capturing(st))
+        return s->dn_order;
+    try {
+        if (build_dn_order(s) != HUB_OK) s->no_dn_order = true;
+    } catch (const std::bad_alloc &) {
+        s->no_dn_order = true;
+    }
+    return s->dn_order;
 }
 
 // Chunk tables of H_spin (see ChunkSet), built on first request and kept for
