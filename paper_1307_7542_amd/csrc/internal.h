@@ -246,6 +246,7 @@ bool capturing(hipStream_t st);
 hub_status scan_lengths(hub_sector *s, const int32_t *len, int64_t n, int32_t *rp, hipStream_t st);
 // chunk tables of H_spin with `rows` columns per chunk (built once, then cached)
 hub_status chunk_set(const hub_sector *s, int spin, int rows, const ChunkSet **out, hipStream_t st);
+bool chunk_ready(const hub_sector *s, int spin, int rows);  // built already
 hub_status rank_device(const hub_sector *s, int spin, const uint64_t *dx, int64_t n, int64_t *dout,
                        hipStream_t st);
 

@@ -1291,7 +1291,7 @@ hub_status launch_rows_auto(const hub_sector *s, const MvArgs<T> &A, hipStream_t
 template <typename T>
 hub_status launch_sched(const hub_sector *s, MvArgs<T> A, hipStream_t st, const Sched &q, const LzEpi<T> *E)
 {
-    if (q.xc == 2) A.dn_order = dn_order(s, st);
+    if (q.xc == 2 && (q.fam == HUB_SCHED_COLUMNS || q.fam == HUB_SCHED_CHUNKED)) A.dn_order = dn_order(s, st);
     if (E && q.fam == HUB_SCHED_CSR) {
         set_error("the csr schedule has no fused Lanczos update");
         return HUB_ERR_UNSUPPORTED;
@@ -1483,7 +1483,9 @@ std::map<ShapeKey, Sched> g_shapes;
 // The schedule of the product (epi = false) or of the product fused with the
 // Lanczos update (epi = true) for aligned vectors: forced, cached, shared by a
 // sector of the same structure, or tuned now (under the sector's lock: tuning
-// launches on the caller's stream and may build chunk tables).
+// launches on the caller's stream and may build chunk tables).  Products of columns
+// of odd length have one-row kernels that need neither, so their first product may
+// be captured.
 template <typename T>
 hub_status schedule_for(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, bool epi, double *apart, Sched &out)
 {
@@ -1499,6 +1501,11 @@ hub_status schedule_for(const hub_sector *s, const MvArgs<T> &A, hipStream_t st,
         std::lock_guard<std::mutex> lk2(g_shape_mu);
         auto it = g_shapes.find(key);
         if (it != g_shapes.end()) q = it->second;
+    }
+    if (q.fam == 0 && !epi && !quad_ok(s) && capturing(st)) {
+        out = Sched{};  // tuning waits for the GPU: one row per lane, this time
+        out.fam = HUB_SCHED_ROWS;
+        return HUB_OK;
     }
     if (q.fam == 0) {
         Sched t;
@@ -1530,6 +1537,8 @@ hub_status run_kron(const hub_sector *s, const void *x, void *y, hipStream_t st)
     Sched q;
     HUB_TRY(schedule_for<T>(s, A, st, false, nullptr, q));
     std::lock_guard<std::mutex> lk(s->mu);  // chunk tables may be built on first use
+    if (q.fam == HUB_SCHED_CHUNKED && !quad_ok(s) && !chunk_ready(s, HUB_SPIN_UP, q.crows) && capturing(st))
+        q.fam = HUB_SCHED_ROWS;  // building them waits, too
     return launch_sched<T>(s, A, st, q, nullptr);
 }
 

@@ -572,6 +572,13 @@ static hub_status build_chunk_set(hub_sector *s, int spin, int chunk_rows, Chunk
     return HUB_OK;
 }
 
+bool chunk_ready(const hub_sector *s, int spin, int rows)
+{
+    for (const ChunkSet &c : s->chunks)
+        if (c.spin == (s->shared_spin ? 0 : spin) && c.rows == rows) return true;
+    return false;
+}
+
 hub_status chunk_set(const hub_sector *cs, int spin, int rows, const ChunkSet **out, hipStream_t st)
 {
     hub_sector *s = const_cast<hub_sector *>(cs);  // the chunk cache is not part of the sector's value
