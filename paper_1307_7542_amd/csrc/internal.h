@@ -78,8 +78,9 @@ struct K0Tables {
     int32_t *hop_n = nullptr;    // [R] up hops from each representative
     int hop_max = 0;             // most of one row
     // hop k of row i at [k R + i]: {translation of the hopped state w.r.t. its
-    // representative : 5, the representative's row : 27}, and -t esign * phase *
-    // sqrt(P_i / P_i')
+    // representative (below L), the representative's row : hop_bits}, and -t esign *
+    // phase * sqrt(P_i / P_i')
+    int hop_bits = 31;
     uint32_t *hop_to = nullptr;
     double *hop_c64 = nullptr;
     float *hop_c32 = nullptr;

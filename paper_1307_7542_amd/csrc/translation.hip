@@ -143,7 +143,7 @@ __global__ void k_hop_fill(const uint32_t *__restrict__ reps, int64_t R, const i
                            const double *__restrict__ t, int nb, const uint64_t *__restrict__ C,
                            const int32_t *__restrict__ rep_idx, const int32_t *__restrict__ shift,
                            const int32_t *__restrict__ phase, const int32_t *__restrict__ row,
-                           uint32_t *__restrict__ hto, double *__restrict__ hc64, float *__restrict__ hc32)
+                           uint32_t *__restrict__ hto, int at, double *__restrict__ hc64, float *__restrict__ hc32)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= R) return;
@@ -157,7 +157,7 @@ __global__ void k_hop_fill(const uint32_t *__restrict__ reps, int64_t R, const i
         const int64_t k2 = t_rank(x2, C);
         const int r2 = row[rep_idx[k2]];
         const double c = -t[e] * (double)es * (double)phase[k2] * sqrt((double)rper[r] / (double)rper[r2]);
-        hto[o] = (uint32_t)r2 | ((uint32_t)shift[k2] << 27);
+        hto[o] = (uint32_t)r2 | ((uint32_t)shift[k2] << at);
         hc64[o] = c;
         hc32[o] = (float)c;
         o += R;
@@ -206,6 +206,7 @@ struct K0Args {
     const T *Us;
     const int32_t *hop_n;
     const uint32_t *hop_to;
+    int hop_bits;
     const T *hop_c;
     const int32_t *dn_rp, *dn_col;
     const T *dn_val;
@@ -312,8 +313,8 @@ __global__ __launch_bounds__(BS) void k_k0_product(K0Args<T> A)
         for (int h = 0; h < n; ++h) {
             const uint32_t to = A.hop_to[h * R + i];
             const T c = A.hop_c[h * R + i];
-            const int s = (int)(to >> 27);
-            const int64_t r2 = to & 0x7FFFFFFu;
+            const int s = (int)(to >> A.hop_bits);
+            const int64_t r2 = to & ((1u << A.hop_bits) - 1u);
             const int so = s * (int)R;  // (only used where q R values fit the LDS)
             if (full) {
 #pragma unroll
@@ -403,6 +404,7 @@ K0Args<T> k0_args(const hub_sector *s, const void *x, void *y)
     A.umask = s->umask;
     A.hop_n = K.hop_n;
     A.hop_to = K.hop_to;
+    A.hop_bits = K.hop_bits;
     A.dn_rp = Dn.rp;
     A.dn_col = Dn.col;
     A.orb_off = K.orb_off;
@@ -571,17 +573,15 @@ hub_status build_k0(hub_sector *s, int w, hipStream_t st)
     const unsigned gr = (unsigned)((R + 255) / 256);
     hipLaunchKernelGGL(k_hop_count, dim3(gr), dim3(256), 0, st, K->reps, R, s->d_bi, s->d_bj, s->nb, K->hop_n);
     HUB_HIP(hipGetLastError());
-    std::vector<int32_t> hn(R);
-    HUB_HIP(hipMemcpyAsync(hn.data(), K->hop_n, sizeof(int32_t) * R, hipMemcpyDeviceToHost, st));
-    HUB_HIP(hipStreamSynchronize(st));
-    for (int32_t n : hn) K->hop_max = std::max(K->hop_max, (int)n);
-    if (R >= (1 << 27)) return tfail(HUB_ERR_RANGE, "more than 2^27 representatives");
+    K->hop_max = s->spin[0].max_row;  // a translation maps a state's hops onto its image's
+    while ((1 << (32 - K->hop_bits)) < K->L) --K->hop_bits;
+    if (R > ((int64_t)1 << K->hop_bits)) return tfail(HUB_ERR_RANGE, "more representatives than an entry holds");
     HUB_TRY(talloc(s, &K->hop_to, (size_t)K->hop_max * R));
     HUB_TRY(talloc(s, &K->hop_c64, (size_t)K->hop_max * R));
     HUB_TRY(talloc(s, &K->hop_c32, (size_t)K->hop_max * R));
     hipLaunchKernelGGL(k_hop_fill, dim3(gr), dim3(256), 0, st, K->reps, R, K->period, s->d_bi, s->d_bj, s->d_t,
                        s->nb, (const uint64_t *)s->d_binom, cu.rep_idx, cu.shift, cu.phase, cu.row,
-                       K->hop_to, K->hop_c64, K->hop_c32);
+                       K->hop_to, K->hop_bits, K->hop_c64, K->hop_c32);
     HUB_HIP(hipGetLastError());
     // down cycles: offsets from the representatives' periods
     uint32_t *dreps = nullptr;

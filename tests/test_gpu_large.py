@@ -89,3 +89,27 @@ def test_product_of_many_short_columns(hub):
     got = y[torch.from_numpy(a + b * s.count_up).cuda()].cpu().numpy()
     assert np.all(np.abs(got - ref) <= 42 * 2.0 ** -53 * 2 * mag)
     s.close()
+
+
+# 173686800 representatives (more than 2^27) of 32 sites with 13 electrons under i -> i - 16
+def test_k0_sector_of_many_representatives(hub):
+    """With one bond, H H = t^2 on the states whose ends differ there, and 0 else."""
+    from types import SimpleNamespace
+    import torch
+    if torch.cuda.mem_get_info()[0] < 80e9:
+        torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 80e9:
+        pytest.skip("needs 80 GB of device memory")
+    t = 1.5
+    m = SimpleNamespace(n_sites=32, bonds=[(0, 16)], t=[t], U=[2.0] * 32, eps=[0.0] * 32, n_up=13, n_dn=0)
+    s = hub.Sector(m, translation=16)
+    reps, periods = s.k0_layout()
+    assert len(reps) == 173686800 and s.dim == len(reps) and periods.min() == 2
+    x = s.start_vector(seed=5, normalize=False)
+    y = s.matvec(x)
+    z = s.matvec(y)
+    r = torch.from_numpy(reps.astype(np.int64)).cuda()
+    hops = ((r ^ (r >> 16)) & 1).bool()
+    assert torch.equal(z, torch.where(hops, t * (t * x), torch.zeros_like(x)))
+    assert not torch.equal(y[hops], t * x[hops])   # the hops go somewhere
+    s.close()
