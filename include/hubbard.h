@@ -183,10 +183,11 @@ hub_status hub_matvec(const hub_sector *sec, int32_t dtype, const void *dev_x, v
  * never changes a result.
  *
  *   HUB_SCHED_COLUMNS  whole columns of V staged in LDS, four rows per lane
- *                      (forced: count_up % 4 == 0; tuned: any count_up >= 4);
+ *                      (count_up >= 4; where count_up % 4 != 0, 1 or 2 columns and
+ *                      order 1 or 2, but not 2 columns of 1024 lanes with order 1);
  *   HUB_SCHED_CHUNKED  columns staged in LDS in chunks of chunk_rows rows, the
  *                      output rows held in registers (columns larger than the
- *                      LDS);
+ *                      LDS; order 2 where count_up % 4 != 0);
  *   HUB_SCHED_ROWS     one row per lane (unaligned vectors, count_up < 4, or no
  *                      compact entries);
  *   HUB_SCHED_CSR      CSR rows from global memory (no compact entries).

@@ -1146,8 +1146,16 @@ hub_status launch_quad_k(const hub_sector *s, const MvArgs<T> &A, hipStream_t st
     return HUB_OK;
 }
 
-// column product of shape (tb in 1..3, bs in {512, 1024} or, xc = 1, {64, 256}, xc;
-// 2 = from the H_dn term already in y); E: fused Lanczos update or NULL
+// Shapes that launch_quad has: tb in 1..3 and bs in {512, 1024} or, xc = 1, {64, 256}
+// (xc 2 = from the H_dn term already in y); fewer for ragged columns
+bool quad_shape(bool ragged, int tb, int bs, int xc)
+{
+    const bool wide = bs == 512 || bs == 1024;
+    if (tb < 1 || tb > 3 || xc < 0 || xc > 2 || !(wide || ((bs == 64 || bs == 256) && xc == 1))) return false;
+    return !ragged || (tb <= 2 && xc != 0 && !(tb == 2 && bs == 1024 && xc == 1));
+}
+
+// column product of shape (tb, bs, xc); E: fused Lanczos update or NULL
 template <typename T>
 hub_status launch_quad(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, int tb, int bs, int xc,
                        const LzEpi<T> *E)
@@ -1398,12 +1406,12 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
     std::vector<Sched> v;
     const bool ragged = !quad_ok(s), columns = column_fits<T>(s, 1, epi), split = split_range<T>(s);
     const int64_t cu = s->spin[0].count;
-    for (int tb = 1; tb <= (ragged ? 2 : 3) && column_fits<T>(s, tb, epi); ++tb)
+    for (int tb = 1; tb <= 3 && column_fits<T>(s, tb, epi); ++tb)
         for (int bs : {64, 256, 512, 1024})
             for (int xc : {0, 1, 2}) {
                 if (!block_suits(cu, s->spin[1].count, bs) || (cu <= 1024 && xc != 1)) continue;
                 if (xc == 2 && !split) continue;
-                if (ragged && (xc == 0 || (tb == 2 && bs == 1024 && xc == 1))) continue;
+                if (!quad_shape(ragged, tb, bs, xc)) continue;
                 if (!launchable(quad_blocks(s->spin[1].count, tb, xc), bs)) continue;
                 Sched c;
                 c.fam = HUB_SCHED_COLUMNS;
@@ -1544,8 +1552,8 @@ hub_status run_kron(const hub_sector *s, const void *x, void *y, hipStream_t st)
 
 // Whether the product fused with the first Lanczos update is available: the
 // columns schedule with its partials in LDS, the row-chunked schedule, or one
-// row per lane (count_up % 4 != 0) when a column fits beside the reduction
-// (forced or tuned).
+// row per lane (fewer than four rows, no compact entries) when a column fits beside
+// the reduction (forced or tuned).
 template <typename T>
 bool lz_fusable(const hub_sector *s)
 {
@@ -1555,8 +1563,8 @@ bool lz_fusable(const hub_sector *s)
     if (s->forced[di]) {
         const Sched &q = s->sched[di];
         if (q.nofuse) return false;
-        if (q.fam == HUB_SCHED_COLUMNS) return quad_ok(s) && column_fits<T>(s, q.tb, true);
-        if (q.fam == HUB_SCHED_CHUNKED) return quad_ok(s);
+        if (q.fam == HUB_SCHED_COLUMNS) return quad_any(s) && column_fits<T>(s, q.tb, true);
+        if (q.fam == HUB_SCHED_CHUNKED) return quad_any(s);
         return q.fam == HUB_SCHED_ROWS && rows_fit<T>(s, true);
     }
     if (!quad_any(s)) return rows_fit<T>(s, true);
@@ -1693,16 +1701,17 @@ hub_status check_forced(const hub_sector *s, const hub_schedule &h, Sched &q)
     };
     switch (q.fam) {
     case HUB_SCHED_COLUMNS:
-        if (!quad_ok(s)) return bad("columns schedule needs count_up % 4 == 0 and compact entries");
-        if (q.tb < 1 || q.tb > 3 || q.xc < 0 || q.xc > 2 ||
-            !(q.bs == 512 || q.bs == 1024 || ((q.bs == 64 || q.bs == 256) && q.xc == 1)))
-            return bad("columns schedule: tile_cols 1..3, block 512 or 1024 with order 0, 1 or 2, 64 or 256 with order 1");
+        if (!quad_any(s)) return bad("columns schedule needs count_up >= 4 and compact entries");
+        if (!quad_shape(!quad_ok(s), q.tb, q.bs, q.xc))
+            return bad("columns schedule: tile_cols 1..3, block 512 or 1024 with order 0, 1 or 2, 64 or 256 with order 1 "
+                       "(count_up % 4 != 0: tile_cols 1 or 2, order 1 or 2, not 2 columns of 1024 lanes with order 1)");
         if (!column_fits<T>(s, q.tb, false)) return bad("columns schedule: the tile does not fit in LDS");
         q.qpl = 0;
         q.crows = 0;
         break;
     case HUB_SCHED_CHUNKED:
-        if (!quad_ok(s)) return bad("chunked schedule needs count_up % 4 == 0 and compact entries");
+        if (!quad_any(s)) return bad("chunked schedule needs count_up >= 4 and compact entries");
+        if (!quad_ok(s) && q.xc != 2) return bad("chunked schedule: order 2 where count_up % 4 != 0");
         if (!chunked_shape_ok<T>(q.tb, q.qpl))
             return bad("chunked schedule: tile_cols 1, 2 or 4 and quads_per_lane 4 or 8 "
                        "(tile_cols * quads_per_lane <= 16 in FP32, 8 in FP64)");

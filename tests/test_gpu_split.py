@@ -190,3 +190,44 @@ def test_two_pass_product_captured_first(hub):
         torch.cuda.synchronize()
         assert torch.equal(y, z), seed
     s.close()
+
+
+# count_up % 4 = 1, 2, 3: 21 (one group of 256 rows), 126, 715 and 455 (several groups)
+@pytest.mark.parametrize("M,n_up,n_dn", [(7, 2, 3), (9, 4, 4), (13, 4, 2), (15, 3, 2)])
+def test_every_ragged_shape_bitwise(hub, M, n_up, n_dn):
+    """Every shape that columns of odd length can have gives the CSR kernel's product
+    bit for bit and the fused solve's energy and steps, and what the tuner reports can
+    be set again."""
+    import torch
+    m = W.ring(M, U=2.0, n_up=n_up, n_dn=n_dn).with_params(eps=[0.05 * ((5 * i) % M) for i in range(M)])
+    s = hub.Sector(m)
+    assert s.count_up % 4 != 0
+    for dt in (hub.F64, hub.F32):
+        x = s.start_vector(seed=5, dtype=dt)
+        s.matvec(x)
+        tuned = s.schedule(dt)
+        s.set_schedule(dt, tuned["family"], tile_cols=tuned["tile_cols"], block=tuned["block"], order=tuned["order"])
+        assert {**s.schedule(dt), "ms": 0} == {**tuned, "ms": 0}
+        s.set_schedule(dt, hub.SCHED_CSR)
+        y0 = s.matvec(x)
+        g0 = None
+        shapes = [(hub.SCHED_COLUMNS, dict(tile_cols=tb, block=bs, order=o)) for tb in (1, 2)
+                  for bs, o in ((64, 1), (256, 1), (512, 1), (1024, 1), (512, 2), (1024, 2)) if (tb, bs, o) != (2, 1024, 1)]
+        shapes += [(hub.SCHED_CHUNKED, dict(tile_cols=tb, quads_per_lane=q, chunk_rows=c, order=2))
+                   for tb, q in ((1, 4), (2, 4), (1, 8)) for c in (0, 100)]
+        for fam, kw in shapes:
+            s.set_schedule(dt, fam, **kw)
+            assert torch.equal(s.matvec(x), y0), (dt, fam, kw)
+            g = s.ground_state(dtype=dt, want_vector=False)
+            g0 = g0 or g
+            assert (g.e0, g.info["iters"]) == (g0.e0, g0.info["iters"]), (dt, fam, kw)
+        for fam, kw in ((hub.SCHED_COLUMNS, dict(tile_cols=1, block=512, order=0)),
+                        (hub.SCHED_COLUMNS, dict(tile_cols=3, block=512, order=1)),
+                        (hub.SCHED_COLUMNS, dict(tile_cols=2, block=1024, order=1)),
+                        (hub.SCHED_COLUMNS, dict(tile_cols=1, block=64, order=2)),
+                        (hub.SCHED_CHUNKED, dict(tile_cols=1, quads_per_lane=4, order=0))):
+            with pytest.raises(hub.HubError) as e:
+                s.set_schedule(dt, fam, **kw)
+            assert e.value.status == 1, kw
+        s.set_schedule(dt, None)
+    s.close()
