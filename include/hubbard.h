@@ -277,6 +277,8 @@ typedef struct hub_lanczos_opts {
     int32_t batch_no_graph; /* hub_batch_ground_state only: 1 launches every step's kernels eagerly
                                instead of replaying the captured step graphs (same kernels, same order,
                                same results); ignored by hub_ground_state */
+    int32_t keep_vectors;  /* plain recurrence with psi: Lanczos vectors kept for it, 0 as many as memory has
+                              room for, n > 0 at most n, < 0 none (the others are run a second time) */
 } hub_lanczos_opts;
 
 typedef struct hub_lanczos_info {

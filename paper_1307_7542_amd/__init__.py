@@ -68,7 +68,7 @@ class LanczosOpts(ctypes.Structure):
         ("dev_start", ctypes.c_void_p), ("vec_dtype", ctypes.c_int32), ("reorth", ctypes.c_int32),
         ("want_vector", ctypes.c_int32), ("refine", ctypes.c_int32), ("check_every", ctypes.c_int32),
         ("time_kernels", ctypes.c_int32), ("e0_target", ctypes.c_double), ("e0_target_rel", ctypes.c_double),
-        ("orth_check", ctypes.c_int32), ("batch_no_graph", ctypes.c_int32),
+        ("orth_check", ctypes.c_int32), ("batch_no_graph", ctypes.c_int32), ("keep_vectors", ctypes.c_int32),
     ]
 
 
@@ -206,6 +206,11 @@ def _dev_ptr(t, dtype_code: int, n: int, name: str):
     if not t.is_cuda or t.dtype != want or not t.is_contiguous() or t.numel() != n:
         raise ValueError(f"{name} must be a contiguous CUDA {want} tensor with {n} elements")
     return ctypes.c_void_p(t.data_ptr())
+
+
+def _keep(keep_vectors):
+    """hub_lanczos_opts.keep_vectors: 0 no limit, n > 0 at most n, -1 none."""
+    return 0 if keep_vectors is None else int(keep_vectors) or -1
 
 
 @dataclass
@@ -358,9 +363,11 @@ class Sector:
                      refine: bool = False, max_iter: int = 400, tol: float = 0.0, seed: int = 7542,
                      start=None, check_every: int = 1, time_kernels: int = 0, psi=None,
                      stream=None, allow_not_converged: bool = False, e0_target: Optional[float] = None,
-                     e0_target_rel: float = 0.0, orth_check: bool = False) -> GroundState:
+                     e0_target_rel: float = 0.0, orth_check: bool = False,
+                     keep_vectors: Optional[int] = None) -> GroundState:
         """reorth: False / 0 plain recurrence, True / 1 / "full" full, 2 / "partial" partial
-        reorthogonalisation (Simon's omega recurrence)."""
+        reorthogonalisation (Simon's omega recurrence).  keep_vectors: most Lanczos vectors
+        that a plain solve keeps for psi (None: as many as there is room for)."""
         ro = {"full": 1, "partial": 2}.get(reorth, reorth) if isinstance(reorth, str) else int(reorth)
         want = want_vector or refine
         if want and psi is None:
@@ -369,7 +376,7 @@ class Sector:
                         _dev_ptr(start, F64, self.dim, "start") if start is not None else None,
                         dtype, ro, int(want_vector), int(refine), check_every, int(time_kernels),
                         float(e0_target or 0.0), float(e0_target_rel if e0_target is not None else 0.0),
-                        int(orth_check))
+                        int(orth_check), 0, _keep(keep_vectors))
         info = LanczosInfo()
         e0 = ctypes.c_double()
         allow = (HUB_OK, HUB_ERR_NOT_CONVERGED) if allow_not_converged else (HUB_OK,)
@@ -508,11 +515,12 @@ class Batch:
 
     def ground_state(self, *, dtype: int = F64, want_vector: bool = False, refine: bool = False,
                      max_iter: int = 400, tol: float = 0.0, seed: int = 7542, check_every: int = 5,
-                     stream=None, allow_not_converged: bool = False, graph: bool = True):
+                     stream=None, allow_not_converged: bool = False, graph: bool = True,
+                     keep_vectors: Optional[int] = None):
         want = want_vector or refine
         psi = self.empty(F64) if want else None
         o = LanczosOpts(max_iter, tol, seed, None, dtype, 0, int(want_vector), int(refine), check_every, 0, 0.0, 0.0,
-                        0, int(not graph))
+                        0, int(not graph), _keep(keep_vectors))
         e0 = np.zeros(len(self.sectors))
         it = np.zeros(len(self.sectors), dtype=np.int32)
         info = BatchInfo()

@@ -1059,7 +1059,8 @@ hub_status batch_solve(hub_batch *b, const hub_lanczos_opts *o, double *e0_out, 
     if (want_psi) {
         size_t free_b = 0, total_b = 0;
         HUB_HIP(hipMemGetInfo(&free_b, &total_b));
-        kept.budget(sizeof(T) * (size_t)n, free_b + ws_idle_bytes(b->device), total_b, max_iter + 1);
+        kept.budget(sizeof(T) * (size_t)n, free_b + ws_idle_bytes(b->device), total_b, max_iter + 1,
+                    o->keep_vectors);
     }
     std::vector<T *> hptr;
     hptr.reserve((size_t)max_iter + 2);

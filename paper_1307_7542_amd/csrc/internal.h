@@ -202,13 +202,15 @@ struct KeptVectors {
     char *next = nullptr;
     int64_t left = 0;
     explicit KeptVectors(Workspace &m) : mem(m) {}
-    void budget(size_t vec_bytes, size_t free_bytes, size_t total_bytes, int64_t most)
+    // at most `most` vectors, and as hub_lanczos_opts.keep_vectors asks
+    void budget(size_t vec_bytes, size_t free_bytes, size_t total_bytes, int64_t most, int32_t keep)
     {
         bytes = (vec_bytes + 255) / 256 * 256;
         const size_t lim = ws_limit(total_bytes);
         cap = (int64_t)(std::min(free_bytes / 8, lim - lim / 32) / bytes);
         if (cap < 8) cap = 0;  // a handful would not pay for the pass over psi
         cap = std::min(cap, most);
+        if (keep != 0) cap = std::min(cap, (int64_t)std::max(keep, 0));
     }
     // room for `most` vectors that are known to fit
     void all(size_t vec_bytes, int64_t most)

@@ -545,7 +545,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     KeptVectors kept(mem);
     std::vector<double> kept_coef;
     if (unnorm && want_vec) {
-        kept.budget(es * (size_t)n, free_b, total_b, max_iter);
+        kept.budget(es * (size_t)n, free_b, total_b, max_iter, o->keep_vectors);
         if (kept.cap > 0) {
             void *u0 = kept.take();
             if (u0) {
@@ -717,6 +717,7 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
                 u = kept.u[(size_t)mk - 1];
                 up = mk > 1 ? kept.u[(size_t)mk - 2] : nullptr;
             } else {
+                W = free_buffer(u, nullptr);  // make_start's scratch
                 HUB_TRY(make_start(u));
                 HUB_TRY(launch_psi_acc(dt, psi, u, d_y, n, 1, st));
             }
