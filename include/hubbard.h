@@ -344,7 +344,7 @@ typedef struct hub_batch_info {
     int32_t steps;            /* lockstep Lanczos steps executed (max over sectors; includes the
                                  group run while the last convergence test was on the host) */
     int32_t graph_replays;    /* steps executed by replaying a captured step or group graph */
-    int32_t rows_per_lane;    /* tuned product: rows each lane has in flight at once */
+    int32_t rows_per_lane;    /* product: consecutive rows of a column per lane (4) */
     int32_t block_size;       /* tuned workgroup size of the product */
     int32_t cols_per_lane;    /* tuned product: columns each lane forms from one H_up entry stream */
     double seconds;           /* wall time of the call */
