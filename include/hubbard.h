@@ -470,7 +470,8 @@ const char *hub_version(void);
  * return it to the driver; that is done before the library reports that device
  * memory has run out, where it would be enough.  They are called
  * from the thread of the call that needs the memory, for blocks of more than
- * 32 MB; a block goes back to the functions that it came from.  With alloc and
+ * 32 MB; a block goes back to the functions that it came from, and one that
+ * alloc refuses comes from the driver if the call cannot do without it.  With alloc and
  * release NULL (the default) such blocks come from the driver and go back to it,
  * and solves keep their Lanczos vectors in 256 MB at most.  The Python binding
  * sets PyTorch's caching allocator.

@@ -162,7 +162,7 @@ namespace hub {
 // ---- workspace (workspace.cpp) ------------------------------------------
 // Device memory for one call on the current device, from the caller's allocator
 // or a bounded list of idle blocks, and back to where it came from.
-hub_status ws_alloc(void **p, size_t bytes, hipStream_t owner, bool &external);
+hub_status ws_alloc(void **p, size_t bytes, hipStream_t owner, bool spare, bool &external);
 // all work on the block has finished (reusable), or its state is unknown (back to the driver)
 void ws_free(int device, void *p, bool reusable);
 void ws_reclaim();  // idle blocks, and the caller's allocator's idle memory, back to the driver
@@ -182,7 +182,8 @@ struct Workspace {
     Workspace(const Workspace &) = delete;
     Workspace &operator=(const Workspace &) = delete;
     ~Workspace();
-    hub_status alloc(void **p, size_t bytes);
+    // spare: the call can do without it
+    hub_status alloc(void **p, size_t bytes, bool spare = false);
 };
 
 // The unnormalised vectors u_0, u_1, ... of the plain recurrence, kept for the
@@ -225,7 +226,7 @@ struct KeptVectors {
         if (left == 0) {
             const int64_t k = std::min({(int64_t)64, cap - (int64_t)u.size(), (int64_t)(((size_t)2 << 30) / bytes) + 1});
             void *p = nullptr;
-            if (mem.alloc(&p, bytes * (size_t)k) != HUB_OK) {
+            if (mem.alloc(&p, bytes * (size_t)k, true) != HUB_OK) {
                 cap = (int64_t)u.size();
                 return nullptr;
             }

@@ -133,8 +133,10 @@ hipError_t device_alloc(void **p, size_t bytes)
 }
 
 // owner: the stream on which the block is taken from the caller's allocator;
-// external: it was (work of another stream then waits for that one)
-hub_status ws_alloc(void **p, size_t bytes, hipStream_t owner, bool &external)
+// external: it was (work of another stream then waits for that one).  What the
+// allocator refuses (a limit of its own, say) comes from the driver if the call needs
+// it, and not at all if it is spare.
+hub_status ws_alloc(void **p, size_t bytes, hipStream_t owner, bool spare, bool &external)
 try {
     *p = nullptr;
     external = false;
@@ -147,8 +149,9 @@ try {
     Block b{bytes, nullptr};
     if (a.alloc && bytes > kOwn) {
         *p = a.alloc(bytes, device, owner);
-        if (!*p && trim_all() > 0) *p = a.alloc(bytes, device, owner);
-        if (!*p) return no_memory(bytes, "refused by the caller's allocator");
+        if (!*p && spare) return no_memory(bytes, "refused by the caller's allocator");
+    }
+    if (*p) {
         b.release = a.release;
         external = true;
     } else {
@@ -244,7 +247,7 @@ Workspace::~Workspace()
     for (void *p : ptrs) ws_free(device, p, idle);
 }
 
-hub_status Workspace::alloc(void **p, size_t bytes)
+hub_status Workspace::alloc(void **p, size_t bytes, bool spare)
 {
     *p = nullptr;
     try {
@@ -253,7 +256,7 @@ hub_status Workspace::alloc(void **p, size_t bytes)
         return no_memory(bytes, "host allocation failed");
     }
     bool external = false;
-    const hub_status r = ws_alloc(p, bytes, owner, external);
+    const hub_status r = ws_alloc(p, bytes, owner, spare, external);
     ptrs.back() = *p;
     if (r != HUB_OK || !external || owner == st) return r;
     // what used the block before is queued on the owner's stream
