@@ -1426,8 +1426,11 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
                 if (!chunked_shape_ok<T>(tb, qpl) || chunked_rows<T>(s, tb) <= 0) continue;
                 if (!launchable(chunk_blocks(s->spin[0].count, s->spin[1].count, tb, qpl), 1024)) continue;
                 if (xc == 0 && (columns || ragged)) continue;
-                // not worth timing beside the two-pass shapes where rows of H_dn are long (2x9
-                // ladder FP64, 14 entries: 55 to 58 ms against 44; tuning 2.0 s with them, 0.9 without)
+                // not worth timing beside the two-pass shapes where rows of H_dn are long: best
+                // one-pass over best two-pass time, FP64, 1.23 at 14.3 entries a row (2x9
+                // ladder, 54.6 and 44.5 ms), 1.31 at 18.8 and 1.46 at 28.2 (random graphs, 18
+                // sites), 1.23 at 22.7 (190 columns); 0.97 to 1.39 from 2 to 11 entries.
+                // (Tuning the ladder 2.0 s with them, 0.9 without.)
                 if (xc == 0 && split && s->spin[1].nnz >= 12 * s->spin[1].count) continue;
                 // two passes: where a tile is not staged whole above, or no one-pass shape exists
                 if (xc == 2 && !(split ? !column_fits<T>(s, tb, epi) : v.empty() || (ragged && !columns))) continue;
