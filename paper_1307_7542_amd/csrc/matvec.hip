@@ -356,11 +356,11 @@ __device__ __forceinline__ T epi_w(const LzEpi<T> &E, const EpiCoef<T> &c, T o, 
 }
 
 // ---- whole columns in LDS, four consecutive rows per lane -----------------
-// One workgroup per TB output columns; lane q owns rows 4q .. 4q+3 (count_up %
-// 4 == 0): the column staging, the H_dn neighbour reads and the stores are
-// 16-byte (FP32) or 2 x 16-byte (FP64) accesses, and the four rows' sliced-ELL
-// entries k are four consecutive lanes of the slice, read with one 16-byte
-// load.  XC: XCD-contiguous tile order (workgroup i on XCD i mod 8 takes the
+// One workgroup per TB output columns; lane q owns rows 4q .. 4q+3 (RAG: count_up %
+// 4 != 0, the last quad is shorter and the others start at any element): the column
+// staging, the H_dn neighbour reads and the stores are 16-byte (FP32) or 2 x 16-byte
+// (FP64) accesses, and the four rows' sliced-ELL entries k are four consecutive lanes
+// of the slice, read with one 16-byte load.  XC: XCD-contiguous tile order (workgroup i on XCD i mod 8 takes the
 // i-th tile of that XCD's range) or plain launch order.  EPI: the first
 // Lanczos update, each group of 64 lane-quads (256 rows) summed by one
 // wavefront in a fixed order, then the groups of a column in increasing order,
@@ -1262,8 +1262,6 @@ hub_status launch_rows(const hub_sector *s, const MvArgs<T> &A, hipStream_t st, 
     return HUB_OK;
 }
 
-// one row per lane: two columns per workgroup when they fit in half of the LDS;
-// CSR rows when a column does not fit
 // One row per lane in the shape the column size allows (two columns per
 // workgroup when both fit in half the LDS), else CSR rows; E: the fused Lanczos
 // update (its reduction array takes 8 KB of the LDS; no CSR fallback).
@@ -1329,9 +1327,12 @@ hub_status launch_sched(const hub_sector *s, MvArgs<T> A, hipStream_t st, const 
 
 // ---- tuner ----------------------------------------------------------------
 
-// Times each candidate launch in two interleaved rounds (one warm-up launch,
-// then 5 timed launches, or 2 when one launch takes over 4 ms) and returns the
-// index of the fastest (its better round), with its time in ms.
+// Times each candidate launch (one warm-up launch, then 5 timed launches, or 1 when
+// one takes over 0.2 ms), then once more those within a quarter of the fastest (5
+// launches, or 2 above 4 ms), and returns the index of the fastest of these (its
+// better round), with its time in ms.  (Two full rounds of 5 took 1.4 to 2.8 times as
+// long on sectors of 14 to 22 sites and gained nothing: 2x9 ladder FP64 939 against
+// 644 ms, 15-site ring FP64 45.5 against 23.7.)
 template <typename F>
 hub_status time_candidates(hipStream_t st, int n, F launch, int &best, float &best_ms)
 {
@@ -1347,22 +1348,26 @@ hub_status time_candidates(hipStream_t st, int n, F launch, int &best, float &be
         }
     } ev{e0, e1};
     std::vector<float> ms((size_t)n, 1e30f);
-    for (int round = 0; round < 2; ++round)
-        for (int c = 0; c < n; ++c) {
-            HUB_HIP(hipEventRecord(e0, st));
-            HUB_TRY(launch(c));
-            HUB_HIP(hipEventRecord(e1, st));
-            HUB_HIP(hipEventSynchronize(e1));
-            float one = 0.f;
-            HUB_HIP(hipEventElapsedTime(&one, e0, e1));
-            const int reps = one > 4.0f ? 2 : 5;
-            HUB_HIP(hipEventRecord(e0, st));
-            for (int r = 0; r < reps; ++r) HUB_TRY(launch(c));
-            HUB_HIP(hipEventRecord(e1, st));
-            HUB_HIP(hipEventSynchronize(e1));
-            HUB_HIP(hipEventElapsedTime(&one, e0, e1));
-            ms[(size_t)c] = std::min(ms[(size_t)c], one / (float)reps);
-        }
+    auto timed = [&](int c, int reps, float &each) -> hub_status {
+        HUB_HIP(hipEventRecord(e0, st));
+        for (int r = 0; r < reps; ++r) HUB_TRY(launch(c));
+        HUB_HIP(hipEventRecord(e1, st));
+        HUB_HIP(hipEventSynchronize(e1));
+        HUB_HIP(hipEventElapsedTime(&each, e0, e1));
+        each /= (float)reps;
+        return HUB_OK;
+    };
+    for (int c = 0; c < n; ++c) {
+        float one = 0.f;
+        HUB_TRY(timed(c, 1, one));
+        HUB_TRY(timed(c, one > 0.2f ? 1 : 5, ms[(size_t)c]));
+    }
+    const float cut = 1.25f * *std::min_element(ms.begin(), ms.end());
+    for (int c = 0; c < n; ++c) {
+        float again = 1e30f;
+        if (ms[(size_t)c] <= cut) HUB_TRY(timed(c, ms[(size_t)c] > 4.0f ? 2 : 5, again));
+        ms[(size_t)c] = ms[(size_t)c] <= cut ? std::min(ms[(size_t)c], again) : 1e30f;
+    }
     best = (int)(std::min_element(ms.begin(), ms.end()) - ms.begin());
     best_ms = ms[(size_t)best];
     return HUB_OK;
