@@ -267,15 +267,18 @@ def k0_timing(hub, torch, model):
 
 
 
-def kernel_name(sched, es):
-    """Name of the product kernels a tuned schedule launches."""
+def kernel_name(sched, es, count_up):
+    """Names of the product kernels a tuned schedule launches, joined by " + "."""
     T = "double" if es == 8 else "float"
     split = sched["order"] == 2  # the H_dn term in a pass of its own
-    first = f"k_dn_rows<{T}>, " if split else ""
+    first = f"k_dn_rows<{T}> + " if split else ""
+    # fused Lanczos update, starts from k_dn_rows, columns of odd length
+    tail = f"false, {str(split).lower()}, {str(count_up % 4 != 0).lower()}"
     if sched["family"] == 1:
-        return f"{first}k_kron_quad<{T}, {sched['tile_cols']}, {sched['block']}, {sched['order'] == 1}, false>"
+        xcd = str(sched["order"] == 1).lower()
+        return f"{first}k_kron_quad<{T}, {sched['tile_cols']}, {sched['block']}, {xcd}, {tail}>"
     if sched["family"] == 2:
-        return f"{first}k_kron_chunked_parts<{T}, 1024, {sched['quads_per_lane']}, {sched['tile_cols']}, false>"
+        return f"{first}k_kron_chunked_parts<{T}, 1024, {sched['quads_per_lane']}, {sched['tile_cols']}, {tail}>"
     return {3: "k_kron_fused", 4: "k_kron_csr"}.get(sched["family"], "?")
 
 
@@ -312,7 +315,7 @@ def headline_products(hub, torch, model, steps, warmup):
         out[key] = {"wall_s": wall, "ms_per_product": wall / steps * 1e3, "avg_launch_ms": avg,
                     "min_launch_ms": min(ms), "max_launch_ms": max(ms), "bytes_per_launch": b,
                     "GBps": b / avg / 1e6, "frac": b / avg / 1e6 / HBM_PEAK_GBPS, "tune_s": tune_s,
-                    "schedule": sched, "kernel": kernel_name(sched, es)}
+                    "schedule": sched, "kernel": kernel_name(sched, es, sec.count_up)}
         del x, y
         torch.cuda.empty_cache()
     sec.close()
@@ -536,19 +539,19 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def committed_traffic(kernel):
-    """HBM bytes per launch of `kernel` from the committed counter summary, only
-    while the product source is unchanged since the counters were taken."""
+def committed_traffic(kernels):
+    """HBM bytes per launch of the product's kernels from the committed counter summary,
+    only while the product source is unchanged since the counters were taken."""
     try:
         import hashlib
         with open(os.path.join(ROOT, "profiles", "product_counters.json")) as f:
             cj = json.load(f)
         with open(os.path.join(ROOT, "paper_1307_7542_amd", "csrc", "matvec.hip"), "rb") as f:
             sha = hashlib.sha256(f.read()).hexdigest()
-        ent = cj["kernels"].get(f"{HEADLINE}:{kernel}")
-        if not ent or cj.get("matvec_source_sha256") != sha:
+        ent = [cj["kernels"].get(f"{HEADLINE}:{k}") for k in kernels.split(" + ")]
+        if not all(ent) or cj.get("matvec_source_sha256") != sha:
             return None
-        return {"bytes": ent["traffic_bytes"],
+        return {"bytes": sum(e["traffic_bytes"] for e in ent),
                 "note": "FETCH_SIZE x %.3f + WRITE_SIZE x %.3f per launch (copy-kernel calibration), counters "
                         "from %s" % (cj["calibration"]["fetch_scale"], cj["calibration"]["write_scale"],
                                      cj.get("command", "?"))}

@@ -430,10 +430,11 @@ hub_status ground_state(const hub_sector *s, const hub_lanczos_opts *o, double *
     // host waits only for that copy.  A step finished after convergence is
     // discarded (its coefficients are never used).
     //
-    // On the plain path (no reorthogonalisation, no reprojection) the
-    // normalisation kernel of step j itself stores alpha_j and beta_{j+1} into
-    // the pinned buffer and then publishes j + 1 in a pinned counter, so a check
-    // waits on host memory only: no copy and no event between the kernels.
+    // On the plain path (no reorthogonalisation, no reprojection) a kernel stores
+    // alpha_j and beta_{j+1} into the pinned buffer and then publishes j + 1 in a
+    // pinned counter, so a check waits on host memory only: no copy and no event
+    // between the kernels.  (The kernel that forms beta_{j+1}: the next product where
+    // the vectors stay unnormalised, else the normalisation of step j.)
     double *hpin = nullptr;  // pinned copy of dscal[0 .. 2 kmax + 1)
     int *hflag = nullptr;    // pinned count of published steps
     HUB_HIP(hipHostMalloc((void **)&hpin, sizeof(double) * (size_t)(2 * kmax + 1),
