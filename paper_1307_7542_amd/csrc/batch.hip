@@ -137,8 +137,9 @@ __device__ __forceinline__ V ld_uniform(const V *p, int i)
 // Every element is formed as in the single-sector product (the H_dn entries in
 // CSR order, then the diagonal, then the H_up entries in sliced-ELL order, one
 // fused multiply-add each): the two agree bit for bit.
-// Bound: the gathers' traffic between L1 and L2, the vector once per entry of
-// H_dn.  64 impurities of 20 x 20 to 924 x 924: one row per lane 62.6 us FP32
+// Bound: the gathers between L1 and L2, the vector once per entry of H_dn, at the
+// latency of items of a few columns (27 lines in flight per CU in FP32, 9 TB/s, where
+// k_dn_rows of the single-sector product has 72 and 16).  64 impurities of 20 x 20 to 924 x 924: one row per lane 62.6 us FP32
 // (FP64 80); four rows 51 (88); every sector's items on one or two XCDs instead
 // of all eight (build_items) 43 (68); a wavefront to a group 40 (66).
 // SEL (the Lanczos step): x = u_k and y = w from the pointer table at the device

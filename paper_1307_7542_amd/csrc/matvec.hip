@@ -841,11 +841,11 @@ __global__ __launch_bounds__(BS) void k_kron_fused(MvArgs<T> A, const int32_t *_
 // each other in time, and of the 14 of a 2x9-ladder column 3.9 instead of 6.1
 // miss the L2 (least-recently-used model): 24.5 -> 21.6 ms FP64; 4x4 torus FP32
 // 572 -> 560 us.
-// Bound: lines in flight per CU (about 90 of 128 bytes, 415 cycles each by the
-// counters, so 15 to 20 TB/s over the chip).  Segments of 256 and 512 bytes hit
-// the L2 more often (4x4 torus FP64: 18 and 28 instead of 44 million reads from
-// beyond it) and are no faster.  In a product: 4x4 torus FP32 0.56 ms,
-// 2x9 ladder 21.6 / 10.9 ms (FP64 / FP32).  Alone, in ascending order: 4x4 torus
+// Bound: lines of 128 bytes in flight per CU, by the counters 72 at 355 cycles each
+// on the 4x4 torus (16 TB/s over the chip) and 82 at 486 on the 2x9 ladder (13
+// TB/s).  Segments of 256 and 512 bytes hit the L2 more often (4x4 torus FP64: 18
+// and 28 instead of 44 million reads from beyond it) and are no faster.  In a
+// product: 4x4 torus FP32 0.56 ms, 2x9 ladder 21.6 / 10.9 ms (FP64 / FP32).  Alone, in ascending order: 4x4 torus
 // 0.89 / 0.50 ms; re-reading the last entry to fill up the batches of eight
 // instead of the tail below, 1.12 / 0.58 ms.
 template <typename T>
@@ -1389,17 +1389,20 @@ bool split_range(const hub_sector *s)
     return (double)s->dim * sizeof(T) > 128.0 * 1024 * 1024 && s->spin[0].count >= 64 * kDnRows<T>;
 }
 
-// Lanes of a workgroup for cd columns of cu rows: up to 1024 rows no more wavefronts
-// than a column fills (the others stage nothing and only hold registers), in the
-// XCDs' order and in one pass, the best of all shapes there.  FP64: 25 x 480700 637
+// Columns and lanes of a workgroup for cd columns of cu rows: up to 1024 rows no
+// more wavefronts than a column fills (the others stage nothing and only hold
+// registers), in the XCDs' order and in one pass, the best of all shapes there.  FP64: 25 x 480700 637
 // us with 64 lanes, 1209 with 256, 2517 with 512; 276 x 42504 98, 102, 175; 455 x
 // 6435 52, 43, 62; 816 x 48620 378, 312, 360; 1140 x 184756 2.77, 2.41, 2.40 ms; 231 x
 // 497420 (919 MB) 1.55 ms in one pass, 1.73 in two.  With few columns, when the chip
 // is not full, idle wavefronts cost nothing and four share the work around the rows
-// (a Lanczos step of 20 x 20 16.4 us with 64 lanes, 16.0 with 256; 252 x 252 15.5, 15.3).
-bool block_suits(int64_t cu, int64_t cd, int bs)
+// (a Lanczos step of 20 x 20 16.4 us with 64 lanes, 16.0 with 256; 252 x 252 15.5,
+// 15.3); and a workgroup keeps to one column then (252 x 252 14.7 us a step, 16.3 with
+// two, 18.3 with three; 792 x 792 20.6, 20.8, 23.8).
+bool tile_suits(int64_t cu, int64_t cd, int tb, int bs)
 {
     const bool few = cd <= 512;
+    if (few && tb > 1) return false;
     if (bs == 64) return cu <= 512 && !few;
     if (bs == 256) return (cu > 256 || few) && cu <= 1024;
     return cu > 1024;
@@ -1414,7 +1417,7 @@ std::vector<Sched> candidates(const hub_sector *s, bool epi)
     for (int tb = 1; tb <= 3 && column_fits<T>(s, tb, epi); ++tb)
         for (int bs : {64, 256, 512, 1024})
             for (int xc : {0, 1, 2}) {
-                if (!block_suits(cu, s->spin[1].count, bs) || (cu <= 1024 && xc != 1)) continue;
+                if (!tile_suits(cu, s->spin[1].count, tb, bs) || (cu <= 1024 && xc != 1)) continue;
                 if (xc == 2 && !split) continue;
                 if (!quad_shape(ragged, tb, bs, xc)) continue;
                 if (!launchable(quad_blocks(s->spin[1].count, tb, xc), bs)) continue;

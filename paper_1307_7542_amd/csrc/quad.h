@@ -132,8 +132,9 @@ __device__ __forceinline__ void put_quad(T *xs, const Q4<T> (&v)[TB], int q, int
 
 // acc[r][t] += the H_up entries of a quad's four rows (entry k of the four in
 // e4[16 k]), two entry columns at a time, the next two loaded meanwhile.  Bound
-// by the LDS: two reads an entry, 76 % of the cycles on the 4x4 torus (FP32, two
-// columns; without the next entries' loads 1.24 instead of 1.20 ms a product).
+// by the LDS: two reads an entry, 62 % of a CU's busy cycles on the 4x4 torus (FP32,
+// two columns), half of them bank conflicts; without the next entries' loads 1.24
+// instead of 1.20 ms a product.
 template <typename T, int TB>
 __device__ __forceinline__ void up_quad(T (&acc)[4][TB], const T *xs, const T *tab, const uint4 *__restrict__ e4,
                                         int len)

@@ -232,7 +232,8 @@ __device__ __forceinline__ T k0_diag(const K0Args<T> &A, uint32_t both)
 // (coalesced, entry-major) are read once for all of them, hop (r2, s) of member m
 // coming from member (m - s) mod q at row r2, with the sign of the wrap around the
 // cycle (q = L; the few shorter cycles look member and sign up in a table).
-// Bound by the LDS gathers where staged.  DN: the H_dn term is already in y (its
+// Bound by latency: a hop's word and coefficient, then the gathers that wait for
+// them, at 15 lines in flight per CU (the LDS is busy 17 % of the cycles).  DN: the H_dn term is already in y (its
 // own pass, k_dn_rows); else it is gathered here.
 // k = 0 block of the 16-site ring (10.4e6 states, FP64), warm: 557 us with one
 // member at a time, two byte tables in LDS and row-major hop lists; 199 us with
